@@ -194,10 +194,10 @@ fio_status fio_bf_apply_adj(fio_bf_t bf, const void *X, long ldx, void *Y, long 
  * two of nrhs, all counts >= 64 in one bucket) and precision use it.  Candidates: for dim = 2
  * the column chunk of the workgroups (8 or 16) times the reduction split of the U and V^*
  * steps (4, 8, 16 dividing the partner count); for dim = 1 (q = 9) the number of transfer
- * levels per fused pass (1, 2, 3), with 3 levels the first leaf factor folded into the first pass
- * or run as its own kernel, and for FIO_PREC_SPLIT_FP16 each of these with the transfer passes
- * on the matrix cores (split FP16) or on the vector units (FP32); the built-in default is always
- * a candidate (fio_tile describes a candidate).  Every candidate applies the same operator
+ * levels per fused pass (1, 2, 3), with 3 levels the leaf factors folded into the passes
+ * or run as their own kernels, and for FIO_PREC_SPLIT_FP16 each of these with the transfer passes
+ * on the matrix cores (split FP16) or on the vector units (FP32); the built-in default (whole sides
+ * per pass, on the vector units) is always a candidate (fio_tile describes a candidate).  Every candidate applies the same operator
  * (results differ at most by rounding order, and the FP32 engine is the more accurate one of a
  * split-precision request).  Y (ldy >= N)
  * receives the last apply; `ws` as for fio_bf_apply (NULL: the handle's workspace).  When
@@ -222,11 +222,12 @@ typedef struct {
     int kc;        /* dim 2: column chunk of the workgroups, 0, 8 or 16 */
     int nsplit;    /* dim 2: reduction split of the U and V^* steps, 0 or a power of two dividing the
                       partner count, at most 16 */
-    int kmax;      /* dim 1: transfer levels per fused pass, 0 (as many as the LDS tile holds) or 1..3 */
-    int leaf_sep;  /* dim 1: 1 runs the first leaf factor as its own kernel instead of folding it into a
-                      first pass of 3 levels */
-    int valu;      /* dim 1, FIO_PREC_SPLIT_FP16 only: 1 runs the transfer passes as FP32 structured
-                      passes on the vector units instead of split FP16 on the matrix cores */
+    int kmax;      /* dim 1: transfer levels per fused pass, 0 (as many as a pass holds) or 1..3 */
+    int leaf_sep;  /* dim 1: 1 runs the leaf factors as their own kernels instead of folding them into
+                      the passes next to them */
+    int valu;      /* dim 1, FIO_PREC_SPLIT_FP16 only, with kmax > 0: 1 runs the transfer passes in FP32 on
+                      the vector units instead of split FP16 on the matrix cores (kmax = 0 runs the
+                      vector units on factors built by the library, the matrix cores on imported ones) */
 } fio_tile;
 
 /* fio_bf_set_tile with every field of fio_tile; FIO_ERR_ARG for values outside the ranges above
@@ -268,10 +269,9 @@ fio_status fio_permute2d(long n, int to_internal, const void *X, long ldx, void 
  * thread-safe with respect to concurrent applies. */
 void fio_set_fused(int on);
 
-/* With fused passes on: on != 0 (default) folds the first leaf factor of an apply (V^[L']
- * forward, U^[L']* adjoint) into its first pass of transfer factors when that pass holds 3
- * levels (FP64 and FP32 structured factors, 2^L' >= 64; the pass then reads the input vectors
- * instead of the leaf coefficients); on == 0 runs the leaf factor as its own kernel.  Both give
+/* With fused passes on: on != 0 (default) folds the leaf factors of an apply into the passes of
+ * transfer factors next to them (factors built by the library; with q other than 9 the first leaf
+ * factor only, into a first pass of 3 levels, 2^L' >= 64); on == 0 runs them as their own kernels.  Both give
  * bitwise identical results.  Not thread-safe with respect to concurrent applies. */
 void fio_set_leaf_fused(int on);
 

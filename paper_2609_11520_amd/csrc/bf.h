@@ -41,6 +41,9 @@ struct fio_bf_s {
     bool structured = false;
     fio::DevBuf tw64, tw32;
     double Pchild[2 * 16 * 16] = {};
+    // q = 9: the diagonals of the structured leaf, transfer and middle factors (bf_side.h) instead of
+    // the twiddles above
+    fio::DevBuf side64, side32;
     fio::DevBuf adj64, adj32;          // 2D: conjugate-transposed factor copies read by the adjoint
     fio::Amp amp;                      // amplitude of the kernel (copied from the descriptor)
     fio::DevBuf ws;                    // handle-owned workspace (ws == NULL in the applies)

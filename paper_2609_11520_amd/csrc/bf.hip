@@ -95,9 +95,6 @@ size_t bf_coef_elems(const fio_bf_s *bf, int nrhs) { return (size_t)bf->N * bf->
 // the entry is rounded once.  Lagrange values are taken in the reference coordinate u of the
 // point in its interpolation box, where p_t(u) is the same for every box.
 
-// c(x) = c0 + c1 sin(2 pi x)
-__device__ dd c_dd(const Geo &g, dd x) { return dd_add(dd_of(g.c0), dd_mul_d(dd_sinpi(dd_ldexp(x, 2.0)), g.c1)); }
-
 __device__ __forceinline__ double2 scaled(double2 e, double v) { return zc(e.x * v, e.y * v); }
 
 // V[sigma][tau][j][s] = exp(2 pi i (y + sgn c(y)) (xi_s - gamma_j)) q_j(xi_s)   (|xi| = sgn xi on the box)
@@ -145,17 +142,6 @@ __global__ void gen_C(Geo g, Nodes tn, int l, double2 *out) {
 }
 
 // M[p][i][j] = k(z_tau,i, gamma_sigma,j), p = tau 2^h + sigma
-// a(z, gamma) of Section 5.1 (1 when the amplitude has no terms)
-__device__ double amp_at(const Amp &a, double z, double gam, double N) {
-    if (a.m == 0) return 1.0;
-    double s = 0.0;
-    for (int k = 0; k < a.m; ++k) {
-        const double dx = z - a.x[k], dxi = (gam - a.xi[k]) / N;
-        s += exp(-(dx * dx + dxi * dxi) / a.s2);
-    }
-    return s;
-}
-
 __global__ void gen_M(Geo g, Nodes tn, Amp am, double2 *out) {
     const int q = g.q;
     size_t n = (size_t)g.N * q * q;
@@ -316,10 +302,15 @@ static void bf_generate(fio_bf_s *bf, hipStream_t s) {
     // structured transfer twiddles and the shared Lagrange matrices
     if (bf->nl > 0) {
         const size_t ntw = (size_t)(bf->N / 2) * 8 * bf->q;
-        bf->tw64.alloc(2 * bf->nl * ntw * sizeof(double2));
-        for (int lev = 0; lev < bf->nl; ++lev) {
-            gen_TW_B<<<grid1d(ntw, T), T, 0, s>>>(g, tn, bf->h + lev, bf->tw64.as<double2>() + bf_tw_off(bf, false, lev));
-            gen_TW_C<<<grid1d(ntw, T), T, 0, s>>>(g, tn, bf->h + lev, bf->tw64.as<double2>() + bf_tw_off(bf, true, lev));
+        if (bf->q == kSideQ) {
+            side_generate(bf, s);
+        } else {
+            bf->tw64.alloc(2 * bf->nl * ntw * sizeof(double2));
+            double2 *tw = bf->tw64.as<double2>();
+            for (int lev = 0; lev < bf->nl; ++lev) {
+                gen_TW_B<<<grid1d(ntw, T), T, 0, s>>>(g, tn, bf->h + lev, tw + bf_tw_off(bf, false, lev));
+                gen_TW_C<<<grid1d(ntw, T), T, 0, s>>>(g, tn, bf->h + lev, tw + bf_tw_off(bf, true, lev));
+            }
         }
         DevBuf pd(2 * bf->q * bf->q * sizeof(double));
         gen_Pchild<<<1, 2 * bf->q * bf->q, 0, s>>>(tn, pd.as<double>());
@@ -341,7 +332,9 @@ static void bf_make_copies(fio_bf_s *bf, hipStream_t s) {
         bf->f32.alloc(bf->total * sizeof(float2));
         cvt_f64_f32<<<grid1d(bf->total, 256), 256, 0, s>>>(bf->f64.as<double2>(), bf->f32.as<float2>(),
                                                          bf->total);
-        if (bf->structured) {
+        if (side_built(bf)) {
+            side_make_f32(bf, s);
+        } else if (bf->structured) {
             const size_t ntw = 2 * bf->nl * (size_t)(bf->N / 2) * 8 * bf->q;
             bf->tw32.alloc(ntw * sizeof(float2));
             cvt_f64_f32<<<grid1d(ntw, 256), 256, 0, s>>>(bf->tw64.as<double2>(), bf->tw32.as<float2>(), ntw);

@@ -4,6 +4,8 @@
 #include <type_traits>
 
 #include "bf.h"
+#include "bf_side.h"
+#include "ddmath.h"
 #include "timing.h"
 
 namespace fio {
@@ -36,6 +38,22 @@ struct Geo {
 
 inline Geo geo_of(const fio_bf_s *bf) {
     return Geo{bf->N, bf->L, bf->h, bf->Lp, bf->q, bf->b, bf->nsl, bf->desc.c0, bf->desc.c1};
+}
+
+// c(x) = c0 + c1 sin(2 pi x)
+__device__ __forceinline__ dd c_dd(const Geo &g, dd x) {
+    return dd_add(dd_of(g.c0), dd_mul_d(dd_sinpi(dd_ldexp(x, 2.0)), g.c1));
+}
+
+// a(z, gamma) of Section 5.1 (1 when the amplitude has no terms)
+__device__ __forceinline__ double amp_at(const Amp &a, double z, double gam, double N) {
+    if (a.m == 0) return 1.0;
+    double s = 0.0;
+    for (int k = 0; k < a.m; ++k) {
+        const double dx = z - a.x[k], dxi = (gam - a.xi[k]) / N;
+        s += exp(-(dx * dx + dxi * dxi) / a.s2);
+    }
+    return s;
 }
 
 // ---------------------------------------------------------------------------
@@ -1035,8 +1053,19 @@ static void apply_q(fio_bf_s *bf, bool adj, const double2 *X, long ldx, double2 
         // run the transfer passes on the vector units in FP32
         const fio_prec pr = f64 ? FIO_PREC_FP64 : (split ? FIO_PREC_SPLIT_FP16 : FIO_PREC_FP32);
         const TileCfg tc = bf_tile(bf, adj, pr, nrhs);
-        if (tc.kmax > 0 && tc.kmax < kmax) kmax = tc.kmax;
         leaf_sep = tc.leaf_sep != 0;
+        // GPU-built q = 9 factors: whole-side passes (bf_side.h).  In split precision they are the
+        // default too (FP32 on the vector units): faster than the matrix-core passes at every
+        // width (see k_side_pass) and more exact; a pinned pass length without `valu` selects
+        // the matrix cores.
+        if constexpr (Q == kSideQ) {
+            if (fused && side_built(bf) && (!split || tc.valu || tc.kmax == 0)) {
+                side_apply<T>(bf, adj, X, ldx, Y, ldy, nrhs, c0, c1, tc.kmax, leaf_sep || leaf_fused_disabled(), Ysub,
+                              ldsub, s);
+                return;
+            }
+        }
+        if (tc.kmax > 0 && tc.kmax < kmax) kmax = tc.kmax;
         if (split && tc.valu) split = false;
     }
     auto pass = [&](bool a, bool cside, int lo, int hi, bool epi, bool leaf = false) {
@@ -1062,50 +1091,52 @@ static void apply_q(fio_bf_s *bf, bool adj, const double2 *X, long ldx, double2 
                     return;
                 }
             }
-            if (bf->structured) {
-                StructArgs<T, Q> sa;
-                const cpx<T> *TWb = f64 ? reinterpret_cast<const cpx<T> *>(bf->tw64.p)
-                                        : reinterpret_cast<const cpx<T> *>(bf->tw32.p);
-                for (int jj = 0; jj < 4; ++jj) sa.TW[jj] = nullptr;
-                for (int jj = 0; jj < kl; ++jj)
-                    sa.TW[jj] = TWb + bf_tw_off(bf, cside, cside ? hi - 1 - jj : lo + jj);
-                sa.M = F + bf->offM;
-                sa.G0 = cside ? (1L << (bf->h + hi - 1)) : (1L << (bf->L - (bf->h + lo) - 1));
-                sa.in = cur;
-                sa.out = nxt;
-                sa.nrhs = nrhs;
-                sa.cside = cside ? 1 : 0;
-                sa.V = F + (a ? bf->offU : bf->offV);
-                sa.X = X;
-                sa.ldx = ldx;
-                for (int c = 0; c < 2; ++c)
-                    for (int i = 0; i < Q; ++i)
-                        for (int t = 0; t < Q; ++t) {
-                            sa.P[c][i][t] = (T)bf->Pchild[(c * Q + i) * Q + t];
-                            sa.PT[c][t][i] = sa.P[c][i][t];
+            if constexpr (Q != kSideQ) {
+                if (bf->structured) {
+                    StructArgs<T, Q> sa;
+                    const cpx<T> *TWb = f64 ? reinterpret_cast<const cpx<T> *>(bf->tw64.p)
+                                            : reinterpret_cast<const cpx<T> *>(bf->tw32.p);
+                    for (int jj = 0; jj < 4; ++jj) sa.TW[jj] = nullptr;
+                    for (int jj = 0; jj < kl; ++jj)
+                        sa.TW[jj] = TWb + bf_tw_off(bf, cside, cside ? hi - 1 - jj : lo + jj);
+                    sa.M = F + bf->offM;
+                    sa.G0 = cside ? (1L << (bf->h + hi - 1)) : (1L << (bf->L - (bf->h + lo) - 1));
+                    sa.in = cur;
+                    sa.out = nxt;
+                    sa.nrhs = nrhs;
+                    sa.cside = cside ? 1 : 0;
+                    sa.V = F + (a ? bf->offU : bf->offV);
+                    sa.X = X;
+                    sa.ldx = ldx;
+                    for (int c = 0; c < 2; ++c)
+                        for (int i = 0; i < Q; ++i)
+                            for (int t = 0; t < Q; ++t) {
+                                sa.P[c][i][t] = (T)bf->Pchild[(c * Q + i) * Q + t];
+                                sa.PT[c][t][i] = sa.P[c][i][t];
+                            }
+                    // symmetric and antisymmetric row combinations of G_0 = P_0^T, in double
+                    // precision before rounding to T: G_0(r, t) = P_0(t, r)
+                    for (int t = 0; t < Q; ++t) {
+                        const double *p0 = bf->Pchild;
+                        for (int r = 0; r < (Q + 1) / 2; ++r) {
+                            const double g = p0[t * Q + r], gm = p0[t * Q + (Q - 1 - r)];
+                            sa.SD[t][r] = (T)(2 * r + 1 == Q ? g : 0.5 * (g + gm));
                         }
-                // symmetric and antisymmetric row combinations of G_0 = P_0^T, in double
-                // precision before rounding to T: G_0(r, t) = P_0(t, r)
-                for (int t = 0; t < Q; ++t) {
-                    const double *p0 = bf->Pchild;
-                    for (int r = 0; r < (Q + 1) / 2; ++r) {
-                        const double g = p0[t * Q + r], gm = p0[t * Q + (Q - 1 - r)];
-                        sa.SD[t][r] = (T)(2 * r + 1 == Q ? g : 0.5 * (g + gm));
+                        for (int r = 0; r < Q / 2; ++r) {
+                            const double g = p0[t * Q + r], gm = p0[t * Q + (Q - 1 - r)];
+                            sa.SD[t][(Q + 1) / 2 + r] = (T)(0.5 * (g - gm));
+                        }
                     }
-                    for (int r = 0; r < Q / 2; ++r) {
-                        const double g = p0[t * Q + r], gm = p0[t * Q + (Q - 1 - r)];
-                        sa.SD[t][(Q + 1) / 2 + r] = (T)(0.5 * (g - gm));
+                    if (leaf) {
+                        FIO_TIMED(f64 ? "bf_struct_leaf_f64" : "bf_struct_leaf_f32", s);
+                        run_struct_leaf<T, Q>(sa, a, epi, bf->N, s);
+                    } else {
+                        FIO_TIMED(f64 ? "bf_struct_f64" : "bf_struct_f32", s);
+                        run_struct<T, Q>(sa, kl, a, epi, bf->N, s);
                     }
+                    std::swap(cur, nxt);
+                    return;
                 }
-                if (leaf) {
-                    FIO_TIMED(f64 ? "bf_struct_leaf_f64" : "bf_struct_leaf_f32", s);
-                    run_struct_leaf<T, Q>(sa, a, epi, bf->N, s);
-                } else {
-                    FIO_TIMED(f64 ? "bf_struct_f64" : "bf_struct_f32", s);
-                    run_struct<T, Q>(sa, kl, a, epi, bf->N, s);
-                }
-                std::swap(cur, nxt);
-                return;
             }
             FusedArgs<T> fa;
             for (int j = 0; j < 4; ++j) fa.A[j] = nullptr;
@@ -1139,14 +1170,13 @@ static void apply_q(fio_bf_s *bf, bool adj, const double2 *X, long ldx, double2 
         }
         std::swap(cur, nxt);
     };
+    // The first leaf factor folds into a first pass of 3 levels of structured factors (one leaf box per
+    // wave) when its workgroups can be grouped by 8 per XCD (2^L' / 8 % 8 == 0).
+    const bool leaf_fused = Q != kSideQ && leaf_foldable<T, Q>() && fused && bf->structured && !leaf_fused_disabled() &&
+                            !leaf_sep && (kmax < bf->nl ? kmax : bf->nl) == 3 && bf->Lp >= 6;
     const bool tiled = ((1L << bf->Lp) % 4) == 0;
     const dim3 tgrid((unsigned)((1L << bf->Lp) / 4), (unsigned)((nrhs + 63) / 64));
     if (!adj) {
-        // V^[L'] folds into the first C pass when that pass is a structured one of 3 levels (one
-        // leaf box per wave) and its workgroups can be grouped by 8 per XCD (2^L' / 8 % 8 == 0)
-        const bool leaf_fused = leaf_foldable<T, Q>() && fused && bf->structured &&
-                                !leaf_fused_disabled() && !leaf_sep && (kmax < bf->nl ? kmax : bf->nl) == 3 &&
-                                bf->Lp >= 6;
         if (!leaf_fused) {
             FIO_TIMED(f64 ? "bf_leaf_in_f64" : "bf_leaf_in_f32", s);
             if (tiled)
@@ -1180,10 +1210,6 @@ static void apply_q(fio_bf_s *bf, bool adj, const double2 *X, long ldx, double2 
             k_leaf_out_fwd<T, Q><<<grid1d(((size_t)1 << bf->Lp) * nrhs, TB), TB, 0, s>>>(g, F + bf->offU, cur, Y,
                                                                                            ldy, nrhs, Ysub, ldsub);
     } else {
-        // U^[L']* folds into the first B* pass under the same conditions as V^[L'] forward
-        const bool leaf_fused = leaf_foldable<T, Q>() && fused && bf->structured &&
-                                !leaf_fused_disabled() && !leaf_sep && (kmax < bf->nl ? kmax : bf->nl) == 3 &&
-                                bf->Lp >= 6;
         if (!leaf_fused) {
             FIO_TIMED(f64 ? "bf_leaf_in_f64" : "bf_leaf_in_f32", s);
             if (tiled)
