@@ -276,10 +276,10 @@ void fio_set_fused(int on);
 void fio_set_leaf_fused(int on);
 
 /* Selects how the HSS construction (hss_build_from_samples, fio_hss_build) runs the node
- * algebra of a level: levels whose largest node has at least `rows` rows run every
- * reflector and pivot step as its own launch spread over many workgroups; smaller levels
- * run one workgroup per node.  Both give the same result up to rounding order.  rows <= 0
- * restores the default (256).  Not thread-safe with respect to concurrent constructions. */
+ * algebra of a level: levels whose largest node has at least `rows` rows run blocked
+ * reflectors and pivot steps spread over many workgroups; smaller levels run one workgroup
+ * per node.  Both give the same result up to rounding order.  rows <= 0 restores the
+ * default (64).  Not thread-safe with respect to concurrent constructions. */
 void fio_hss_set_big_node(int rows);
 
 /* The same choice for the basis elimination of hss_ulv_factor (QL of each node's basis and

@@ -469,7 +469,7 @@ def set_leaf_fused(on=True):
 
 def set_hss_big_node(rows):
     """HSS construction: levels whose largest node has >= rows rows use the multi-workgroup
-    reflector path (rows <= 0: default 256)."""
+    reflector path (rows <= 0: default 64)."""
     lib().fio_hss_set_big_node(int(rows))
 
 

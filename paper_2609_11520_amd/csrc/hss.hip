@@ -13,6 +13,7 @@
 //   QRCP takes the remaining column of largest norm (recomputed every step),
 //   lowest index on ties.
 #include "hss.h"
+#include "hss_qr.h"
 
 #include <cmath>
 
@@ -143,6 +144,7 @@ struct NodeArgs {
     double2 *Dres;         // residual block slot (m x m) of every node
     const size_t *doff;
     int root;              // 1: only H0 = Y Omega^+ (made Hermitian) into Dres
+    int lead;              // 1: the scratch of a node starts with A, 0: with Z
 };
 
 // Section 3.1 for one node (blockIdx.x), or the root solve of Section 3.2, in two phases
@@ -151,7 +153,7 @@ struct NodeArgs {
 //            U_tau), T = Y_tau Omega_tau^+ = Z1 R^{-*}; at the root H0 = (T + T^*)/2 and done;
 //   (batched GEMMs: X = T - U U^* T, then D-breve = X + U (X U)^*, in place in T)
 //   k_node_finish: out = (D-breve + D-breve^*)/2 and U_tau to its slot.
-// Scratch of a node (leading dimensions m): A (s x m), Z (m x s, T = its first m columns),
+// Scratch of a node (leading dimensions m): A (s x m, one-workgroup path only), Z (m x s, T = its first m columns),
 // U (m x m slot), P (m x m slot), X (m x m slot).
 __global__ void __launch_bounds__(1024) k_node_basis(NodeArgs a) {
     __shared__ double sh[16];
@@ -291,7 +293,7 @@ __global__ void __launch_bounds__(1024) k_node_finish(NodeArgs a) {
     if (m == 0) return;
     const int r = a.rank_out[node];
     double2 *out = a.Dres + a.doff[node];
-    const double2 *Z = a.scratch + a.stride * node + (size_t)s * m;   // D-breve in Z[:, 0:m]
+    const double2 *Z = a.scratch + a.stride * node + (size_t)a.lead * s * m;   // D-breve in Z[:, 0:m]
     const double2 *U = Z + (size_t)m * s;
     for (int e = tid; e < m * m; e += nt) {
         int i = e % m, j = e / m;
@@ -303,72 +305,160 @@ __global__ void __launch_bounds__(1024) k_node_finish(NodeArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// Large nodes (the upper levels of 2D trees, hundreds to thousands of rows, few nodes per
-// level): the same Section 3.1 steps as k_node_basis, one reflector or pivot step per
-// launch, each launch spread over many workgroups (grid.y = node, grid.x = column or row
-// chunk).  The reflector and pivot arithmetic is k_node_basis's; only the work split differs.
+// Levels of larger nodes: the same Section 3.1 steps as k_node_basis, spread over the card.  The QR of
+// Omega_tau^* runs on the s x 2 m array [Omega_tau^* | Y_tau^*], so that its blocked reflectors
+// (hss_qr.h) also form Q^* Y_tau^* = (Y_tau Q)^*; R X = the top m rows (X = T^*) is a blocked
+// triangular solve, the other rows are W^* = (Y_tau Gamma)^*; the QRCP of W runs one pivot per
+// pair of launches.  The reflector and pivot arithmetic is k_node_basis's.  The node data of a level
+// fits the caches, so that passes over it and the chain of dependent launches bound the steps: a
+// launch per reflector took 740 ms for the nine levels of 2D n = 64 (786 rows x 1582 samples at the
+// top), the blocks take 52 ms; the pivots (3 us each per pivot and update) are 22 ms of it.
 struct BigArgs {
     NodeArgs n;
-    double *tauA, *tauW;   // reflector scalars per node (kMaxM each)
+    double2 *B;            // [Omega^* | Y^*] per node (s x 2 m, stride bstride)
+    size_t bstride;
+    double *tauW;          // QRCP reflector scalars per node (ldt each)
+    int ldt;
     double *nrm;           // column norms per node (ldn each)
     int ldn;
     int *done;             // 1 once the node's QRCP has stopped
+    double2 *Rinv;         // inverses of the diagonal blocks of R, ntri blocks per node
+    int ntri;
 };
 
-// columns (or rows) per workgroup of the apply kernels, four lanes each: small workgroups, so
-// that the few large nodes of a level still spread over most of the GPU
-constexpr int kBigChunk = 16, kBigThreads = 4 * kBigChunk;
+constexpr int kTri = 32;   // block of the triangular solve
 
-__global__ void k_big_init(BigArgs b) {
+// 32 x 32 tiles of B <- [Omega^* | Y^*] (IN) or of Z = [T | W] (m x s) <- the right half of B, both
+// conjugate transposes
+template <bool IN> __global__ void __launch_bounds__(256) k_big_pack(BigArgs b) {
+    __shared__ double2 t[32][33];
     const NodeArgs &a = b.n;
-    const int node = blockIdx.y, m = a.msz[node], s = a.s;
-    if (m == 0) return;
-    double2 *A = a.scratch + a.stride * node, *Z = A + (size_t)s * m;
-    const double2 *Om = a.Om + a.moff[node], *Yt = a.Y + a.moff[node];
-    for (long e = blockIdx.x * (long)blockDim.x + threadIdx.x; e < (long)s * m; e += (long)gridDim.x * blockDim.x) {
-        const int i = (int)(e % s), j = (int)(e / s);
-        const double2 v = Om[j + (size_t)i * a.ldR];
-        A[e] = zc(v.x, -v.y);
-        const int zi = (int)(e % m), zj = (int)(e / m);
-        Z[e] = Yt[zi + (size_t)zj * a.ldR];
-    }
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
+    const int node = blockIdx.z, m = a.msz[node], s = a.s;
+    const int i0 = blockIdx.x * 32, j0 = blockIdx.y * 32;       // rows of B, columns of B (IN) or of its right half
+    const int ncol = IN ? 2 * m : m;
+    if (IN && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
         if (!a.root) a.rank_out[node] = 0;
         b.done[node] = 0;
     }
+    if (i0 >= s || j0 >= ncol) return;
+    double2 *B = b.B + b.bstride * node;
+    const int x = threadIdx.x & 31, y = threadIdx.x >> 5;
+    if (IN) {
+        for (int k = y; k < 32; k += 8) {
+            const int i = i0 + k, j = j0 + x;
+            if (i < s && j < ncol) {
+                const double2 v = (j < m ? a.Om + a.moff[node] + j : a.Y + a.moff[node] + (j - m))[(size_t)i * a.ldR];
+                t[k][x] = zc(v.x, -v.y);
+            }
+        }
+        __syncthreads();
+        for (int k = y; k < 32; k += 8)
+            if (i0 + x < s && j0 + k < ncol) B[i0 + x + (size_t)(j0 + k) * s] = t[x][k];
+    } else {
+        double2 *Z = a.scratch + a.stride * node;
+        for (int k = y; k < 32; k += 8)
+            if (i0 + x < s && j0 + k < m) {
+                const double2 v = B[i0 + x + (size_t)(m + j0 + k) * s];
+                t[k][x] = zc(v.x, -v.y);
+            }
+        __syncthreads();
+        for (int k = y; k < 32; k += 8)
+            if (j0 + x < m && i0 + k < s) Z[j0 + x + (size_t)(i0 + k) * m] = t[x][k];
+    }
 }
 
-// Householder vector of column j of A (rows j..s-1)
-__global__ void __launch_bounds__(1024) k_big_house_A(BigArgs b, int j) {
-    __shared__ double sh[16];
+// inverse of diagonal block blockIdx.x of R, one column per thread
+__global__ void __launch_bounds__(64) k_big_triinv(BigArgs b) {
+    __shared__ double2 R[kTri][kTri + 1], X[kTri][kTri + 1];
     const NodeArgs &a = b.n;
-    const int node = blockIdx.y, m = a.msz[node], s = a.s;
-    if (j >= m) return;
-    double2 *A = a.scratch + a.stride * node;
-    const double tau = wg_house(A + j + (size_t)j * s, s - j, sh, nullptr);
-    if (threadIdx.x == 0) b.tauA[(size_t)node * kMaxM + j] = tau;
+    const int node = blockIdx.y, m = a.msz[node], s = a.s, k0 = blockIdx.x * kTri;
+    if (k0 >= m) return;
+    const int nb = m - k0 < kTri ? m - k0 : kTri;
+    const double2 *B = b.B + b.bstride * node + k0 + (size_t)k0 * s;
+    for (int e = threadIdx.x; e < nb * nb; e += 64) R[e % nb][e / nb] = B[e % nb + (size_t)(e / nb) * s];
+    __syncthreads();
+    const int c = threadIdx.x;
+    if (c < nb) {
+        for (int i = nb - 1; i >= 0; --i) {
+            double2 v = zc(i == c ? 1.0 : 0.0, 0.0);
+            if (i > c) {
+                X[i][c] = zc(0.0, 0.0);
+                continue;
+            }
+            for (int l = i + 1; l <= c; ++l) v = csub(v, cmul(R[i][l], X[l][c]));
+            const double2 r = R[i][i];
+            const double d = r.x * r.x + r.y * r.y;
+            X[i][c] = zc((v.x * r.x + v.y * r.y) / d, (v.y * r.x - v.x * r.y) / d);
+        }
+        double2 *O = b.Rinv + ((size_t)node * b.ntri + blockIdx.x) * kTri * kTri;
+        for (int i = 0; i < nb; ++i) O[i + c * kTri] = X[i][c];
+    }
 }
 
-// H_j applied to columns j+1.. of A
-__global__ void __launch_bounds__(256) k_big_left_A(BigArgs b, int j) {
+// Rows of block kb of X: X_kb = R_kk^-1 (C_kb - R_(kb, >kb) X_(>kb)), 32 columns per workgroup
+__global__ void __launch_bounds__(256) k_big_trisolve(BigArgs b, int kb) {
+    __shared__ double2 As[16][kTri + 1], Bs[16][33], Cs[kTri][33];
     const NodeArgs &a = b.n;
-    const int node = blockIdx.y, m = a.msz[node], s = a.s;
-    const int c0 = j + 1 + blockIdx.x * kBigChunk;
-    if (j >= m || c0 >= m) return;
-    double2 *A = a.scratch + a.stride * node;
-    const int nc = m - c0 < kBigChunk ? m - c0 : kBigChunk;
-    wg_house_left(A + j + 1 + (size_t)j * s, s - j, b.tauA[(size_t)node * kMaxM + j], A + j + (size_t)c0 * s, s, nc);
-}
-
-// Z <- Z H_j on a chunk of Z's rows
-__global__ void __launch_bounds__(256) k_big_right_Z(BigArgs b, int j) {
-    const NodeArgs &a = b.n;
-    const int node = blockIdx.y, m = a.msz[node], s = a.s;
-    const int r0 = blockIdx.x * kBigChunk;
-    if (j >= m || r0 >= m) return;
-    double2 *A = a.scratch + a.stride * node, *Z = A + (size_t)s * m;
-    const int nr = m - r0 < kBigChunk ? m - r0 : kBigChunk;
-    wg_house_right(A + j + 1 + (size_t)j * s, s - j, b.tauA[(size_t)node * kMaxM + j], Z + r0 + (size_t)j * m, m, nr);
+    const int node = blockIdx.y, m = a.msz[node], s = a.s, k0 = kb * kTri, n0 = blockIdx.x * 32;
+    if (k0 >= m || n0 >= m) return;
+    const int nb = m - k0 < kTri ? m - k0 : kTri, nc = m - n0 < 32 ? m - n0 : 32;
+    const double2 *R = b.B + b.bstride * node;
+    double2 *X = b.B + b.bstride * node + (size_t)m * s;
+    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
+    double2 acc[2][2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int v = 0; v < 2; ++v) acc[u][v] = zc(0.0, 0.0);
+    for (int l0 = k0 + nb; l0 < m; l0 += 16) {
+        double2 ta[2], tb[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int e = tid + 256 * q, am = e & 31, ak = e >> 5, bk = e & 15, bn = e >> 4;
+            const bool ok = am < nb && l0 + ak < m, okb = l0 + bk < m && bn < nc;
+            ta[q] = R[k0 + (ok ? am : 0) + (size_t)(ok ? l0 + ak : k0) * s];
+            tb[q] = X[(okb ? l0 + bk : 0) + (size_t)(n0 + (okb ? bn : 0)) * s];
+            if (!ok) ta[q] = zc(0.0, 0.0);
+            if (!okb) tb[q] = zc(0.0, 0.0);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int e = tid + 256 * q;
+            As[e >> 5][e & 31] = ta[q];
+            Bs[e & 15][e >> 4] = tb[q];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            const double2 a0 = As[k][tx], a1 = As[k][tx + 16], b0 = Bs[k][ty], b1 = Bs[k][ty + 16];
+            cfma(acc[0][0], a0, b0);
+            cfma(acc[0][1], a0, b1);
+            cfma(acc[1][0], a1, b0);
+            cfma(acc[1][1], a1, b1);
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int v = 0; v < 2; ++v) {
+            const int i = tx + 16 * u, j = ty + 16 * v;
+            double2 c = zc(0.0, 0.0);
+            if (i < nb && j < nc) c = csub(X[k0 + i + (size_t)(n0 + j) * s], acc[u][v]);
+            Cs[i][j] = c;
+        }
+    __syncthreads();
+    const double2 *Ri = b.Rinv + ((size_t)node * b.ntri + kb) * kTri * kTri;
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int v = 0; v < 2; ++v) {
+            const int i = tx + 16 * u, j = ty + 16 * v;
+            if (i >= nb || j >= nc) continue;
+            double2 x = zc(0.0, 0.0);
+            for (int l = i; l < nb; ++l) cfma(x, Ri[i + l * kTri], Cs[l][j]);
+            X[k0 + i + (size_t)(n0 + j) * s] = x;
+        }
 }
 
 __device__ __forceinline__ int big_kmax(const NodeArgs &a, int m) {
@@ -378,84 +468,100 @@ __device__ __forceinline__ int big_kmax(const NodeArgs &a, int m) {
     return kmax;
 }
 
-// QRCP step j: norms of the remaining columns of W (rows j..m-1), 4 lanes per column
-__global__ void __launch_bounds__(256) k_big_norms(BigArgs b, int j) {
-    const NodeArgs &a = b.n;
-    const int node = blockIdx.y, m = a.msz[node], s = a.s;
-    if (m == 0 || b.done[node] || j >= big_kmax(a, m)) return;
-    const int nw = s - m;
-    const double2 *W = a.scratch + a.stride * node + (size_t)s * m + (size_t)m * m;
-    const int sub = threadIdx.x & 3;
-    const int c = j + blockIdx.x * kBigChunk + (threadIdx.x >> 2);
-    double p = 0.0;
-    if (c < nw)
-        for (int i = j + sub; i < m; i += 4) {
-            const double2 v = W[i + (size_t)c * m];
-            p += v.x * v.x + v.y * v.y;
-        }
-    p += __shfl_xor(p, 1);
-    p += __shfl_xor(p, 2);
-    if (c < nw && sub == 0) b.nrm[(size_t)node * b.ldn + c] = sqrt(p);
-}
-
-// QRCP step j: pivot (largest norm, lowest index on ties), stop test, swap, reflector
-__global__ void __launch_bounds__(1024) k_big_pivot(BigArgs b, int j) {
-    __shared__ double sh[16];
-    __shared__ int s_piv;
-    __shared__ double s_max;
+// QRCP: H_j applied to the columns c > j of W (rows j..m-1) and the norm of what remains of each (rows
+// > j), one wave per column; j = -1: the first norms only
+__global__ void __launch_bounds__(256) k_big_qrcp_update(BigArgs b, int j) {
     const NodeArgs &a = b.n;
     const int node = blockIdx.y, m = a.msz[node], s = a.s;
     if (m == 0 || b.done[node]) return;
+    const int nw = s - m, lane = threadIdx.x & 63;
+    const int c = j + 1 + blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (c >= nw) return;
+    double2 *W = a.scratch + a.stride * node + (size_t)m * m;
+    double2 *col = W + (size_t)c * m;
+    double p = 0.0;
+    if (j < 0) {
+        for (int i = lane; i < m; i += 64) p = fma(col[i].x, col[i].x, fma(col[i].y, col[i].y, p));
+    } else {
+        const double2 *v = W + (size_t)j * m;
+        const double tau = b.tauW[(size_t)node * b.ldt + j];
+        double2 w = zc(0.0, 0.0);
+        for (int i = j + 1 + lane; i < m; i += 64) cfmac(w, v[i], col[i]);
+        for (int o = 32; o > 0; o >>= 1) {
+            w.x += __shfl_xor(w.x, o);
+            w.y += __shfl_xor(w.y, o);
+        }
+        w = cadd(w, col[j]);
+        const double2 tw = zc(tau * w.x, tau * w.y);
+        for (int i = j + 1 + lane; i < m; i += 64) {
+            const double2 x = csub(col[i], cmul(v[i], tw));
+            col[i] = x;
+            p = fma(x.x, x.x, fma(x.y, x.y, p));
+        }
+        if (lane == 0) col[j] = csub(col[j], tw);
+    }
+    for (int o = 32; o > 0; o >>= 1) p += __shfl_xor(p, o);
+    if (lane == 0) b.nrm[(size_t)node * b.ldn + c] = sqrt(p);
+}
+
+// QRCP step j: pivot (largest norm, lowest index on ties), stop test, swap, reflector
+__global__ void __launch_bounds__(256) k_big_pivot(BigArgs b, int j) {
+    __shared__ double sh[16], sv[4];
+    __shared__ int si[4];
+    const NodeArgs &a = b.n;
+    const int node = blockIdx.x, m = a.msz[node], s = a.s, tid = threadIdx.x;
+    if (m == 0 || b.done[node]) return;
     if (j >= big_kmax(a, m)) {
-        if (threadIdx.x == 0) b.done[node] = 1;
+        if (tid == 0) b.done[node] = 1;
         return;
     }
     const int nw = s - m;
-    double2 *W = a.scratch + a.stride * node + (size_t)s * m + (size_t)m * m;
+    double2 *W = a.scratch + a.stride * node + (size_t)m * m;
     const double *nrm = b.nrm + (size_t)node * b.ldn;
-    if (threadIdx.x == 0) {
-        int best = j;
-        double bv = nrm[j];
-        for (int c = j + 1; c < nw; ++c)
-            if (nrm[c] > bv) {
-                bv = nrm[c];
-                best = c;
-            }
-        s_piv = best;
-        s_max = bv;
+    const double first = nrm[j];
+    double bv = -1.0;
+    int best = nw;
+    for (int c = j + tid; c < nw; c += 256)
+        if (nrm[c] > bv) {
+            bv = nrm[c];
+            best = c;
+        }
+    for (int o = 1; o < 64; o <<= 1) {
+        const double ov = __shfl_xor(bv, o);
+        const int oi = __shfl_xor(best, o);
+        if (ov > bv || (ov == bv && oi < best)) {
+            bv = ov;
+            best = oi;
+        }
+    }
+    if ((tid & 63) == 0) {
+        sv[tid >> 6] = bv;
+        si[tid >> 6] = best;
     }
     __syncthreads();
-    if (!(s_max > a.tol_abs)) {
-        if (threadIdx.x == 0) b.done[node] = 1;
+    for (int w = 0; w < 4; ++w)
+        if (sv[w] > bv || (sv[w] == bv && si[w] < best)) {
+            bv = sv[w];
+            best = si[w];
+        }
+    // a NaN in the first place stops the search, as it does where the norms are scanned in order
+    if (!(bv > a.tol_abs) || first != first) {
+        if (tid == 0) b.done[node] = 1;
         return;
     }
-    const int pc = s_piv;
-    if (pc != j) {
-        for (int i = threadIdx.x; i < m; i += blockDim.x) {
+    if (best != j) {
+        for (int i = tid; i < m; i += 256) {
             const double2 t = W[i + (size_t)j * m];
-            W[i + (size_t)j * m] = W[i + (size_t)pc * m];
-            W[i + (size_t)pc * m] = t;
+            W[i + (size_t)j * m] = W[i + (size_t)best * m];
+            W[i + (size_t)best * m] = t;
         }
         __syncthreads();
     }
     const double tau = wg_house(W + j + (size_t)j * m, m - j, sh, nullptr);
-    if (threadIdx.x == 0) {
-        b.tauW[(size_t)node * kMaxM + j] = tau;
+    if (tid == 0) {
+        b.tauW[(size_t)node * b.ldt + j] = tau;
         a.rank_out[node] = j + 1;
     }
-}
-
-// QRCP step j: H_j applied to columns j+1.. of W
-__global__ void __launch_bounds__(256) k_big_left_W(BigArgs b, int j) {
-    const NodeArgs &a = b.n;
-    const int node = blockIdx.y, m = a.msz[node], s = a.s;
-    if (m == 0 || b.done[node]) return;
-    const int nw = s - m;
-    const int c0 = j + 1 + blockIdx.x * kBigChunk;
-    if (c0 >= nw) return;
-    double2 *W = a.scratch + a.stride * node + (size_t)s * m + (size_t)m * m;
-    const int nc = nw - c0 < kBigChunk ? nw - c0 : kBigChunk;
-    wg_house_left(W + j + 1 + (size_t)j * m, m - j, b.tauW[(size_t)node * kMaxM + j], W + j + (size_t)c0 * m, m, nc);
 }
 
 // U = [I_r; 0]
@@ -464,53 +570,18 @@ __global__ void k_big_uinit(BigArgs b) {
     const int node = blockIdx.y, m = a.msz[node], s = a.s;
     if (m == 0) return;
     const int r = a.rank_out[node];
-    double2 *U = a.scratch + a.stride * node + (size_t)s * m + (size_t)m * s;
+    double2 *U = a.scratch + a.stride * node + (size_t)m * s;
     for (long e = blockIdx.x * (long)blockDim.x + threadIdx.x; e < (long)m * r; e += (long)gridDim.x * blockDim.x) {
         const int i = (int)(e % m), jj = (int)(e / m);
         U[e] = zc(i == jj ? 1.0 : 0.0, 0.0);
     }
 }
 
-// U <- H_j U (rows j..m-1) on a chunk of U's r columns
-__global__ void __launch_bounds__(256) k_big_left_U(BigArgs b, int j) {
-    const NodeArgs &a = b.n;
-    const int node = blockIdx.y, m = a.msz[node], s = a.s;
-    if (m == 0) return;
-    const int r = a.rank_out[node];
-    const int c0 = blockIdx.x * kBigChunk;
-    if (j >= r || c0 >= r) return;
-    double2 *Z = a.scratch + a.stride * node + (size_t)s * m;
-    double2 *W = Z + (size_t)m * m, *U = Z + (size_t)m * s;
-    const int nc = r - c0 < kBigChunk ? r - c0 : kBigChunk;
-    wg_house_left(W + j + 1 + (size_t)j * m, m - j, b.tauW[(size_t)node * kMaxM + j], U + j + (size_t)c0 * m, m, nc);
-}
-
-// T = Z1 R^{-*} (R = upper m x m of A), one lane per row; at the root also H0 = (T + T^*)/2
-__global__ void __launch_bounds__(256) k_big_tsolve(BigArgs b) {
-    const NodeArgs &a = b.n;
-    const int node = blockIdx.y, m = a.msz[node], s = a.s;
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (m == 0 || i >= m) return;
-    const double2 *A = a.scratch + a.stride * node;
-    double2 *Z = const_cast<double2 *>(A) + (size_t)s * m;
-    for (int j = m - 1; j >= 0; --j) {
-        double2 acc = Z[i + (size_t)j * m];
-        for (int k = j + 1; k < m; ++k) {
-            const double2 rjk = A[j + (size_t)k * s];
-            const double2 t = Z[i + (size_t)k * m];
-            acc.x -= t.x * rjk.x + t.y * rjk.y;
-            acc.y -= t.y * rjk.x - t.x * rjk.y;
-        }
-        const double2 rjj = A[j + (size_t)j * s];
-        const double d = rjj.x * rjj.x + rjj.y * rjj.y;
-        Z[i + (size_t)j * m] = zc((acc.x * rjj.x - acc.y * rjj.y) / d, (acc.x * rjj.y + acc.y * rjj.x) / d);
-    }
-}
-
+// H0 = (T + T^*) / 2
 __global__ void k_big_root_out(BigArgs b) {
     const NodeArgs &a = b.n;
-    const int node = blockIdx.y, m = a.msz[node], s = a.s;
-    const double2 *Z = a.scratch + a.stride * node + (size_t)s * m;
+    const int node = blockIdx.y, m = a.msz[node];
+    const double2 *Z = a.scratch + a.stride * node;
     double2 *out = a.Dres + a.doff[node];
     for (long e = blockIdx.x * (long)blockDim.x + threadIdx.x; e < (long)m * m; e += (long)gridDim.x * blockDim.x) {
         const int i = (int)(e % m), j = (int)(e / m);
@@ -525,7 +596,7 @@ __global__ void k_node_conj_transpose(NodeArgs a) {
     const int m = a.msz[node], s = a.s;
     if (m == 0) return;
     const int r = a.rank_out[node];
-    const double2 *Z = a.scratch + a.stride * node + (size_t)s * m;
+    const double2 *Z = a.scratch + a.stride * node + (size_t)a.lead * s * m;
     double2 *P = const_cast<double2 *>(Z) + (size_t)m * s + (size_t)m * m;
     const double2 *Y = P + (size_t)m * m;
     for (long e = blockIdx.x * (long)blockDim.x + threadIdx.x; e < (long)r * m; e += (long)gridDim.x * blockDim.x) {
@@ -612,69 +683,93 @@ template <typename T> static DevBuf *upload(const std::vector<T> &v, hipStream_t
     return b;
 }
 
-// Section 3.1 on a level of large nodes, one reflector or pivot step per launch (see BigArgs).
-static int g_big_node = 256;       // levels whose largest node has at least this many rows take this path
+// Levels whose largest node has at least this many rows take the level-wide path: at 64 rows (1024 leaves
+// of N = 2^16) the construction takes 25.8 ms with it and 29.9 ms with one workgroup per node, 2D n = 32
+// (nodes of 64 to 424 rows) 79 and 131 ms; below 64 rows the two measure the same.
+constexpr int kBigNode = 64;
+static int g_big_node = kBigNode;
 
 static unsigned cdiv(long a, long b) { return (unsigned)(a <= 0 ? 0 : (a + b - 1) / b); }
 
-static void basis_big(const NodeArgs &na, const std::vector<int> &ms, int nn, int mmax, int sl, bool root,
+// device buffers of the level steps, kept over the levels of a construction
+struct BigWork {
+    DevBuf B, nrm, tauW, done, Rinv;
+    WyWork wy;
+};
+
+static void basis_big(const NodeArgs &na, const std::vector<int> &ms, int nn, int mmax, int sl, bool root, BigWork &w,
                       hipStream_t s) {
-    DevBuf tauA((size_t)nn * kMaxM * sizeof(double)), tauW((size_t)nn * kMaxM * sizeof(double)),
-        nrm((size_t)nn * sl * sizeof(double)), done((size_t)nn * sizeof(int));
     BigArgs b;
     b.n = na;
-    b.tauA = tauA.as<double>();
-    b.tauW = tauW.as<double>();
-    b.nrm = nrm.as<double>();
+    b.bstride = (size_t)2 * sl * mmax;
+    b.ntri = (int)cdiv(mmax, kTri);
     b.ldn = sl;
-    b.done = done.as<int>();
+    b.ldt = mmax;
+    w.B.ensure(b.bstride * nn * sizeof(double2));
+    w.nrm.ensure((size_t)nn * b.ldn * sizeof(double));
+    w.tauW.ensure((size_t)nn * b.ldt * sizeof(double));
+    w.done.ensure((size_t)nn * sizeof(int));
+    w.Rinv.ensure((size_t)nn * b.ntri * kTri * kTri * sizeof(double2));
+    b.B = w.B.as<double2>();
+    b.nrm = w.nrm.as<double>();
+    b.tauW = w.tauW.as<double>();
+    b.done = w.done.as<int>();
+    b.Rinv = w.Rinv.as<double2>();
     const unsigned y = (unsigned)nn;
-    k_big_init<<<dim3(256, y), 256, 0, s>>>(b);
-    // full Householder QR of Omega_tau^* (s x m), then Z = Y_tau H_0 ... H_{m-1}
-    for (int j = 0; j < mmax; ++j) {
-        k_big_house_A<<<dim3(1, y), 1024, 0, s>>>(b, j);
-        if (mmax - 1 - j > 0) k_big_left_A<<<dim3(cdiv(mmax - 1 - j, kBigChunk), y), kBigThreads, 0, s>>>(b, j);
+    k_big_pack<true><<<dim3(cdiv(sl, 32), cdiv(2 * mmax, 32), y), 256, 0, s>>>(b);
+    std::vector<WyNode> qn(nn);
+    for (int j = 0; j < nn; ++j) {
+        double2 *B = b.B + b.bstride * j;
+        qn[j] = WyNode{B, B, sl, sl, sl, ms[j], 2 * ms[j]};
     }
-    for (int j = 0; j < mmax; ++j) k_big_right_Z<<<dim3(cdiv(mmax, kBigChunk), y), kBigThreads, 0, s>>>(b, j);
+    wy_qr(qn, w.wy, s);
+    k_big_triinv<<<dim3((unsigned)b.ntri, y), 64, 0, s>>>(b);
+    for (int kb = b.ntri - 1; kb >= 0; --kb) k_big_trisolve<<<dim3(cdiv(mmax, 32), y), 256, 0, s>>>(b, kb);
+    k_big_pack<false><<<dim3(cdiv(sl, 32), cdiv(mmax, 32), y), 256, 0, s>>>(b);
     FIO_HIP(hipGetLastError());
-    if (!root) {
-        // QRCP of W = Z[:, m:s]; every 32 steps the host stops once every node has stopped
-        int mmin = mmax, kcap = 0;
-        for (int v : ms)
-            if (v > 0) mmin = v < mmin ? v : mmin;
-        for (int v : ms) {
-            if (v == 0) continue;
-            int k = v < sl - v ? v : sl - v;
-            if (na.cap > 0 && na.cap < k) k = na.cap;
-            kcap = k > kcap ? k : kcap;
-        }
-        const int nwmax = sl - mmin;
-        std::vector<int> hd(nn);
-        for (int j = 0; j < kcap; ++j) {
-            k_big_norms<<<dim3(cdiv(nwmax - j, kBigChunk), y), kBigThreads, 0, s>>>(b, j);
-            k_big_pivot<<<dim3(1, y), 1024, 0, s>>>(b, j);
-            if (nwmax - j - 1 > 0) k_big_left_W<<<dim3(cdiv(nwmax - j - 1, kBigChunk), y), kBigThreads, 0, s>>>(b, j);
-            if ((j & 31) == 31) {
-                FIO_HIP(hipMemcpyAsync(hd.data(), done.p, nn * sizeof(int), hipMemcpyDeviceToHost, s));
-                FIO_HIP(hipStreamSynchronize(s));
-                bool all = true;
-                for (int k = 0; k < nn; ++k) all = all && (hd[k] || ms[k] == 0);
-                if (all) break;
-            }
-        }
-        std::vector<int> rk(nn);
-        FIO_HIP(hipMemcpyAsync(rk.data(), na.rank_out, nn * sizeof(int), hipMemcpyDeviceToHost, s));
-        FIO_HIP(hipStreamSynchronize(s));
-        int rmax = 0;
-        for (int v : rk) rmax = v > rmax ? v : rmax;
-        // U = H_0 ... H_{r-1} [I_r; 0]
-        k_big_uinit<<<dim3(64, y), 256, 0, s>>>(b);
-        for (int j = rmax - 1; j >= 0; --j) k_big_left_U<<<dim3(cdiv(rmax, kBigChunk), y), kBigThreads, 0, s>>>(b, j);
+    if (root) {
+        k_big_root_out<<<dim3(64, y), 256, 0, s>>>(b);
+        FIO_HIP(hipGetLastError());
+        return;
     }
-    k_big_tsolve<<<dim3(cdiv(mmax, 256), y), 256, 0, s>>>(b);
-    if (root) k_big_root_out<<<dim3(64, y), 256, 0, s>>>(b);
+    // QRCP of W = Z[:, m:s]; every 16 steps the host stops once every node has stopped
+    int mmin = mmax, kcap = 0;
+    for (int v : ms) {
+        if (v == 0) continue;
+        mmin = v < mmin ? v : mmin;
+        int k = v < sl - v ? v : sl - v;
+        if (na.cap > 0 && na.cap < k) k = na.cap;
+        kcap = k > kcap ? k : kcap;
+    }
+    const int nwmax = sl - mmin;
+    std::vector<int> hd(nn);
+    k_big_qrcp_update<<<dim3(cdiv(nwmax, 4), y), 256, 0, s>>>(b, -1);
+    for (int j = 0; j < kcap; ++j) {
+        k_big_pivot<<<nn, 256, 0, s>>>(b, j);
+        if (nwmax - j - 1 > 0) k_big_qrcp_update<<<dim3(cdiv(nwmax - j - 1, 4), y), 256, 0, s>>>(b, j);
+        if ((j & 15) == 15) {
+            FIO_HIP(hipMemcpyAsync(hd.data(), w.done.p, nn * sizeof(int), hipMemcpyDeviceToHost, s));
+            FIO_HIP(hipStreamSynchronize(s));
+            bool all = true;
+            for (int k = 0; k < nn; ++k) all = all && (hd[k] || ms[k] == 0);
+            if (all) break;
+        }
+    }
+    std::vector<int> rk(nn);
+    FIO_HIP(hipMemcpyAsync(rk.data(), na.rank_out, nn * sizeof(int), hipMemcpyDeviceToHost, s));
+    FIO_HIP(hipStreamSynchronize(s));
+    // U = H_0 ... H_{r-1} [I_r; 0]
+    k_big_uinit<<<dim3(16, y), 256, 0, s>>>(b);
+    std::vector<WyNode> un(nn);
+    for (int j = 0; j < nn; ++j) {
+        double2 *Z = na.scratch + na.stride * j;
+        const int m = ms[j], r = m > 0 ? rk[j] : 0;
+        un[j] = WyNode{Z + (size_t)m * m, Z + (size_t)m * sl, m, m, m, r, r};
+    }
+    wy_factors(un, b.tauW, b.ldt, w.wy, s);
+    wy_apply(un, w.wy, true, s);
     FIO_HIP(hipGetLastError());
-    FIO_HIP(hipStreamSynchronize(s));    // the work arrays are released here
+    FIO_HIP(hipStreamSynchronize(s));    // the node lists are released here
 }
 
 void hss_layout_level(hss_s *h, int l) {
@@ -799,6 +894,7 @@ static fio_status build_impl(long n, const hss_opts *o, const Sampler &sm, hipSt
     fio_status st = guarded([&] {
         double g = o->norm_est;
         DevBuf Om, Ob, Yb, Y, t0, t1, scratch;
+        BigWork bw;
         for (int l = Lh; l >= 0; --l) {
             const bool root = (l == 0);
             if (!root) hss_layout_level(h, l);
@@ -842,7 +938,8 @@ static fio_status build_impl(long n, const hss_opts *o, const Sampler &sm, hipSt
                 int mmin = mmax;
                 for (int v : ms)
                     if (v > 0) mmin = v < mmin ? v : mmin;
-                if (!root && mmax < g_big_node && sl - mmin > kMaxNW) throw Err{FIO_ERR_UNSUPPORTED};
+                const bool spread = mmax >= g_big_node;
+                if (!root && !spread && sl - mmin > kMaxNW) throw Err{FIO_ERR_UNSUPPORTED};
                 h->samples[l] = sl;
                 Om.ensure((size_t)R * sl * sizeof(double2));
                 if (sm.omega(sm.octx, l, R, sl, Om.p, s) != 0) throw Err{FIO_ERR_CALLBACK};
@@ -861,7 +958,8 @@ static fio_status build_impl(long n, const hss_opts *o, const Sampler &sm, hipSt
                     g = sqrt(ny) / sqrt(no);
                 }
                 // per-node algebra
-                size_t stride = (size_t)2 * sl * mmax + (size_t)3 * mmax * mmax;
+                const int lead = spread ? 0 : 1;
+                size_t stride = (size_t)(1 + lead) * sl * mmax + (size_t)3 * mmax * mmax;
                 scratch.ensure(stride * nn * sizeof(double2));
                 std::vector<size_t> uo(nn, 0);
                 if (!root) uo = h->uoff[l];
@@ -884,11 +982,12 @@ static fio_status build_impl(long n, const hss_opts *o, const Sampler &sm, hipSt
                 na.Dres = Dres[l]->as<double2>();
                 na.doff = ddo->as<size_t>();
                 na.root = root ? 1 : 0;
-                if (mmax < g_big_node) {
+                na.lead = lead;
+                if (!spread) {
                     k_node_basis<<<nn, node_threads(mmax), 0, s>>>(na);
                     FIO_HIP(hipGetLastError());
                 } else {
-                    basis_big(na, ms, nn, mmax, sl, root, s);
+                    basis_big(na, ms, nn, mmax, sl, root, bw, s);
                 }
                 if (!root) {
                     h->rank[l].assign(nn, 0);
@@ -902,7 +1001,7 @@ static fio_status build_impl(long n, const hss_opts *o, const Sampler &sm, hipSt
                         const int m = ms[j], r = h->rank[l][j];
                         if (m == 0) continue;
                         rmax = r > rmax ? r : rmax;
-                        double2 *T = sc + stride * j + (size_t)sl * m;
+                        double2 *T = sc + stride * j + (size_t)lead * sl * m;
                         double2 *U = T + (size_t)m * sl, *P = U + (size_t)m * m, *X = P + (size_t)m * m;
                         g1.add(U, m, T, m, P, m, r, m, m);        // P = U^* T      (r x m)
                         g2.add(U, m, P, m, T, m, m, m, r);        // T -= U P       (X, m x m)
@@ -1263,4 +1362,4 @@ extern "C" fio_status hss_matvec(hss_t h, const void *X, long ldx, void *Y, long
 
 extern "C" void hss_destroy(hss_t h) { delete h; }
 
-extern "C" void fio_hss_set_big_node(int rows) { fio::g_big_node = rows > 0 ? rows : 256; }
+extern "C" void fio_hss_set_big_node(int rows) { fio::g_big_node = rows > 0 ? rows : fio::kBigNode; }
