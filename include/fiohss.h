@@ -282,9 +282,9 @@ void fio_set_leaf_fused(int on);
  * default (64).  Not thread-safe with respect to concurrent constructions. */
 void fio_hss_set_big_node(int rows);
 
-/* The same choice for the basis elimination of hss_ulv_factor (QL of each node's basis and
- * the explicit Q): levels whose largest node has at least `rows` rows apply every reflector
- * in its own launch over many workgroups.  rows <= 0 restores the default (256). */
+/* The same choice for the node algebra of hss_ulv_factor: levels whose largest node has at
+ * least `rows` rows run it in blocked steps over many workgroups.  rows <= 0 restores the
+ * default (64). */
 void fio_ulv_set_big_node(int rows);
 
 /* ---------------------------------------------------------------------------

@@ -474,8 +474,8 @@ def set_hss_big_node(rows):
 
 
 def set_ulv_big_node(rows):
-    """ULV factorization: levels whose largest node has >= rows rows apply the basis reflectors
-    with the multi-workgroup path (rows <= 0: default 256)."""
+    """ULV factorization: levels whose largest node has >= rows rows take the
+    multi-workgroup path (rows <= 0: default 64)."""
     lib().fio_ulv_set_big_node(int(rows))
 
 

@@ -28,8 +28,8 @@ struct WyWork {
 void wy_qr(const std::vector<WyNode> &nodes, WyWork &w, hipStream_t s);
 // Triangular factors of existing reflectors with the scalars tau (ldtau per node) into w
 void wy_factors(const std::vector<WyNode> &nodes, const double *tau, int ldtau, WyWork &w, hipStream_t s);
-// C <- H_0 H_1 ... H_(k-1) C for every node (after wy_qr or wy_factors on the same nodes); unit: the columns
-// of C are those of [I; 0], so block j0 leaves the columns before j0 alone
+// C <- H_0 H_1 ... H_(k-1) C for every node (after wy_qr or wy_factors on nodes with the
+// same V, n and k); unit: the columns of C are those of [I; 0], so block j0 leaves the columns before j0 alone
 void wy_apply(const std::vector<WyNode> &nodes, WyWork &w, bool unit, hipStream_t s);
 
 }  // namespace fio

@@ -446,6 +446,7 @@ void wy_factors(const std::vector<WyNode> &nodes, const double *tau, int ldtau, 
 void wy_apply(const std::vector<WyNode> &nodes, WyWork &w, bool unit, hipStream_t s) {
     const Extent e = extent(nodes);
     if (e.k == 0) return;
+    upload_nodes(nodes, w, e.n, e.k, s);
     for (int j0 = w.kt - w.block; j0 >= 0; j0 -= w.block)
         update(w, (int)nodes.size(), j0, unit ? 1 : 0, e.nc - (unit ? j0 : 0), false, s);
     FIO_HIP(hipGetLastError());

@@ -1,6 +1,6 @@
 // ULV factorization of an HPD HSS matrix and its solve (Section 2.4) on gfx950.
 //
-// Factor (offline, one workgroup per node, level by level from the leaves):
+// Factor (offline, level by level from the leaves):
 //   QL basis elimination U = Q [0; Uhat2] with Householder reflectors taken from
 //   the bottom of each column; Dchk = Q^* D Q; Cholesky Dchk11 = L11 L11^*;
 //   Dhat21 = Dchk21 L11^{-*}; Dhat22 = Dchk22 - Dhat21 Dhat21^*; then the merge
@@ -11,6 +11,7 @@
 // c_tau = W^* [bhat1; chat2]; the root keeps Linv = L_rho^{-1}.  The online solve
 // is therefore 2 Lh + 2 batched small GEMM launches (see k_ulv_level).
 #include "hss.h"
+#include "hss_qr.h"
 #include "timing.h"
 
 #include <cmath>
@@ -238,137 +239,285 @@ __global__ void __launch_bounds__(1024) k_ulv_node(FactArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// Large nodes (upper levels of 2D trees): phase 0 of k_ulv_node with one reflector per
-// launch spread over many workgroups (grid.y = node, grid.x = 64-column chunk).  Node j of
-// the level eliminates its columns jj = r-1 .. 0 at host steps t = r-1-jj, and builds Q
-// with jj = t.  Same reflector arithmetic as k_ulv_node; the dot products run over four
-// lanes per column.
-struct UlvBig {
-    FactArgs f;
-    double *tau;            // kUlvMaxM per node
+// Levels of larger nodes: the same two phases spread over the card.
+//
+// Phase 0: with the rows and columns of U in reverse order the QL elimination is a QR, and Q is the
+// product of its reflectors applied to the identity: both run in the blocks of hss_qr.h.
+// Phase 1: Dchk11 = L11 L11^*, X = L11^{-1} Dchk12 and W1 = L11^{-1} Q1^* are one forward
+// substitution on the rows [Dchk11 Dchk12 | Q1^*] (the rows of Dchk11 become L11^*), 32 rows a step:
+// k_fact_diag brings the diagonal block up to date and factors it, k_fact_rows the rest of the rows.
+// Both are chains of small dependent steps on data in cache.  With a launch per reflector and one
+// workgroup per node for the substitutions the factorization of 2D n = 64 (nodes of 64 to 784 rows, a
+// root of 832) took 212 ms, with these kernels 29.6 ms.
+struct TriNode {
+    double2 *T, *W;         // m x m each: the matrix and the right-hand sides of its row sweep
+    int m, k;               // k rows are factored
 };
 
-constexpr int kUlvChunk = 16, kUlvThreads = 4 * kUlvChunk;   // columns per workgroup, four lanes each
+constexpr int kFact = 32;
 
-__global__ void k_ubig_init(UlvBig b) {
-    const FactArgs &a = b.f;
+// Uw <- U in reverse order (m x r), T <- I
+__global__ void k_ubig_init(FactArgs a) {
     const int node = blockIdx.y, m = a.msz[node], r = a.rsz[node];
     if (m == 0) return;
-    double2 *Uw = a.scratch + a.scoff[node], *Q = Uw + (size_t)m * m;
+    double2 *Uw = a.scratch + a.scoff[node], *T = Uw + (size_t)2 * m * m;
     const double2 *Uin = a.U + a.uoff[node];
     for (long e = blockIdx.x * (long)blockDim.x + threadIdx.x; e < (long)m * m; e += (long)gridDim.x * blockDim.x) {
-        if (e < (long)m * r) Uw[e] = Uin[e];
-        Q[e] = zc((e % m) == (e / m) ? 1.0 : 0.0, 0.0);
+        const int i = (int)(e % m), j = (int)(e / m);
+        if (j < r) Uw[e] = Uin[(m - 1 - i) + (size_t)(r - 1 - j) * m];
+        T[e] = zc(i == j ? 1.0 : 0.0, 0.0);
     }
 }
 
-__global__ void __launch_bounds__(1024) k_ubig_house(UlvBig b, int t) {
-    __shared__ double sh[16];
-    const FactArgs &a = b.f;
-    const int node = blockIdx.y, m = a.msz[node], r = a.rsz[node], k = m - r;
-    const int jj = r - 1 - t;
-    if (m == 0 || jj < 0) return;
-    const int tid = threadIdx.x, nt = blockDim.x;
-    const int p = k + jj, n = p + 1;
-    double2 *x = a.scratch + a.scoff[node] + (size_t)jj * m;
-    const double2 al = x[p];
-    double part = 0.0;
-    for (int i = tid; i < n; i += nt) part += x[i].x * x[i].x + x[i].y * x[i].y;
-    const double sigma = sqrt(wsum(part, sh));
-    double tau = 0.0;
-    if (sigma > 0.0) {
-        const double aa = sqrt(al.x * al.x + al.y * al.y);
-        const double2 ph = aa > 0.0 ? zc(al.x / aa, al.y / aa) : zc(1.0, 0.0);
-        const double2 beta = zc(-ph.x * sigma, -ph.y * sigma);
-        const double2 den = csub(al, beta);
-        const double dn = den.x * den.x + den.y * den.y;
-        const double2 inv = zc(den.x / dn, -den.y / dn);
-        for (int i = tid; i < p; i += nt) x[i] = cmul(x[i], inv);
-        __syncthreads();
-        if (tid == 0) x[p] = beta;
-        tau = 1.0 + aa / sigma;
-    }
-    if (tid == 0) b.tau[(size_t)node * kUlvMaxM + jj] = tau;
-}
-
-// columns [c0, c1) of A (lda) <- H A, H = I - tau v v^*, v = [x[0..p); 1] (rows 0..p)
-__device__ void ql_apply_cols(const double2 *x, int p, double tau, double2 *A, int lda, int c0, int c1) {
-    const int sub = threadIdx.x & 3;
-    for (int cb = c0; cb < c1; cb += (int)(blockDim.x >> 2)) {
-        const int c = cb + (int)(threadIdx.x >> 2);
-        double2 *col = A + (size_t)(c < c1 ? c : c0) * lda;
-        double2 w = zc(0.0, 0.0);
-        if (c < c1)
-            for (int i = sub; i < p; i += 4) cfmac(w, x[i], col[i]);
-        w.x += __shfl_xor(w.x, 1);
-        w.y += __shfl_xor(w.y, 1);
-        w.x += __shfl_xor(w.x, 2);
-        w.y += __shfl_xor(w.y, 2);
-        if (c < c1) {
-            w = cadd(w, col[p]);
-            const double2 tw = zc(tau * w.x, tau * w.y);
-            if (sub == 0) col[p] = csub(col[p], tw);
-            for (int i = sub; i < p; i += 4) col[i] = csub(col[i], cmul(x[i], tw));
+// Q and Uhat2 back in order
+__global__ void k_ubig_finish(FactArgs a) {
+    const int node = blockIdx.y, m = a.msz[node], r = a.rsz[node];
+    if (m == 0) return;
+    const double2 *Uw = a.scratch + a.scoff[node], *T = Uw + (size_t)2 * m * m;
+    double2 *Q = a.scratch + a.scoff[node] + (size_t)m * m, *U2 = a.U2 + a.soff[node];
+    for (long e = blockIdx.x * (long)blockDim.x + threadIdx.x; e < (long)m * m; e += (long)gridDim.x * blockDim.x) {
+        Q[e] = T[(size_t)m * m - 1 - e];
+        if (e < (long)r * r) {
+            const int i = (int)(e % r), c = (int)(e / r);
+            U2[e] = c <= i ? Uw[(r - 1 - i) + (size_t)(r - 1 - c) * m] : zc(0.0, 0.0);
         }
     }
 }
 
-// the current reflector applied to the node's remaining columns 0..jj-1
-__global__ void __launch_bounds__(256) k_ubig_left(UlvBig b, int t) {
-    const FactArgs &a = b.f;
-    const int node = blockIdx.y, m = a.msz[node], r = a.rsz[node], k = m - r;
-    const int jj = r - 1 - t;
-    const int c0 = blockIdx.x * kUlvChunk;
-    if (m == 0 || jj < 0 || c0 >= jj) return;
-    const double tau = b.tau[(size_t)node * kUlvMaxM + jj];
-    if (tau == 0.0) return;
-    double2 *Uw = a.scratch + a.scoff[node];
-    const int c1 = c0 + kUlvChunk < jj ? c0 + kUlvChunk : jj;
-    ql_apply_cols(Uw + (size_t)jj * m, k + jj, tau, Uw, m, c0, c1);
+// W <- Q^*, D22 <- Dchk22, one 32 x 32 tile per workgroup
+__global__ void __launch_bounds__(256) k_fact_prep(FactArgs a) {
+    __shared__ double2 t[32][33];
+    const int node = blockIdx.z, m = a.msz[node], r = a.rsz[node], k = m - r;
+    const int i0 = blockIdx.x * 32, j0 = blockIdx.y * 32;
+    if (i0 >= m || j0 >= m) return;
+    const double2 *Q = a.scratch + a.scoff[node] + (size_t)m * m, *T = Q + (size_t)m * m;
+    double2 *W = a.W + a.woff[node], *D22 = a.D22 + a.soff[node];
+    const int x = threadIdx.x & 31, y = threadIdx.x >> 5;
+    for (int q = y; q < 32; q += 8)
+        if (i0 + x < m && j0 + q < m) {
+            const double2 v = Q[i0 + x + (size_t)(j0 + q) * m];
+            t[q][x] = zc(v.x, -v.y);
+            const int i = i0 + x - k, j = j0 + q - k;
+            if (i >= 0 && j >= 0) D22[i + (size_t)j * r] = T[i0 + x + (size_t)(j0 + q) * m];
+        }
+    __syncthreads();
+    for (int q = y; q < 32; q += 8)
+        if (j0 + x < m && i0 + q < m) W[j0 + x + (size_t)(i0 + q) * m] = t[x][q];
 }
 
-// Q <- H_jj Q, jj = t (Q = H_{r-1} ... H_0)
-__global__ void __launch_bounds__(256) k_ubig_q(UlvBig b, int t) {
-    const FactArgs &a = b.f;
-    const int node = blockIdx.y, m = a.msz[node], r = a.rsz[node], k = m - r;
-    const int c0 = blockIdx.x * kUlvChunk;
-    if (m == 0 || t >= r || c0 >= m) return;
-    const double tau = b.tau[(size_t)node * kUlvMaxM + t];
-    if (tau == 0.0) return;
-    double2 *Uw = a.scratch + a.scoff[node], *Q = Uw + (size_t)m * m;
-    const int c1 = c0 + kUlvChunk < m ? c0 + kUlvChunk : m;
-    ql_apply_cols(Uw + (size_t)t * m, k + t, tau, Q, m, c0, c1);
-}
-
-__global__ void k_ubig_u2(UlvBig b) {
-    const FactArgs &a = b.f;
-    const int node = blockIdx.y, m = a.msz[node], r = a.rsz[node], k = m - r;
-    if (m == 0) return;
-    const double2 *Uw = a.scratch + a.scoff[node];
-    double2 *U2 = a.U2 + a.soff[node];
-    for (long e = blockIdx.x * (long)blockDim.x + threadIdx.x; e < (long)r * r; e += (long)gridDim.x * blockDim.x) {
-        const int i = (int)(e % r), c = (int)(e / r);
-        U2[e] = (c <= i) ? Uw[(k + i) + (size_t)c * m] : zc(0.0, 0.0);
+// 32 x 32 tile sum over rows l0 <= l < l1 of conj(R(l, rows)) X(l, columns); R has nb columns, X nc
+__device__ __forceinline__ void fact_tile(const double2 *R, const double2 *X, int m, int l0, int l1, int nb, int nc,
+                                          double2 (*As)[33], double2 (*Bs)[33], double2 (&acc)[2][2]) {
+    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int v = 0; v < 2; ++v) acc[u][v] = zc(0.0, 0.0);
+    for (int l = l0; l < l1; l += 16) {
+        double2 ta[2], tb[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int e = tid + 256 * q, kk = l + (e & 15), c = e >> 4;
+            const bool oa = kk < l1 && c < nb, ob = kk < l1 && c < nc;
+            ta[q] = R[(oa ? kk : 0) + (size_t)(oa ? c : 0) * m];
+            tb[q] = X[(ob ? kk : 0) + (size_t)(ob ? c : 0) * m];
+            if (!oa) ta[q] = zc(0.0, 0.0);
+            if (!ob) tb[q] = zc(0.0, 0.0);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int e = tid + 256 * q;
+            As[e & 15][e >> 4] = zc(ta[q].x, -ta[q].y);
+            Bs[e & 15][e >> 4] = tb[q];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int kk = 0; kk < 16; ++kk) {
+            const double2 a0 = As[kk][tx], a1 = As[kk][tx + 16], b0 = Bs[kk][ty], b1 = Bs[kk][ty + 16];
+            cfma(acc[0][0], a0, b0);
+            cfma(acc[0][1], a0, b1);
+            cfma(acc[1][0], a1, b0);
+            cfma(acc[1][1], a1, b1);
+        }
     }
 }
 
-static int g_ulv_big = 256;        // levels whose largest node has at least this many rows take this path
-
-static void ulv_phase0_big(const FactArgs &fa, int nn, int mlev, int rmax, hipStream_t s) {
-    DevBuf tau((size_t)nn * kUlvMaxM * sizeof(double));
-    UlvBig b{fa, tau.as<double>()};
-    const unsigned y = (unsigned)nn;
-    k_ubig_init<<<dim3(256, y), 256, 0, s>>>(b);
-    for (int t = 0; t < rmax; ++t) {
-        k_ubig_house<<<dim3(1, y), 1024, 0, s>>>(b, t);
-        const int ncol = rmax - 1 - t;     // an upper bound of every node's remaining columns
-        if (ncol > 0) k_ubig_left<<<dim3((unsigned)((ncol + kUlvChunk - 1) / kUlvChunk), y), kUlvThreads, 0, s>>>(b, t);
+// Diagonal block k0 of a node: R_kk (upper, R_kk^* R_kk = the updated block) into T and R_kk^{-*} into
+// Li.  The elimination runs on [block | I] in registers: thread (column, row mod 4), one barrier per row.
+__global__ void __launch_bounds__(256) k_fact_diag(const TriNode *__restrict__ nodes, int k0, double2 *Li, int *fail) {
+    __shared__ double2 As[16][33], Bs[16][33], Cs[kFact][kFact + 1];
+    __shared__ double2 row[2][64];
+    const TriNode d = nodes[blockIdx.x];
+    if (k0 >= d.k) return;
+    const int m = d.m, nb = d.k - k0 < kFact ? d.k - k0 : kFact, tid = threadIdx.x;
+    double2 *T = d.T + (size_t)k0 * m;
+    double2 acc[2][2];
+    fact_tile(T, T, m, 0, k0, nb, nb, As, Bs, acc);
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int v = 0; v < 2; ++v) {
+            const int i = (tid & 15) + 16 * u, j = (tid >> 4) + 16 * v;
+            double2 c = zc(i == j ? 1.0 : 0.0, 0.0);
+            if (i < nb && j < nb) c = csub(T[k0 + i + (size_t)j * m], acc[u][v]);
+            Cs[i][j] = c;
+        }
+    __syncthreads();
+    const int j = tid & 63, w = tid >> 6;
+    double ax[8], ay[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        const int i = w + 4 * q;
+        const double2 c = j < kFact ? Cs[i][j & 31] : zc(j - kFact == i ? 1.0 : 0.0, 0.0);
+        ax[q] = c.x;
+        ay[q] = c.y;
     }
-    for (int t = 0; t < rmax; ++t)
-        k_ubig_q<<<dim3((unsigned)((mlev + kUlvChunk - 1) / kUlvChunk), y), kUlvThreads, 0, s>>>(b, t);
-    k_ubig_u2<<<dim3(64, y), 256, 0, s>>>(b);
+    bool bad = false;
+#pragma unroll
+    for (int c = 0; c < kFact; ++c) {
+        if ((c & 3) == w) {
+            double p = __shfl(ax[c >> 2], c);
+            if (!(p > 0.0) || !isfinite(p)) {
+                bad = true;
+                p = 1.0;
+            }
+            p = sqrt(p);
+            ax[c >> 2] /= p;
+            ay[c >> 2] = j == c ? 0.0 : ay[c >> 2] / p;
+            row[c & 1][j] = zc(ax[c >> 2], ay[c >> 2]);
+        }
+        __syncthreads();
+        const double2 rj = row[c & 1][j];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int i = w + 4 * q;
+            if (4 * q + 3 > c) {
+                const double2 ri = row[c & 1][i];
+                if (i > c) {
+                    ax[q] -= ri.x * rj.x + ri.y * rj.y;
+                    ay[q] -= ri.x * rj.y - ri.y * rj.x;
+                }
+            }
+        }
+    }
+    if (bad && j == 0) atomicAdd(fail, 1);
+    double2 *O = Li + (size_t)blockIdx.x * kFact * kFact;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        const int i = w + 4 * q;
+        if (j >= kFact)
+            O[i + (j - kFact) * kFact] = zc(ax[q], ay[q]);
+        else if (i <= j && j < nb)
+            T[k0 + i + (size_t)j * m] = zc(ax[q], ay[q]);
+    }
+}
+
+// The other columns of rows k0 .. k0 + 31 of [T | W], 32 columns per workgroup.  UNIT: W started as
+// the identity, so that only its columns up to the block are not zero.
+template <bool UNIT>
+__global__ void __launch_bounds__(256) k_fact_rows(const TriNode *__restrict__ nodes, int k0,
+                                                  const double2 *__restrict__ Li) {
+    __shared__ double2 As[16][33], Bs[16][33], Cs[kFact][kFact + 1], Ls[kFact][kFact + 1];
+    const TriNode d = nodes[blockIdx.y];
+    if (k0 >= d.k) return;
+    const int m = d.m, nb = d.k - k0 < kFact ? d.k - k0 : kFact, tid = threadIdx.x;
+    const int ct = m - k0 - nb, nt = (ct + 31) / 32;
+    const bool inT = (int)blockIdx.x < nt;
+    const int c0 = inT ? k0 + nb + 32 * blockIdx.x : 32 * (blockIdx.x - nt), cend = inT ? m : UNIT ? k0 + nb : m;
+    if (c0 >= cend) return;
+    const int nc = cend - c0 < 32 ? cend - c0 : 32;
+    double2 *X = (inT ? d.T : d.W) + (size_t)c0 * m;
+    for (int e = tid; e < kFact * kFact; e += 256) Ls[e / kFact][e % kFact] = Li[(size_t)blockIdx.y * kFact * kFact + e];
+    double2 acc[2][2];
+    fact_tile(d.T + (size_t)k0 * m, X, m, UNIT && !inT ? c0 : 0, k0, nb, nc, As, Bs, acc);
+    const int tx = tid & 15, ty = tid >> 4;
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int v = 0; v < 2; ++v) {
+            const int i = tx + 16 * u, j = ty + 16 * v;
+            double2 c = zc(0.0, 0.0);
+            if (i < nb && j < nc) c = csub(X[k0 + i + (size_t)j * m], acc[u][v]);
+            Cs[i][j] = c;
+        }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int v = 0; v < 2; ++v) {
+            const int i = tx + 16 * u, j = ty + 16 * v;
+            if (i >= nb || j >= nc) continue;
+            double2 x = zc(0.0, 0.0);
+            for (int l = 0; l <= i; ++l) cfma(x, Ls[l][i], Cs[l][j]);
+            X[k0 + i + (size_t)j * m] = x;
+        }
+}
+
+// device buffers of the level steps, kept over the levels of a factorization
+struct UlvWork {
+    WyWork wy;
+    DevBuf nodes, Li;
+};
+
+// the row sweep over all nodes of a list (mmax, kmax: the largest m and k)
+static void fact_sweep(const std::vector<TriNode> &nodes, int mmax, int kmax, bool unit, int *fail, UlvWork &w,
+                       hipStream_t s) {
+    const unsigned nn = (unsigned)nodes.size();
+    w.nodes.ensure(nn * sizeof(TriNode));
+    w.Li.ensure((size_t)nn * kFact * kFact * sizeof(double2));
+    FIO_HIP(hipMemcpyAsync(w.nodes.p, nodes.data(), nn * sizeof(TriNode), hipMemcpyHostToDevice, s));
+    const TriNode *d = w.nodes.as<TriNode>();
+    double2 *Li = w.Li.as<double2>();
+    for (int k0 = 0; k0 < kmax; k0 += kFact) {
+        k_fact_diag<<<nn, 256, 0, s>>>(d, k0, Li, fail);
+        // a node with few rows left in this block has more columns to its right
+        const unsigned tiles = (unsigned)((mmax - k0 + 31) / 32 + ((unit ? k0 + kFact : mmax) + 31) / 32);
+        if (unit)
+            k_fact_rows<true><<<dim3(tiles, nn), 256, 0, s>>>(d, k0, Li);
+        else
+            k_fact_rows<false><<<dim3(tiles, nn), 256, 0, s>>>(d, k0, Li);
+    }
     FIO_HIP(hipGetLastError());
-    FIO_HIP(hipStreamSynchronize(s));   // the reflector scalars are released here
+}
+
+// Levels whose largest node has at least this many rows take these kernels: with 1024 leaves of 64 rows (N = 2^16)
+// the factorization takes 3.87 ms with them and 4.84 ms with one workgroup per node, for 2D n = 64 29.6 and
+// 30.6 ms (54.6 from 256 rows on); the levels of 8 rows above the leaves of 1D trees lose with them (4.46 ms).
+constexpr int kUlvBig = 64;
+static int g_ulv_big = kUlvBig;
+
+static void ulv_phase0_big(const FactArgs &fa, const std::vector<int> &ms, const std::vector<int> &rs,
+                           const std::vector<size_t> &scoff, UlvWork &w, hipStream_t s) {
+    const unsigned y = (unsigned)ms.size();
+    k_ubig_init<<<dim3(16, y), 256, 0, s>>>(fa);
+    std::vector<WyNode> un(ms.size()), qn(ms.size());
+    for (size_t j = 0; j < ms.size(); ++j) {
+        double2 *Uw = fa.scratch + scoff[j];
+        un[j] = WyNode{Uw, Uw, ms[j], ms[j], ms[j], rs[j], rs[j]};
+        qn[j] = WyNode{Uw, Uw + (size_t)2 * ms[j] * ms[j], ms[j], ms[j], ms[j], rs[j], ms[j]};
+    }
+    wy_qr(un, w.wy, s);
+    wy_apply(qn, w.wy, true, s);
+    k_ubig_finish<<<dim3(16, y), 256, 0, s>>>(fa);
+    FIO_HIP(hipGetLastError());
+    FIO_HIP(hipStreamSynchronize(s));   // the node lists are released here
+}
+
+static void ulv_phase1_big(const FactArgs &fa, const std::vector<int> &ms, const std::vector<int> &rs,
+                           const std::vector<size_t> &scoff, const std::vector<size_t> &woff, UlvWork &w,
+                           hipStream_t s) {
+    std::vector<TriNode> tn(ms.size());
+    int mmax = 0, kmax = 0;
+    for (size_t j = 0; j < ms.size(); ++j) {
+        tn[j] = TriNode{fa.scratch + scoff[j] + (size_t)2 * ms[j] * ms[j], fa.W + woff[j], ms[j], ms[j] - rs[j]};
+        mmax = ms[j] > mmax ? ms[j] : mmax;
+        kmax = tn[j].k > kmax ? tn[j].k : kmax;
+    }
+    const unsigned t = (unsigned)((mmax + 31) / 32);
+    k_fact_prep<<<dim3(t, t, (unsigned)ms.size()), 256, 0, s>>>(fa);
+    fact_sweep(tn, mmax, kmax, false, fa.fail, w, s);
+    FIO_HIP(hipStreamSynchronize(s));   // the node list is released here
 }
 
 // Merge of eq. ulv_merge for every parent (one workgroup per parent):
@@ -427,89 +576,17 @@ __global__ void __launch_bounds__(1024) k_ulv_merge_fill(MergeArgs a) {
     }
 }
 
-// Root: Cholesky of D+ and the explicit inverse Linv of the lower factor, blocked by
-// kRootBlock columns: the diagonal blocks and the triangular solves run in small kernels,
-// the trailing updates of the Cholesky and of the inverse as GEMMs over the whole GPU.
-constexpr int kRootBlock = 64;
-
-__global__ void __launch_bounds__(256) k_root_diag(double2 *D, int m, int k0, int kb, int *fail) {
-    __shared__ double sh[16];
-    __shared__ int s_flag;
-    if (!wg_potrf(D + k0 + (size_t)k0 * m, m, kb, sh, &s_flag))
-        if (threadIdx.x == 0) atomicAdd(fail, 1);
+__global__ void k_root_eye(double2 *X, int m) {
+    for (long e = blockIdx.x * (long)blockDim.x + threadIdx.x; e < (long)m * m; e += (long)gridDim.x * blockDim.x)
+        X[e] = zc(e % m == e / m ? 1.0 : 0.0, 0.0);
 }
 
-// rows i >= k0 + kb of the block column: x L_kk^* = a (forward over the kb columns)
-__global__ void k_root_panel(double2 *D, int m, int k0, int kb) {
-    const int i = k0 + kb + blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= m) return;
-    for (int j = 0; j < kb; ++j) {
-        double2 acc = D[i + (size_t)(k0 + j) * m];
-        for (int l = 0; l < j; ++l) {
-            const double2 x = D[i + (size_t)(k0 + l) * m], Ljl = D[(k0 + j) + (size_t)(k0 + l) * m];
-            acc.x -= x.x * Ljl.x + x.y * Ljl.y;       // acc -= x conj(Ljl)
-            acc.y -= x.y * Ljl.x - x.x * Ljl.y;
-        }
-        const double d = D[(k0 + j) + (size_t)(k0 + j) * m].x;
-        D[i + (size_t)(k0 + j) * m] = zc(acc.x / d, acc.y / d);
-    }
-}
-
-// PH (kb x rest) = panel^* of D rows k0+kb.., columns k0..k0+kb
-__global__ void k_root_ct(const double2 *D, int m, int k0, int kb, double2 *PH) {
-    const int rest = m - k0 - kb;
-    for (long e = blockIdx.x * (long)blockDim.x + threadIdx.x; e < (long)rest * kb; e += (long)gridDim.x * blockDim.x) {
-        const int j = (int)(e % kb), i = (int)(e / kb);
-        const double2 v = D[(k0 + kb + i) + (size_t)(k0 + j) * m];
-        PH[j + (size_t)i * kb] = zc(v.x, -v.y);
-    }
-}
-
-__global__ void k_root_clear_upper_and_eye(double2 *D, double2 *X, int m) {
-    for (long e = blockIdx.x * (long)blockDim.x + threadIdx.x; e < (long)m * m; e += (long)gridDim.x * blockDim.x) {
-        const int i = (int)(e % m), j = (int)(e / m);
-        if (j > i) D[e] = zc(0.0, 0.0);
-        X[e] = zc(i == j ? 1.0 : 0.0, 0.0);
-    }
-}
-
-// rows k0..k0+kb of X <- L_kk^{-1} rows k0..k0+kb of X, one lane per column
-__global__ void k_root_fwd(const double2 *D, double2 *X, int m, int k0, int kb) {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= m) return;
-    for (int j = 0; j < kb; ++j) {
-        double2 acc = X[(k0 + j) + (size_t)c * m];
-        for (int l = 0; l < j; ++l) acc = csub(acc, cmul(D[(k0 + j) + (size_t)(k0 + l) * m], X[(k0 + l) + (size_t)c * m]));
-        const double d = D[(k0 + j) + (size_t)(k0 + j) * m].x;
-        X[(k0 + j) + (size_t)c * m] = zc(acc.x / d, acc.y / d);
-    }
-}
-
-static void ulv_root_factor(double2 *D, int m, double2 *Linv, int *fail, hipStream_t s) {
-    const int nb = kRootBlock;
-    DevBuf ph((size_t)nb * m * sizeof(double2) + 16);
-    for (int k0 = 0; k0 < m; k0 += nb) {
-        const int kb = m - k0 < nb ? m - k0 : nb, rest = m - k0 - kb;
-        k_root_diag<<<1, 256, 0, s>>>(D, m, k0, kb, fail);
-        if (rest == 0) break;
-        k_root_panel<<<(rest + 255) / 256, 256, 0, s>>>(D, m, k0, kb);
-        k_root_ct<<<64, 256, 0, s>>>(D, m, k0, kb, ph.as<double2>());
-        // trailing update D22 -= P P^* (the whole square; only the lower triangle is used)
-        ZgemmDesc d{D + (k0 + kb) + (size_t)k0 * m, ph.as<double2>(), D + (k0 + kb) + (size_t)(k0 + kb) * m,
-                    rest, rest, kb, m, kb, m};
-        zgemm_one(d, false, zc(-1.0, 0.0), zc(1.0, 0.0), s);
-    }
-    k_root_clear_upper_and_eye<<<256, 256, 0, s>>>(D, Linv, m);
-    // Linv: blocked forward substitution of L X = I
-    for (int k0 = 0; k0 < m; k0 += nb) {
-        const int kb = m - k0 < nb ? m - k0 : nb, rest = m - k0 - kb;
-        k_root_fwd<<<(m + 255) / 256, 256, 0, s>>>(D, Linv, m, k0, kb);
-        if (rest == 0) break;
-        ZgemmDesc d{D + (k0 + kb) + (size_t)k0 * m, Linv + k0, Linv + (k0 + kb), rest, m, kb, m, m, m};
-        zgemm_one(d, false, zc(-1.0, 0.0), zc(1.0, 0.0), s);
-    }
-    FIO_HIP(hipGetLastError());
-    FIO_HIP(hipStreamSynchronize(s));     // the panel buffer is released here
+// Root: the row sweep on [D+ | I] leaves Linv = L_rho^{-1}
+static void ulv_root_factor(double2 *D, int m, double2 *Linv, int *fail, UlvWork &w, hipStream_t s) {
+    k_root_eye<<<256, 256, 0, s>>>(Linv, m);
+    const std::vector<TriNode> tn{TriNode{D, Linv, m, m}};
+    fact_sweep(tn, m, m, true, fail, w, s);
+    FIO_HIP(hipStreamSynchronize(s));     // the node list is released here
 }
 
 // One level of the ULV solve.  UP: z = W y_tau, rows < k to Bh, rows >= k to the parent's
@@ -890,6 +967,7 @@ static fio_status factor_impl(hss_s *h, hipStream_t s, hss_ulv_t *out) {
         FIO_HIP(hipMemsetAsync(failb.p, 0, sizeof(int), s));
         // level-by-level factorization
         DevBuf Dcur, Ucur, D22, U2, scr, tmp;
+        UlvWork uw;
         const double2 *Din = h->Dbuf.as<double2>();
         std::vector<size_t> din_off(h->nodes(Lh)), uin_off = h->uoff[Lh];
         for (int j = 0; j < h->nodes(Lh); ++j) din_off[j] = (size_t)j * h->leaf * h->leaf;
@@ -937,9 +1015,7 @@ static fio_status factor_impl(hss_s *h, hipStream_t s, hss_ulv_t *out) {
                 k_ulv_node<0><<<nn, ulv_threads(mlev), 0, s>>>(fa);
                 FIO_HIP(hipGetLastError());
             } else {
-                int rmax = 0;
-                for (int v : f->r[l]) rmax = v > rmax ? v : rmax;
-                ulv_phase0_big(fa, nn, mlev, rmax, s);
+                ulv_phase0_big(fa, f->m[l], f->r[l], scoff, uw, s);
             }
             {
                 // Dchk = Q^* D Q for every node of the level: W slot <- Q^* D, T <- (Q^* D) Q
@@ -958,8 +1034,12 @@ static fio_status factor_impl(hss_s *h, hipStream_t s, hss_ulv_t *out) {
                 g2.run(false, zc(1.0, 0.0), zc(0.0, 0.0), s);
                 FIO_HIP(hipStreamSynchronize(s));   // the descriptor lists are released here
             }
-            k_ulv_node<1><<<nn, ulv_threads(mlev), 0, s>>>(fa);
-            FIO_HIP(hipGetLastError());
+            if (mlev < g_ulv_big) {
+                k_ulv_node<1><<<nn, ulv_threads(mlev), 0, s>>>(fa);
+                FIO_HIP(hipGetLastError());
+            } else {
+                ulv_phase1_big(fa, f->m[l], f->r[l], scoff, f->woff[l], uw, s);
+            }
             {
                 // Dhat22 = Dchk22 - X^* X and W2 = Q2^* - X^* W1 for every node of the level, with
                 // X = Dhat21^* (k x r) left in T(0..k, k..m) by the node kernel
@@ -1061,7 +1141,7 @@ static fio_status factor_impl(hss_s *h, hipStream_t s, hss_ulv_t *out) {
             uin_off = uooff;
         }
         if (f->m0 > 0) {
-            ulv_root_factor(Dcur.as<double2>(), f->m0, f->Linv.as<double2>(), failb.as<int>(), s);
+            ulv_root_factor(Dcur.as<double2>(), f->m0, f->Linv.as<double2>(), failb.as<int>(), uw, s);
             int fail = 0;
             FIO_HIP(hipMemcpy(&fail, failb.p, sizeof(int), hipMemcpyDeviceToHost));
             if (fail) throw Err{FIO_ERR_NOT_HPD};
@@ -1272,4 +1352,4 @@ extern "C" fio_status hss_ulv_solve(hss_ulv_t f, const void *Y, long ldy, void *
 
 extern "C" void hss_ulv_destroy(hss_ulv_t f) { delete f; }
 
-extern "C" void fio_ulv_set_big_node(int rows) { fio::g_ulv_big = rows > 0 ? rows : 256; }
+extern "C" void fio_ulv_set_big_node(int rows) { fio::g_ulv_big = rows > 0 ? rows : fio::kUlvBig; }
