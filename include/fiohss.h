@@ -219,7 +219,7 @@ fio_status fio_bf_set_tile(fio_bf_t bf, int adj, fio_prec prec, int nrhs, int kc
 /* One tile configuration of an apply (fio_bf_autotune's candidates).  0 everywhere is the
  * built-in default. */
 typedef struct {
-    int kc;        /* dim 2: column chunk of the workgroups, 0, 8 or 16 */
+    int kc;        /* dim 2: right-hand sides per wave, 0 (the default, 8), 8 or 16 */
     int nsplit;    /* dim 2: reduction split of the U and V^* steps, 0 or a power of two dividing the
                       partner count, at most 16 */
     int kmax;      /* dim 1: transfer levels per fused pass, 0 (as many as a pass holds) or 1..3 */

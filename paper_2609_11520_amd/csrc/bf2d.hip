@@ -26,15 +26,18 @@
 //   Madj block (tau' * 4^h + sigma) * rr + d = M_{tau' rr + d, sigma}^*  (q^2 x q^2)
 //   Uadj block p = U_p^*  (q^2 x b^2)
 //
-// Apply: one kernel per factor.  A workgroup owns one output block (a pair's
-// q^2 coefficients, or a leaf box's b^2 values) for a chunk of KC right-hand
-// sides; lane r accumulates row r for the KC columns; the factor block streams
-// from HBM once per chunk, the input coefficients are wave-uniform reads.  The
-// leaf-box sums over 4^lc blocks are split over workgroups and reduced in a
-// fixed order (deterministic results).
+// Apply: one kernel per factor (k2_mm).  A wave owns up to 6 x 16 rows of one output block (a pair's
+// q^2 coefficients, or a leaf box's b^2 values) for 8 or 16 right-hand sides and runs the products on the
+// matrix cores.  The leaf-box sums over 4^lc blocks are split over waves and reduced in a fixed
+// order; every column is summed in the same order at any width and split of rows (deterministic
+// results).  Few columns: the factor stream bounds it (n = 128, 8 columns: 9.6 GB in 1.90 ms, 5.0 TB/s; one
+// lane per row took 1.97 ms).  Many columns: the FP64 matrix rate (n = 64, 144 columns: 46 of 75
+// TFLOP/s with the 81 rows padded to 96; one lane per row reached 24).  In between the launches of few, long waves: n = 8
+// 105 -> 27 us, n = 16 80 -> 26 us at 8 columns.
 //
-// Coefficient buffers: entry (pair p, coefficient i, column c) at
-// (p q^2 + i) * ldc + c with ldc = nrhs rounded up to KC.
+// Coefficient buffers: entry (pair p, coefficient i, column c) at (p q^2 + i) * ldc + c with ldc = nrhs
+// rounded up to the columns of a wave; the adjoint steps store their pairs in the order in which
+// the next step sums them.
 #include <cmath>
 
 #include "bf.h"
@@ -273,169 +276,239 @@ template <typename T> struct K2Args {
     const cpx<T> *cin;      // input coefficients (MF, UF, MA, VA)
     const double2 *X;       // input vector (VF: frequency side, UA: spatial side)
     long ldx;
-    cpx<T> *cout;           // output coefficients (VF, MF, UA, MA)
+    cpx<T> *cout;           // output coefficients (VF, MF, UA, MA) or partial sums (UF, VA, nsplit > 1)
     double2 *Y;             // output vector (UF: spatial side, VA: frequency side), when nsplit == 1
-    cpx<T> *part;           // split partial sums (UF, VA), when nsplit > 1
     long ldy;
     int nrhs, ldc;          // right-hand sides, coefficient row stride
     int nb, nsplit;         // blocks per output, splits of the block range
     int fint;               // frequency-side vectors in Morton order (no index map)
-    long nout;              // output blocks (workgroup rows) of the launch
+    int step, rows, cols;   // the Step, rows and columns of a factor block
+    int rgroups, cgroups;   // row and column groups (waves) of an output
+    unsigned nwave;         // waves of the launch: output blocks x splits x groups
 };
 
-template <typename C> __device__ __forceinline__ C to_c(double2 v);
-template <> __device__ __forceinline__ double2 to_c<double2>(double2 v) { return v; }
-template <> __device__ __forceinline__ float2 to_c<float2>(double2 v) { return make_float2((float)v.x, (float)v.y); }
 __device__ __forceinline__ double2 to_z(double2 v) { return v; }
 __device__ __forceinline__ double2 to_z(float2 v) { return zc(v.x, v.y); }
 
-// rows of one output block / columns of one factor block, per step
-template <int STEP> __device__ __forceinline__ int rows_of(const G2 &g) {
-    return (STEP == UF || STEP == VA) ? g.b2 : g.q2;
+// 16 x 16 tile of four reals per lane: lane l holds column l & 15
+template <typename T> struct Mat4;
+template <> struct Mat4<double> {
+    using V = double __attribute__((ext_vector_type(4)));
+    static __device__ __forceinline__ V mac(double a, double b, V c) {
+        return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+    }
+    static __device__ __forceinline__ int row(int lane, int i) { return (lane >> 4) + 4 * i; }
+};
+template <> struct Mat4<float> {
+    using V = float __attribute__((ext_vector_type(4)));
+    static __device__ __forceinline__ V mac(float a, float b, V c) {
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+    }
+    static __device__ __forceinline__ int row(int lane, int i) { return 4 * (lane >> 4) + i; }
+};
+
+// the other half of a 16-lane row: lane l gets lane l xor 8
+__device__ __forceinline__ float row_half(float v) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x128, 0xf, 0xf, true));
 }
-template <int STEP> __device__ __forceinline__ int cols_of(const G2 &g) {
-    return (STEP == VF || STEP == UA) ? g.b2 : g.q2;
+__device__ __forceinline__ double row_half(double v) {
+    const long b = __builtin_bit_cast(long, v);
+    const int lo = __builtin_amdgcn_mov_dpp((int)b, 0x128, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), 0x128, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, ((long)hi << 32) | (unsigned)lo);
 }
 
-template <typename T, int KC, int STEP>
-__global__ void __launch_bounds__(128) k2_step(K2Args<T> a) {
+// One step of an apply: each wave forms NR x 16 rows of an output block for 8 NC right-hand sides on
+// the matrix cores.  The real and imaginary parts of 8 columns are the 16 columns of one real tile, so that
+// A_r X and A_i X are two products, combined once at the end, and a block of 8 columns wastes
+// nothing.  The blocks of one output and the coefficients they act on are consecutive in memory, so the
+// product runs over all their columns as one inner dimension, 4 at a time; entries go straight from
+// memory to registers, D steps ahead, at a wave-uniform address plus a lane offset that does not change.
+template <typename T, int NR, int NC, bool VEC, int D>
+__global__ void __launch_bounds__(256) k2_mm(K2Args<T> a) {
     using C = cpx<T>;
+    using M = Mat4<T>;
+    using V = typename M::V;
     const G2 &g = a.g;
-    const int R = rows_of<STEP>(g), CC = cols_of<STEP>(g);
-    const int r = threadIdx.x;
-    // grid: x = column chunk (fastest, so the chunks of one output block run together and share
-    // its factor blocks through L2), y (+ z) = output block, z = split for the leaf-box sums
-    const bool splitk = STEP == UF || STEP == VA;
-    const long o = splitk ? (long)blockIdx.y : (long)blockIdx.y + (long)blockIdx.z * gridDim.y;
-    const int split = splitk ? (int)blockIdx.z : 0;
-    const int c0 = blockIdx.x * KC;
-    if (o >= a.nout) return;
-    const int nc = min(KC, a.nrhs - c0);
-    const bool act = r < R;
-    C acc[KC];
+    const int lane = threadIdx.x & 63, lr = lane & 15, lk = lane >> 4;
+    // consecutive workgroups run on one XCD, whose L2 then serves the column groups of an output
+    const unsigned wg = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    const unsigned W = wg * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (W >= a.nwave) return;
+    const unsigned tiles = a.rgroups * a.cgroups;
+    const int os = (int)(W / tiles), tile = (int)(W - os * tiles), o = os / a.nsplit, split = os - o * a.nsplit;
+    const int lS = 2 * g.h, lT = 2 * g.lc, S = 1 << lS, TT = 1 << lT, lrr = lS - lT;   // S, T and rr = S / T
+    const int rg = tile / a.cgroups, c0 = (tile - rg * a.cgroups) * 8 * NC, r0 = rg * 16 * NR;
+    const int R = a.rows, nbs = a.nb / a.nsplit, K = nbs * a.cols, nfull = K >> 2, rem = K & 3;
+    // factor entries: rows beyond the block repeat its last one and are not stored
+    const char *pa = reinterpret_cast<const char *>(a.A + ((size_t)o * a.nb + (size_t)split * nbs) * R * a.cols);
+    const int astep = 4 * R * (int)sizeof(C);
+    unsigned va[NR];
 #pragma unroll
-    for (int c = 0; c < KC; ++c) acc[c] = czero<C>();
-    const int nbs = a.nb / a.nsplit;
-    // lanes beyond the block's rows read its last row (no lane condition on the loads, which would
-    // put each one in a block of its own and wait for it there) and store nothing
-    const int rc = act ? r : R - 1;
-    for (int bb = split * nbs; bb < (split + 1) * nbs; ++bb) {
-        const C *Ab = a.A + ((size_t)o * a.nb + bb) * R * CC + rc;
-        if (STEP == VF || STEP == UA) {
-            // input from a user vector: the b^2 points of one leaf box
-            const long base = (STEP == VF) ? (o % g.S) * g.b2 : (o / g.T) * g.b2;
-            const bool internal = STEP == VF && a.fint;
-            for (int j = 0; j < CC; ++j) {
-                const C av = Ab[(size_t)j * R];
-                const long m = base + j;
-                const long row = internal ? m : lex_of(m, g.L, g.n);
-                const double2 *xp = a.X + row + (size_t)c0 * a.ldx;
-#pragma unroll
-                for (int c = 0; c < KC; ++c) {
-                    const C x = c < nc ? to_c<C>(xp[(size_t)c * a.ldx]) : czero<C>();
-                    cfma(acc[c], av, x);
-                }
-            }
-        } else {
-            long srow;
-            if (STEP == MF) {
-                const long u = o / g.T, v = o % g.T;
-                srow = (u / g.rr) * g.S + v * g.rr + bb;
-            } else if (STEP == UF) {
-                srow = o * g.T + bb;
-            } else if (STEP == MA) {
-                const long taup = o / g.S, sigma = o % g.S;
-                srow = (taup * g.rr + bb) * g.T + sigma / g.rr;
-            } else {   // VA
-                srow = bb * g.S + o;
-            }
-            const C *xp = a.cin + (size_t)srow * g.q2 * a.ldc + c0;
-#pragma unroll 3
-            for (int j = 0; j < CC; ++j) {
-                const C av = Ab[(size_t)j * R];
-#pragma unroll
-                for (int c = 0; c < KC; ++c) cfma(acc[c], av, xp[(size_t)j * a.ldc + c]);
-            }
-        }
+    for (int t = 0; t < NR; ++t) {
+        const int r = r0 + 16 * t + lr;
+        va[t] = (unsigned)(lk * R + (r < R ? r : R - 1)) * (unsigned)sizeof(C);
     }
-    if (!act) return;
-    if (STEP == UF || STEP == VA) {
-        if (a.nsplit > 1) {
-            C *pp = a.part + (((size_t)split * a.nout + o) * R + r) * a.ldc + c0;
+    // inputs: the points of one leaf box (VEC) or the coefficients of the output's partner pairs
+    const char *pb;
+    unsigned bstep = 0;
+    size_t vb[NC];
+    bool inner = false;
+    if (VEC) {
+        const int box = a.step == VF ? o & (S - 1) : o >> lT;
+        inner = a.step == VF && a.fint;
+        pb = reinterpret_cast<const char *>(a.X + (inner ? (long)box * g.b2 : lex_of((long)box * g.b2, g.L, g.n)));
+        // the lane's point among 4: Morton bits 1 and 0
+        const long pt = inner ? lk : (long)(lk >> 1) * g.n + (lk & 1);
 #pragma unroll
-            for (int c = 0; c < KC; ++c) pp[c] = acc[c];
-        } else {
-            const long m = o * g.b2 + r;
-            const long row = (STEP == VA && a.fint) ? m : lex_of(m, g.L, g.n);
-            double2 *yp = a.Y + row + (size_t)c0 * a.ldy;
-#pragma unroll
-            for (int c = 0; c < KC; ++c)
-                if (c < nc) yp[(size_t)c * a.ldy] = to_z(acc[c]);
+        for (int u = 0; u < NC; ++u) {
+            const int c = c0 + 8 * u + (lr & 7);
+            vb[u] = (pt + (size_t)(c < a.nrhs ? c : a.nrhs - 1) * a.ldx) * sizeof(double2) + (lr >> 3) * sizeof(double);
         }
     } else {
-        C *cp = a.cout + ((size_t)o * g.q2 + r) * a.ldc + c0;
+        int pair = split * nbs;                // the first partner pair, as stored (see the end), or leaf box
+        if (a.step == VF)
+            pair = o & (S - 1);
+        else if (a.step == UA)
+            pair = o >> lT;
+        else if (a.step == MF)
+            pair += ((o >> lS) << lS) + ((o & (TT - 1)) << lrr);
+        else if (a.step == MA)
+            pair += (((o >> lS) << lT) + ((o & (S - 1)) >> lrr)) << lrr;
+        else
+            pair += o << lT;
+        pb = reinterpret_cast<const char *>(a.cin + (size_t)pair * a.cols * a.ldc + c0);
+        bstep = 4 * a.ldc * (unsigned)sizeof(C);
 #pragma unroll
-        for (int c = 0; c < KC; ++c) cp[c] = acc[c];
+        for (int u = 0; u < NC; ++u)
+            vb[u] = (unsigned)((lk * a.ldc + 8 * u + (lr & 7)) * sizeof(C) + (lr >> 3) * sizeof(T));
     }
+    // offset of the inputs of step k (wave-uniform)
+    auto boff = [&](int k) -> size_t {
+        if (!VEC) return (size_t)k * bstep;
+        if (inner) return (size_t)k * 4 * sizeof(double2);
+        const int j1 = ((k >> 1) & 1) | ((k >> 2) & 2), j2 = (k & 1) | ((k >> 1) & 2);   // hb <= 3
+        return ((size_t)2 * j1 * g.n + 2 * j2) * sizeof(double2);
+    };
+    auto bval = [&](const char *p) -> T {
+        if (VEC) return (T) * reinterpret_cast<const double *>(p);
+        return *reinterpret_cast<const T *>(p);
+    };
+    C fa[D][NR], ta[NR];
+    T fb[D][NC], tb[NC];
+    auto load = [&](C(&xa)[NR], T(&xb)[NC], int k) {
+        const char *qa = pa + (size_t)k * astep, *qb = pb + boff(k);
+#pragma unroll
+        for (int t = 0; t < NR; ++t) xa[t] = *reinterpret_cast<const C *>(qa + va[t]);
+#pragma unroll
+        for (int u = 0; u < NC; ++u) xb[u] = bval(qb + vb[u]);
+    };
+    V P[NR][NC], Q[NR][NC];
+#pragma unroll
+    for (int t = 0; t < NR; ++t)
+#pragma unroll
+        for (int u = 0; u < NC; ++u) P[t][u] = Q[t][u] = V{0, 0, 0, 0};
+    auto mac = [&](const C(&xa)[NR], const T(&xb)[NC]) {
+#pragma unroll
+        for (int t = 0; t < NR; ++t)
+#pragma unroll
+            for (int u = 0; u < NC; ++u) {
+                P[t][u] = M::mac(xa[t].x, xb[u], P[t][u]);
+                Q[t][u] = M::mac(xa[t].y, xb[u], Q[t][u]);
+            }
+    };
+    if (!VEC && rem) {
+        // the K mod 4 last columns first: lanes beyond them read the first of these and count zero (a leaf box
+        // has a multiple of 4 points)
+        const bool in = lk < rem;
+        const char *qa = pa + (size_t)nfull * astep - (in ? 0 : (size_t)lk * R * sizeof(C));
+        const char *qb = pb + boff(nfull);
+        if (!in) qb -= (size_t)lk * a.ldc * sizeof(C);
+#pragma unroll
+        for (int t = 0; t < NR; ++t) {
+            ta[t] = *reinterpret_cast<const C *>(qa + va[t]);
+            if (!in) ta[t] = czero<C>();
+        }
+#pragma unroll
+        for (int u = 0; u < NC; ++u) {
+            tb[u] = bval(qb + vb[u]);
+            if (!in) tb[u] = T(0);
+        }
+    }
+#pragma unroll
+    for (int d = 0; d < D; ++d)
+        if (d < nfull) load(fa[d], fb[d], d);
+    if (!VEC && rem) mac(ta, tb);
+    int k = 0;
+    for (; k + D <= nfull; k += D) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            mac(fa[d], fb[d]);
+            if (k + d + D < nfull) load(fa[d], fb[d], k + d + D);
+        }
+    }
+#pragma unroll
+    for (int d = 0; d < D; ++d)
+        if (k + d < nfull) mac(fa[d], fb[d]);
+    // lanes of columns 0 .. 7 hold A_r X_r and A_i X_r, the others A_r X_i and A_i X_i
+    const bool im = lr >= 8;
+    // where the pair is stored: in the order in which the next step reads
+    int at = os;
+    if (a.step == UA)
+        at = ((((o >> lT) >> lrr << lT) + (o & (TT - 1))) << lrr) + ((o >> lT) & ((1 << lrr) - 1));
+    else if (a.step == MA)
+        at = ((o & (S - 1)) << lT) + (o >> lS);
+    C *out = a.cout ? a.cout + (size_t)at * R * a.ldc + c0 : nullptr;
+    const long ybase = (a.step == VA && a.fint) ? (long)o * g.b2 : lex_of((long)o * g.b2, g.L, g.n);
+#pragma unroll
+    for (int t = 0; t < NR; ++t)
+#pragma unroll
+        for (int u = 0; u < NC; ++u)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                // a lane gets the entry of row i, the lane 8 on that of row i + 2
+                const T tp = row_half(im ? P[t][u][i] : P[t][u][i + 2]), tq = row_half(im ? Q[t][u][i] : Q[t][u][i + 2]);
+                C v;
+                v.x = im ? tp - Q[t][u][i + 2] : P[t][u][i] - tq;
+                v.y = im ? P[t][u][i + 2] + tq : tp + Q[t][u][i];
+                const int r = r0 + 16 * t + M::row(lane, i) + (im ? M::row(0, 2) : 0), c = 8 * u + (lr & 7);
+                if (r >= R) continue;
+                if (out) {
+                    out[(unsigned)(r * a.ldc + c)] = v;
+                } else if (c0 + c < a.nrhs) {
+                    int j1, j2;
+                    demorton(r, g.hb, j1, j2);
+                    const long row = ybase + ((a.step == VA && a.fint) ? r : (long)j1 * g.n + j2);
+                    a.Y[row + (size_t)(c0 + c) * a.ldy] = to_z(v);
+                }
+            }
 }
 
-// VF / UA: the input is the user vector on one leaf box (b^2 points, gathered through the
-// index map), shared by G consecutive output pairs of the workgroup: it is staged once in
-// LDS and read back as wave-uniform broadcasts, while the G factor blocks stream from HBM.
-//   VF: box sigma, outputs (tau' = t0 + g) * S + sigma;  UA: box tau, outputs tau * T + v0 + g.
-template <typename T, int KC, int STEP, int G>
-__global__ void __launch_bounds__(128) k2_leaf_in(K2Args<T> a) {
-    using C = cpx<T>;
-    const G2 &g = a.g;
-    constexpr int MAXB2 = 128;
-    __shared__ C xs[MAXB2 * KC];
-    const int R = g.q2, CC = g.b2;
-    const int r = threadIdx.x;
-    const long groups = g.T / G;
-    const long wg = (long)blockIdx.y + (long)blockIdx.z * gridDim.y;   // x = column chunk (fastest)
-    if (wg >= a.nout) return;
-    const long box = wg / groups;
-    const long first = (wg % groups) * G;
-    const int c0 = blockIdx.x * KC;
-    const int nc = min(KC, a.nrhs - c0);
-    const bool internal = STEP == VF && a.fint;
-    for (int e = threadIdx.x; e < CC * KC; e += blockDim.x) {
-        const int j = e / KC, c = e % KC;
-        const long m = box * g.b2 + j;
-        const long row = internal ? m : lex_of(m, g.L, g.n);
-        xs[e] = c < nc ? to_c<C>(a.X[row + (size_t)(c0 + c) * a.ldx]) : czero<C>();
-    }
-    __syncthreads();
-    if (r >= R) return;
-    for (int gg = 0; gg < G; ++gg) {
-        const long o = STEP == VF ? (first + gg) * g.S + box : box * g.T + first + gg;
-        const C *Ab = a.A + (size_t)o * R * CC + r;
-        C acc[KC];
-#pragma unroll
-        for (int c = 0; c < KC; ++c) acc[c] = czero<C>();
-#pragma unroll 4
-        for (int j = 0; j < CC; ++j) {
-            const C av = Ab[(size_t)j * R];
-#pragma unroll
-            for (int c = 0; c < KC; ++c) cfma(acc[c], av, xs[j * KC + c]);
-        }
-        C *cp = a.cout + ((size_t)o * g.q2 + r) * a.ldc + c0;
-#pragma unroll
-        for (int c = 0; c < KC; ++c) cp[c] = acc[c];
-    }
+// P(m, c) = X(point m, c): an input block in internal point order, columns fastest, padded to ldc
+template <typename T>
+__global__ void k2_pack(G2 g, const double2 *X, long ldx, int nrhs, int ldc, int inner, cpx<T> *P) {
+    const size_t id = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
+    if (id >= (size_t)g.S * g.b2 * ldc) return;
+    const int c = (int)(id % ldc);
+    const long m = (long)(id / ldc);
+    const double2 x = X[(inner ? m : lex_of(m, g.L, g.n)) + (size_t)(c < nrhs ? c : nrhs - 1) * ldx];
+    cpx<T> v;
+    v.x = (T)x.x;
+    v.y = (T)x.y;
+    P[id] = v;
 }
 
 // fixed-order sum of the split partials, scattered to the user vector
 template <typename T>
-__global__ void k2_reduce(G2 g, const cpx<T> *part, int nsplit, long nout, int ldc, int nrhs, int frequency,
-                          int fint, double2 *Y, long ldy) {
+__global__ void k2_reduce(G2 g, const cpx<T> *part, int nsplit, int ldc, int nrhs, int frequency, int fint, double2 *Y, long ldy) {
     const size_t id = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
-    const size_t tot = (size_t)nout * g.b2 * nrhs;
+    const size_t tot = (size_t)g.S * g.b2 * nrhs;
     if (id >= tot) return;
     const int c = (int)(id % nrhs);
     const long m = (long)(id / nrhs);               // o * b2 + r
+    const cpx<T> *p = part + ((size_t)(m / g.b2) * nsplit * g.b2 + m % g.b2) * ldc + c;
     cpx<T> s = czero<cpx<T>>();
-    for (int k = 0; k < nsplit; ++k) s = cadd(s, part[((size_t)k * nout * g.b2 + m) * ldc + c]);
+    for (int k = 0; k < nsplit; ++k) s = cadd(s, p[(size_t)k * g.b2 * ldc]);
     const long row = (frequency && fint) ? m : lex_of(m, g.L, g.n);
     Y[row + (size_t)c * ldy] = to_z(s);
 }
@@ -456,39 +529,50 @@ __global__ void k_perm2(int n, int L, int to_int, const double2 *X, long ldx, do
 
 int nsplit_of(long nb) { return (int)(nb < 16 ? nb : 16); }
 
-// output pairs per workgroup of the leaf-input steps: 8 when the box has that many partners
-// grid for `n` workgroup rows with the column chunks fastest: (chunks, min(n, 32768), rest)
-dim3 grid_rows(unsigned chunks, long n) {
-    const long gy = n < 32768 ? n : 32768;
-    return dim3(chunks, (unsigned)gy, (unsigned)((n + gy - 1) / gy));
+constexpr long kFewWaves = 2048;
+
+template <typename T, int NR, int NC, bool VEC, int D> void launch_mm(K2Args<T> &a, long nout, hipStream_t s) {
+    const int nrt = (a.rows + 15) / 16;
+    a.rgroups = (nrt + NR - 1) / NR;
+    const long nwave = nout * a.nsplit * a.rgroups * a.cgroups, wgs = (nwave + 3) / 4;
+    if (nwave > (1L << 31)) throw Err{FIO_ERR_UNSUPPORTED};
+    a.nwave = (unsigned)nwave;
+    k2_mm<T, NR, NC, VEC, D><<<dim3((unsigned)((wgs + 7) / 8 * 8)), 256, 0, s>>>(a);
 }
 
-template <typename T, int KC, int STEP>
-void launch_leaf_in(const K2Args<T> &a_in, const G2 &g, unsigned chunks, unsigned blk, hipStream_t s) {
-    K2Args<T> a = a_in;
-    const long G = g.T >= 8 ? 8 : 1;
-    a.nout = g.S * (g.T / G);
-    if (G == 8)
-        k2_leaf_in<T, KC, STEP, 8><<<grid_rows(chunks, a.nout), blk, 0, s>>>(a);
+// Rows per wave.  At most 4 tiles (2 waves per SIMD hide little, fewer rows read the inputs more often), in the
+// fewest equal groups; fewer when that leaves the card without 2 waves per SIMD (n = 16, 8 columns: 40.0 us
+// with 3 tiles, 28.8 us with 1 or 2, which also look 4 steps ahead); the 6 tiles of q = 9 in one wave when
+// a single column group streams the factors (n = 128, 8 columns: 2006 us with 3 + 3 tiles, 1900 us).
+template <typename T, int NC, bool VEC> void run_step(K2Args<T> &a, long nout, hipStream_t s) {
+    a.cgroups = a.ldc / (8 * NC);
+    const int nrt = (a.rows + 15) / 16, groups = (nrt + 3) / 4, nr = (nrt + groups - 1) / groups;
+    const long waves = nout * a.nsplit * a.cgroups;            // per row group
+    if (nr == 1 || waves * ((nrt + 1) / 2) < kFewWaves)
+        launch_mm<T, 1, NC, VEC, 4>(a, nout, s);
+    else if (nr == 2 || waves * groups < kFewWaves)
+        launch_mm<T, 2, NC, VEC, 4>(a, nout, s);
+    else if (NC == 1 && (nrt == 5 || nrt == 6) && a.cgroups == 1 && waves >= 4 * kFewWaves)
+        launch_mm<T, 6, 1, VEC, 2>(a, nout, s);
+    else if (nr == 3)
+        launch_mm<T, 3, NC, VEC, 2>(a, nout, s);
     else
-        k2_leaf_in<T, KC, STEP, 1><<<grid_rows(chunks, a.nout), blk, 0, s>>>(a);
+        launch_mm<T, 4, NC, VEC, 2>(a, nout, s);
 }
 
-// KC columns per workgroup: 8 for few right-hand sides, 16 for wide blocks (the HSS sample
-// blocks), which halves how often the factors stream while the FMAs per factor entry double
-template <typename T, int KC>
+// NC x 8 columns per wave
+template <typename T, int NC>
 void apply2k(fio_bf_s *bf, bool adj, const double2 *X, long ldx, double2 *Y, long ldy, int nrhs, const cpx<T> *F,
              const cpx<T> *Fa, void *ws, bool fint, int nsplit, hipStream_t s) {
     using C = cpx<T>;
     const G2 g = g2_of(bf);
+    constexpr int KC = 8 * NC;
     const int ldc = (nrhs + KC - 1) / KC * KC;
     const size_t ncoef = (size_t)bf->N * g.q2 * ldc;
     C *c1 = reinterpret_cast<C *>(ws);
     C *c2 = c1 + ncoef;
     C *part = c2 + ncoef;
-    const unsigned chunks = (unsigned)(ldc / KC);
     const bool f64 = sizeof(T) == 8;
-    const unsigned blkq = 64 * ((g.q2 + 63) / 64), blkb = 64 * ((g.b2 + 63) / 64);
     const long NP = bf->N;                            // pairs on either side
     // reduction split of the U / V^* steps: a power of two dividing the T partner blocks, at most
     // nsplit_of(T) (the workspace holds that many partial sums)
@@ -499,57 +583,64 @@ void apply2k(fio_bf_s *bf, bool adj, const double2 *X, long ldx, double2 *Y, lon
     a.nrhs = nrhs;
     a.ldc = ldc;
     a.fint = fint ? 1 : 0;
+    a.X = X;
+    a.ldx = ldx;
+    a.Y = Y;
+    a.ldy = ldy;
+    // leaf-input, middle and leaf-output step of the direction
+    auto first = [&](int step, const C *A, C *out, C *spare) {
+        K2Args<T> v = a;
+        v.step = step; v.A = A; v.cin = spare; v.cout = out; v.nb = 1; v.nsplit = 1; v.rows = g.q2; v.cols = g.b2;
+        // the columns of a user vector are gathered once into rows when 64 or more outputs read a box (n = 64:
+        // 70 columns 1087 -> 1031 us, 8 columns 267 -> 263 us; n = 32, 16 partners: 8 columns 117 -> 120 us)
+        if (nrhs < 8 || g.T < 64) {
+            run_step<T, NC, true>(v, NP, s);
+        } else {
+            k2_pack<T><<<grid1d((size_t)bf->N * ldc, 256), 256, 0, s>>>(g, X, ldx, nrhs, ldc, step == VF && fint, spare);
+            run_step<T, NC, false>(v, NP, s);
+        }
+    };
+    auto middle = [&](int step, const C *A, const C *in, C *out) {
+        K2Args<T> v = a;
+        v.step = step; v.A = A; v.cin = in; v.cout = out; v.nb = (int)g.rr; v.nsplit = 1; v.rows = v.cols = g.q2;
+        run_step<T, NC, false>(v, NP, s);
+    };
+    auto last = [&](int step, const C *A, const C *in) {
+        K2Args<T> v = a;
+        v.step = step; v.A = A; v.cin = in; v.cout = nsp > 1 ? part : nullptr; v.nb = (int)g.T; v.nsplit = nsp;
+        v.rows = g.b2; v.cols = g.q2;
+        run_step<T, NC, false>(v, g.S, s);
+        if (nsp > 1)
+            k2_reduce<T><<<grid1d((size_t)g.S * g.b2 * nrhs, 256), 256, 0, s>>>(g, part, nsp, ldc, nrhs, step == VA,
+                                                                              a.fint, Y, ldy);
+    };
     if (!adj) {
         const C *V = F + bf->offV, *M = F + bf->offM, *U = F + bf->offU;
         {
             FIO_TIMED(f64 ? "bf2_V_f64" : "bf2_V_f32", s);
-            K2Args<T> v = a;
-            v.A = V; v.X = X; v.ldx = ldx; v.cout = c1; v.nb = 1; v.nsplit = 1;
-            launch_leaf_in<T, KC, VF>(v, g, chunks, blkq, s);
+            first(VF, V, c1, c2);
         }
         {
             FIO_TIMED(f64 ? "bf2_M_f64" : "bf2_M_f32", s);
-            K2Args<T> m = a;
-            m.A = M; m.cin = c1; m.cout = c2; m.nb = (int)g.rr; m.nsplit = 1;
-            m.nout = NP;
-            k2_step<T, KC, MF><<<grid_rows(chunks, NP), blkq, 0, s>>>(m);
+            middle(MF, M, c1, c2);
         }
         {
             FIO_TIMED(f64 ? "bf2_U_f64" : "bf2_U_f32", s);
-            K2Args<T> u = a;
-            u.A = U; u.cin = c2; u.Y = Y; u.ldy = ldy; u.part = part; u.nb = (int)g.T; u.nsplit = nsp;
-            u.nout = g.S;
-            k2_step<T, KC, UF><<<dim3(chunks, (unsigned)g.S, nsp), blkb, 0, s>>>(u);
-            if (nsp > 1) {
-                const size_t tot = (size_t)g.S * g.b2 * nrhs;
-                k2_reduce<T><<<grid1d(tot, 256), 256, 0, s>>>(g, part, nsp, g.S, ldc, nrhs, 0, 0, Y, ldy);
-            }
+            last(UF, U, c2);
         }
     } else {
         const C *Va = Fa + bf->offV, *Ma = Fa + bf->offM, *Ua = Fa + bf->offU;
         {
             FIO_TIMED(f64 ? "bf2_U_f64" : "bf2_U_f32", s);
-            K2Args<T> u = a;
-            u.A = Ua; u.X = X; u.ldx = ldx; u.cout = c2; u.nb = 1; u.nsplit = 1;
-            launch_leaf_in<T, KC, UA>(u, g, chunks, blkq, s);
+            first(UA, Ua, c2, c1);
         }
         {
             FIO_TIMED(f64 ? "bf2_M_f64" : "bf2_M_f32", s);
-            K2Args<T> m = a;
-            m.A = Ma; m.cin = c2; m.cout = c1; m.nb = (int)g.rr; m.nsplit = 1;
-            m.nout = NP;
-            k2_step<T, KC, MA><<<grid_rows(chunks, NP), blkq, 0, s>>>(m);
+            middle(MA, Ma, c2, c1);
         }
         {
             FIO_TIMED(f64 ? "bf2_V_f64" : "bf2_V_f32", s);
-            K2Args<T> v = a;
-            v.A = Va; v.cin = c1; v.Y = Y; v.ldy = ldy; v.part = part; v.nb = (int)g.T; v.nsplit = nsp;
-            v.nout = g.S;
-            k2_step<T, KC, VA><<<dim3(chunks, (unsigned)g.S, nsp), blkb, 0, s>>>(v);
-            if (nsp > 1) {
-                const size_t tot = (size_t)g.S * g.b2 * nrhs;
-                k2_reduce<T><<<grid1d(tot, 256), 256, 0, s>>>(g, part, nsp, g.S, ldc, nrhs, 1, a.fint, Y, ldy);
-            }
+            last(VA, Va, c1);
         }
     }
     FIO_HIP(hipGetLastError());
@@ -558,13 +649,13 @@ void apply2k(fio_bf_s *bf, bool adj, const double2 *X, long ldx, double2 *Y, lon
 template <typename T>
 void apply2(fio_bf_s *bf, bool adj, const double2 *X, long ldx, double2 *Y, long ldy, int nrhs, const cpx<T> *F,
             const cpx<T> *Fa, void *ws, bool fint, hipStream_t s) {
-    // column chunk and reduction split: tuned (fio_bf_autotune) or 16 columns for wide blocks
+    // columns per wave and reduction split: tuned (fio_bf_autotune) or 8 columns, which pads least (n = 64, 70
+    // columns: 1031 us against 1207 us with 16)
     const TileCfg c = bf_tile(bf, adj, sizeof(T) == 8 ? FIO_PREC_FP64 : FIO_PREC_FP32, nrhs);
-    const int kc = c.kc ? c.kc : (nrhs >= 16 ? 16 : 8);
-    if (kc == 16)
-        apply2k<T, 16>(bf, adj, X, ldx, Y, ldy, nrhs, F, Fa, ws, fint, c.nsplit, s);
+    if (c.kc == 16)
+        apply2k<T, 2>(bf, adj, X, ldx, Y, ldy, nrhs, F, Fa, ws, fint, c.nsplit, s);
     else
-        apply2k<T, 8>(bf, adj, X, ldx, Y, ldy, nrhs, F, Fa, ws, fint, c.nsplit, s);
+        apply2k<T, 1>(bf, adj, X, ldx, Y, ldy, nrhs, F, Fa, ws, fint, c.nsplit, s);
 }
 
 }  // namespace
