@@ -95,10 +95,20 @@ size_t bf_coef_elems(const fio_bf_s *bf, int nrhs) { return (size_t)bf->N * bf->
 // the entry is rounded once.  Lagrange values are taken in the reference coordinate u of the
 // point in its interpolation box, where p_t(u) is the same for every box.
 
+// They are tabulated once per operator: out[c][i][t] = P_c(i, t) = p_t((c - 1/2) + t_i / 2), then
+// [s][t] = p_t of point s of a leaf box of b points.
+__global__ void gen_lagrange(Nodes tn, int b, double *out) {
+    const int q = tn.q, id = blockIdx.x * blockDim.x + threadIdx.x, t = id % q, r = id / q;
+    if (r >= 2 * q + b) return;
+    const double hw = 0.5 * b;
+    const dd u = r < 2 * q ? dd_add(dd_of(r / q - 0.5), dd_ldexp(tn.t(r % q), 0.5)) : dd_of((r - 2 * q - hw) / hw);
+    out[id] = dd_lagrange(u, t, tn);
+}
+
 __device__ __forceinline__ double2 scaled(double2 e, double v) { return zc(e.x * v, e.y * v); }
 
 // V[sigma][tau][j][s] = exp(2 pi i (y + sgn c(y)) (xi_s - gamma_j)) q_j(xi_s)   (|xi| = sgn xi on the box)
-__global__ void gen_V(Geo g, Nodes tn, double2 *out) {
+__global__ void gen_V(Geo g, Nodes tn, const double *lag, double2 *out) {
     size_t n = (size_t)(1L << g.Lp) * g.nsl * g.q * g.b;
     size_t id = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
     if (id >= n) return;
@@ -114,31 +124,39 @@ __global__ void gen_V(Geo g, Nodes tn, double2 *out) {
     const double y = (tau + 0.5) / g.nsl;
     const dd kap = dd_add(dd_of(y), dd_mul_d(c_dd(g, dd_of(y)), sgn));
     const dd dxi = dd_sub(dd_of(s - hw), dd_ldexp(tn.t(j), hw));  // xi_s - gamma_j
-    const double qv = dd_lagrange(dd_of((s - hw) / hw), j, tn);
-    out[id] = scaled(dd_expi2pi(dd_frac(dd_mul(kap, dxi))), qv);
+    out[id] = scaled(dd_expi2pi(dd_frac(dd_mul(kap, dxi))), lag[s * g.q + j]);
 }
 
+// The transfer factors take 8 groups of one alpha (consecutive sigma; an alpha has at least 8, since
+// L - L' = 3) per workgroup: what depends on the spatial points alone is formed once in LDS, and an entry
+// costs one phase product and one exponential.  N = 2^16, 10.6 M entries a level: B 2.10 -> 0.22 ms, C
+// 1.47 -> 0.21 ms, of which the series of ddmath.h and the tabulated Lagrange values gave 0.66 and
+// 0.44 ms; the double-double exponential bounds both.
+constexpr int kGenGroups = 8;
+
 // C^[l+1]: group (alpha at spatial level L-l-1, sigma at frequency level l)
-__global__ void gen_C(Geo g, Nodes tn, int l, double2 *out) {
+__global__ void __launch_bounds__(256) gen_C(Geo g, Nodes tn, const double *P, int l, double2 *out) {
+    __shared__ dd kap[2][2];                 // [c_out][frequency half]
     const int q = g.q, q2 = 2 * q;
-    size_t n = (size_t)(g.N / 2) * q2 * q2;
-    size_t id = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
-    if (id >= n) return;
-    int col = id % q2, row = (id / q2) % q2;
-    long grp = id / ((size_t)q2 * q2);
-    long G = 1L << l;
-    long alpha = grp / G, sigma = grp % G;
-    int cout = row / q, j = row % q, cin = col / q, t = col % q;
-    long tau = 2 * alpha + cout;
-    const double y = (tau + 0.5) / (double)(1L << (g.L - l));
-    const double ws = (double)g.N / (double)(1L << l), wb = 0.5 * ws;
-    const double eta_s = -0.5 * g.N + (sigma + 0.5) * ws;
-    const double sgn = eta_s > 0 ? 1.0 : -1.0;
-    const dd kap = dd_add(dd_of(y), dd_mul_d(c_dd(g, dd_of(y)), sgn));
-    // gamma_beta,t - gamma_sigma,j
-    const dd dgam = dd_add(dd_of((cin - 0.5) * wb), dd_sub(dd_ldexp(tn.t(t), 0.5 * wb), dd_ldexp(tn.t(j), 0.5 * ws)));
-    const dd u = dd_add(dd_of(cin - 0.5), dd_ldexp(tn.t(t), 0.5));
-    out[id] = scaled(dd_expi2pi(dd_frac(dd_mul(kap, dgam))), dd_lagrange(u, j, tn));
+    const long G = 1L << l, grp0 = (long)blockIdx.x * kGenGroups, alpha = grp0 / G, sigma0 = grp0 % G;
+    const double ws = (double)g.N / (double)G, wb = 0.5 * ws;
+    if (threadIdx.x < 4) {
+        const double y = (2 * alpha + (threadIdx.x >> 1) + 0.5) / (double)(1L << (g.L - l));
+        kap[threadIdx.x >> 1][threadIdx.x & 1] =
+            dd_add(dd_of(y), dd_mul_d(c_dd(g, dd_of(y)), threadIdx.x & 1 ? 1.0 : -1.0));
+    }
+    __syncthreads();
+    double2 *o = out + (size_t)grp0 * q2 * q2;
+    for (int id = threadIdx.x; id < kGenGroups * q2 * q2; id += 256) {
+        const int col = id % q2, r = id / q2, row = r % q2;
+        const long sigma = sigma0 + r / q2;
+        const int cout = row / q, j = row % q, cin = col / q, t = col % q;
+        const double eta_s = -0.5 * g.N + (sigma + 0.5) * ws;
+        // gamma_beta,t - gamma_sigma,j
+        const dd dgam =
+            dd_add(dd_of((cin - 0.5) * wb), dd_sub(dd_ldexp(tn.t(t), 0.5 * wb), dd_ldexp(tn.t(j), 0.5 * ws)));
+        o[id] = scaled(dd_expi2pi(dd_frac(dd_mul(kap[cout][eta_s > 0], dgam))), P[(cin * q + t) * q + j]);
+    }
 }
 
 // M[p][i][j] = k(z_tau,i, gamma_sigma,j), p = tau 2^h + sigma
@@ -165,31 +183,34 @@ __global__ void gen_M(Geo g, Nodes tn, Amp am, double2 *out) {
 
 // B^[l+1]: group (alpha at spatial level l, sigma at frequency level L-l-1)
 //   exp(2 pi i ((z_tau,i - z_alpha,t) eta + (c(z_tau,i) - c(z_alpha,t)) |eta|)) p_t(u_i)
-__global__ void gen_B(Geo g, Nodes tn, int l, double2 *out) {
+__global__ void __launch_bounds__(256) gen_B(Geo g, Nodes tn, const double *P, int l, double2 *out) {
+    __shared__ dd dz[3 * kMaxQ], cz[3 * kMaxQ];     // points minus y_alpha and their c: z_tau,i, then z_alpha,t
     const int q = g.q, q2 = 2 * q;
-    size_t n = (size_t)(g.N / 2) * q2 * q2;
-    size_t id = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
-    if (id >= n) return;
-    int col = id % q2, row = (id / q2) % q2;
-    long grp = id / ((size_t)q2 * q2);
-    long G = 1L << (g.L - l - 1);
-    long alpha = grp / G, sigma = grp % G;
-    int cout = row / q, i = row % q, cin = col / q, t = col % q;
+    const long G = 1L << (g.L - l - 1), grp0 = (long)blockIdx.x * kGenGroups, alpha = grp0 / G, sigma0 = grp0 % G;
     const double wa = 1.0 / (double)(1L << l), wt = 0.5 * wa;
     const double ya = (alpha + 0.5) * wa;
-    const dd d1 = dd_add(dd_of((cout - 0.5) * wt), dd_ldexp(tn.t(i), 0.5 * wt));   // z_tau,i - y_alpha
-    const dd d2 = dd_ldexp(tn.t(t), 0.5 * wa);                                       // z_alpha,t - y_alpha
-    const long beta = 2 * sigma + cin;
+    if (threadIdx.x < 3 * q) {
+        const int k = threadIdx.x / q, i = threadIdx.x % q;
+        const dd d = k < 2 ? dd_add(dd_of((k - 0.5) * wt), dd_ldexp(tn.t(i), 0.5 * wt)) : dd_ldexp(tn.t(i), 0.5 * wa);
+        dz[threadIdx.x] = d;
+        cz[threadIdx.x] = c_dd(g, dd_add(dd_of(ya), d));
+    }
+    __syncthreads();
     const double wf = (double)g.N / (double)(1L << (g.L - l));
-    const double eta = -0.5 * g.N + (beta + 0.5) * wf;
-    const dd dc = dd_sub(c_dd(g, dd_add(dd_of(ya), d1)), c_dd(g, dd_add(dd_of(ya), d2)));
-    const dd ph = dd_add(dd_frac(dd_mul_d(dd_sub(d1, d2), eta)), dd_frac(dd_mul_d(dc, fabs(eta))));
-    const dd u = dd_add(dd_of(cout - 0.5), dd_ldexp(tn.t(i), 0.5));
-    out[id] = scaled(dd_expi2pi(ph), dd_lagrange(u, t, tn));
+    double2 *o = out + (size_t)grp0 * q2 * q2;
+    for (int id = threadIdx.x; id < kGenGroups * q2 * q2; id += 256) {
+        const int col = id % q2, r = id / q2, row = r % q2;
+        const int cin = col / q, t = col % q;       // row = c_out q + i
+        const long beta = 2 * (sigma0 + r / q2) + cin;
+        const double eta = -0.5 * g.N + (beta + 0.5) * wf;
+        const dd dc = dd_sub(cz[row], cz[q2 + t]);
+        const dd ph = dd_add(dd_frac(dd_mul_d(dd_sub(dz[row], dz[q2 + t]), eta)), dd_frac(dd_mul_d(dc, fabs(eta))));
+        o[id] = scaled(dd_expi2pi(ph), P[row * q + t]);
+    }
 }
 
 // U[tau][sigma][s][i] = exp(2 pi i ((x_s - z_tau,i) eta + (c(x_s) - c(z_tau,i)) |eta|)) p_i(x_s)
-__global__ void gen_U(Geo g, Nodes tn, double2 *out) {
+__global__ void gen_U(Geo g, Nodes tn, const double *lag, double2 *out) {
     const int q = g.q;
     size_t n = (size_t)(1L << g.Lp) * g.nsl * g.b * q;
     size_t id = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
@@ -208,7 +229,7 @@ __global__ void gen_U(Geo g, Nodes tn, double2 *out) {
     const double eta = -0.5 * g.N + (sigma + 0.5) * ((double)g.N / g.nsl);
     const dd dc = dd_sub(c_dd(g, dd_of(x)), c_dd(g, dd_add(dd_of(y), dzt)));
     const dd ph = dd_add(dd_frac(dd_mul_d(dx, eta)), dd_frac(dd_mul_d(dc, fabs(eta))));
-    out[id] = scaled(dd_expi2pi(ph), dd_lagrange(dd_of((s - hb) / hb), i, tn));
+    out[id] = scaled(dd_expi2pi(ph), lag[s * q + i]);
 }
 
 // Structured transfer factors: every 2q x 2q transfer block is, per (c_out, c_in) quadrant,
@@ -265,15 +286,6 @@ __global__ void gen_TW_C(Geo g, Nodes tn, int l, double2 *out) {
     out[id] = dd_expi2pi(dd_frac(dd_mul(kap, d)));
 }
 
-__global__ void gen_Pchild(Nodes tn, double *out) {
-    // out[c][i][t] = P_c(i, t) = p_t((c - 1/2) + t_i / 2)
-    const int q = tn.q;
-    const int id = blockIdx.x * blockDim.x + threadIdx.x;
-    if (id >= 2 * q * q) return;
-    const int t = id % q, i = (id / q) % q, c = id / (q * q);
-    out[id] = dd_lagrange(dd_add(dd_of(c - 0.5), dd_ldexp(tn.t(i), 0.5)), t, tn);
-}
-
 __global__ void cvt_f64_f32(const double2 *in, float2 *out, size_t n) {
     size_t id = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
     if (id < n) {
@@ -288,16 +300,21 @@ static void bf_generate(fio_bf_s *bf, hipStream_t s) {
     const Nodes tn = make_nodes(bf->q);
     double2 *base = bf->f64.as<double2>();
     const unsigned T = 256;
+    const int nlag = (2 * bf->q + bf->b) * bf->q;
+    DevBuf lagb(nlag * sizeof(double));
+    const double *P = lagb.as<double>(), *lag = P + 2 * bf->q * bf->q;
+    gen_lagrange<<<grid1d(nlag, 64), 64, 0, s>>>(tn, bf->b, lagb.as<double>());
     size_t nV = (size_t)(1L << bf->Lp) * bf->nsl * bf->q * bf->b;
-    gen_V<<<grid1d(nV, T), T, 0, s>>>(g, tn, base + bf->offV);
-    size_t nT = (size_t)(bf->N / 2) * 4 * bf->q * bf->q;
+    gen_V<<<grid1d(nV, T), T, 0, s>>>(g, tn, lag, base + bf->offV);
     for (int lev = 0; lev < bf->nl; ++lev) {
-        gen_C<<<grid1d(nT, T), T, 0, s>>>(g, tn, bf->h + lev, base + bf->offC[lev]);
-        gen_B<<<grid1d(nT, T), T, 0, s>>>(g, tn, bf->h + lev, base + bf->offB[lev]);
+        const int l = bf->h + lev;
+        const unsigned wgs = (unsigned)(bf->N / 2 / kGenGroups);
+        gen_C<<<wgs, T, 0, s>>>(g, tn, P, l, base + bf->offC[lev]);
+        gen_B<<<wgs, T, 0, s>>>(g, tn, P, l, base + bf->offB[lev]);
     }
     size_t nM = (size_t)bf->N * bf->q * bf->q;
     gen_M<<<grid1d(nM, T), T, 0, s>>>(g, tn, bf->amp, base + bf->offM);
-    gen_U<<<grid1d(nV, T), T, 0, s>>>(g, tn, base + bf->offU);
+    gen_U<<<grid1d(nV, T), T, 0, s>>>(g, tn, lag, base + bf->offU);
     FIO_HIP(hipGetLastError());
     // structured transfer twiddles and the shared Lagrange matrices
     if (bf->nl > 0) {
@@ -312,13 +329,11 @@ static void bf_generate(fio_bf_s *bf, hipStream_t s) {
                 gen_TW_C<<<grid1d(ntw, T), T, 0, s>>>(g, tn, bf->h + lev, tw + bf_tw_off(bf, true, lev));
             }
         }
-        DevBuf pd(2 * bf->q * bf->q * sizeof(double));
-        gen_Pchild<<<1, 2 * bf->q * bf->q, 0, s>>>(tn, pd.as<double>());
         FIO_HIP(hipGetLastError());
-        FIO_HIP(hipMemcpyAsync(bf->Pchild, pd.p, 2 * bf->q * bf->q * sizeof(double), hipMemcpyDeviceToHost, s));
-        FIO_HIP(hipStreamSynchronize(s));
+        FIO_HIP(hipMemcpyAsync(bf->Pchild, P, 2 * bf->q * bf->q * sizeof(double), hipMemcpyDeviceToHost, s));
         bf->structured = true;
     }
+    FIO_HIP(hipStreamSynchronize(s));        // the tables are released here
 }
 
 void bf_make_lowprec(fio_bf_s *bf, hipStream_t s);   // bf_lowprec.hip

@@ -97,7 +97,15 @@ __device__ __forceinline__ long lex_of(long m, int L, int n) {
 // Phases are formed in double-double arithmetic from exact points (ddmath.h; box corners and
 // grid points are binary fractions or integers, Chebyshev points are center + (w/2) t_i) and
 // reduced modulo 1 before the single rounding of an entry; Lagrange values are taken in the
-// reference coordinate of the point in its box.
+// reference coordinate of the point in its box, which is the same for every box: lag[s][i] = q_i(point s
+// of the b on a side).
+__global__ void gen2_lagrange(Nodes tn, int b, double *lag) {
+    const int id = blockIdx.x * blockDim.x + threadIdx.x;
+    if (id >= b * tn.q) return;
+    const double hw = 0.5 * b;
+    lag[id] = dd_lagrange(dd_of((id / tn.q - hw) / hw), id % tn.q, tn);
+}
+
 __device__ dd rho2_dd(const G2 &g, dd x1, dd x2, dd k1, dd k2) {
     dd s1, co1, s2, co2;
     dd_sincospi(dd_ldexp(x1, 2.0), s1, co1);
@@ -129,7 +137,7 @@ __device__ __forceinline__ void f_box(const G2 &g, int l, long box, double &lo1,
 // --- factor generation ------------------------------------------------------------
 // V(i, s) of pair p = tau' * S + sigma:
 //   exp(2 pi i (y.(xi_s - gamma_i) + rho(y, xi_s) - rho(y, gamma_i))) q_i(xi_s)
-__global__ void gen2_V(G2 g, Nodes tn, double2 *out) {
+__global__ void gen2_V(G2 g, Nodes tn, const double *lag, double2 *out) {
     const size_t nV = (size_t)g.T * g.S * g.q2 * g.b2;
     const size_t id = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
     if (id >= nV) return;
@@ -150,9 +158,9 @@ __global__ void gen2_V(G2 g, Nodes tn, double2 *out) {
     const dd g1 = dd_add(dd_of(c1), dd_ldexp(tn.t(i1), hw)), g2 = dd_add(dd_of(c2), dd_ldexp(tn.t(i2), hw));
     const dd lin = dd_add(dd_frac(dd_mul_d(dd_sub(dd_of(k1), g1), y1)), dd_frac(dd_mul_d(dd_sub(dd_of(k2), g2), y2)));
     const dd nl = dd_sub(rho2_dd(g, dd_of(y1), dd_of(y2), dd_of(k1), dd_of(k2)), rho2_dd(g, dd_of(y1), dd_of(y2), g1, g2));
-    const double lag = dd_lagrange(dd_of((k1 - c1) / hw), i1, tn) * dd_lagrange(dd_of((k2 - c2) / hw), i2, tn);
+    const double w = lag[a1 * g.q + i1] * lag[a2 * g.q + i2];
     const double2 e = dd_expi2pi(dd_add(lin, dd_frac(nl)));
-    out[id] = zc(e.x * lag, e.y * lag);
+    out[id] = zc(e.x * w, e.y * w);
 }
 
 // M(i, j) of block u * S + sigma: k(z_u,i, gamma_sigma,j)
@@ -192,7 +200,7 @@ __global__ void gen2_M(G2 g, Nodes tn, double2 *out) {
 
 // U(s, i) of pair p = tau * T + sigma':
 //   exp(2 pi i ((x_s - z_i).eta + rho(x_s, eta) - rho(z_i, eta))) p_i(x_s)
-__global__ void gen2_U(G2 g, Nodes tn, double2 *out) {
+__global__ void gen2_U(G2 g, Nodes tn, const double *lag, double2 *out) {
     const size_t nU = (size_t)g.S * g.T * g.q2 * g.b2;
     const size_t id = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
     if (id >= nU) return;
@@ -213,9 +221,9 @@ __global__ void gen2_U(G2 g, Nodes tn, double2 *out) {
     const dd z1 = dd_add(dd_of(c1), dd_ldexp(tn.t(i1), hs)), z2 = dd_add(dd_of(c2), dd_ldexp(tn.t(i2), hs));
     const dd lin = dd_add(dd_frac(dd_mul_d(dd_sub(dd_of(x1), z1), e1)), dd_frac(dd_mul_d(dd_sub(dd_of(x2), z2), e2)));
     const dd nl = dd_sub(rho2_dd(g, dd_of(x1), dd_of(x2), dd_of(e1), dd_of(e2)), rho2_dd(g, z1, z2, dd_of(e1), dd_of(e2)));
-    const double lag = dd_lagrange(dd_of((x1 - c1) / hs), i1, tn) * dd_lagrange(dd_of((x2 - c2) / hs), i2, tn);
+    const double w = lag[a1 * g.q + i1] * lag[a2 * g.q + i2];
     const double2 e = dd_expi2pi(dd_add(lin, dd_frac(nl)));
-    out[id] = zc(e.x * lag, e.y * lag);
+    out[id] = zc(e.x * w, e.y * w);
 }
 
 // conjugate-transposed copies of the three factors (layout in the file header)
@@ -712,10 +720,14 @@ void bf2d_generate(fio_bf_s *bf, hipStream_t s) {
     double2 *base = bf->f64.as<double2>();
     const size_t nV = bf->offM - bf->offV, nM = bf->offU - bf->offM, nU = bf->total - bf->offU;
     const Nodes tn = make_nodes(bf->q);
-    gen2_V<<<grid1d(nV, 256), 256, 0, s>>>(g, tn, base + bf->offV);
+    DevBuf lagb(bf->b * bf->q * sizeof(double));
+    const double *lag = lagb.as<double>();
+    gen2_lagrange<<<grid1d(bf->b * bf->q, 64), 64, 0, s>>>(tn, bf->b, lagb.as<double>());
+    gen2_V<<<grid1d(nV, 256), 256, 0, s>>>(g, tn, lag, base + bf->offV);
     gen2_M<<<grid1d(nM, 256), 256, 0, s>>>(g, tn, base + bf->offM);
-    gen2_U<<<grid1d(nU, 256), 256, 0, s>>>(g, tn, base + bf->offU);
+    gen2_U<<<grid1d(nU, 256), 256, 0, s>>>(g, tn, lag, base + bf->offU);
     FIO_HIP(hipGetLastError());
+    FIO_HIP(hipStreamSynchronize(s));        // the table is released here
 }
 
 // adjoint copies and the single-precision copies of both

@@ -8,9 +8,8 @@
 //
 // Methods: Knuth's error-free sum, the FMA form of the error-free product, one correction
 // step for quotients and square roots (Dekker 1971), and sin/cos(pi x) by reduction to
-// |x| <= 1/4 followed by their Taylor series summed term by term, each term obtained from the
-// previous one by a multiplication and an exact-integer division.  All functions are
-// __host__ __device__: the host fills small node tables with the same code.
+// |x| <= 1/4 followed by their Taylor series.  All functions are __host__ __device__: the host
+// fills small node tables with the same code.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -94,22 +93,47 @@ FIO_DD_FN dd dd_frac(dd a) {
 constexpr double kPiHi = 3.141592653589793116e+00;
 constexpr double kPiLo = 1.224646799147353207e-16;
 
-// sin(pi x) and cos(pi x) for a double-double x
-FIO_DD_FN void dd_sincospi(dd x, dd &s, dd &c) {
+// sin(pi x) and cos(pi x) for a double-double x: Horner's scheme on the Taylor coefficients (-1)^k /
+// (2k + 1)! and (-1)^k / (2k)!, k = 14 .. 1, of which the first K are carried in double-double and the
+// tail, which adds at most (pi/4)^(2K+2) / (2K+2)! to 1, in double: its rounding reaches 2^-112 of the
+// result for K = 8 and 2^-86 for K = 5.
+template <int K> FIO_DD_FN void dd_sincospi_k(dd x, dd &s, dd &c) {
 #pragma clang fp contract(off)
+    constexpr double sh[14] = {-0x1.5555555555555p-3, 0x1.1111111111111p-7, -0x1.a01a01a01a01ap-13,
+                               0x1.71de3a556c734p-19, -0x1.ae64567f544e4p-26, 0x1.6124613a86d09p-33,
+                               -0x1.ae7f3e733b81fp-41, 0x1.952c77030ad4ap-49, -0x1.2f49b46814157p-57,
+                               0x1.71b8ef6dcf572p-66, -0x1.761b41316381ap-75, 0x1.3f3ccdd165fa9p-84,
+                               -0x1.d1ab1c2dccea3p-94, 0x1.259f98b4358adp-103};
+    constexpr double ch[14] = {-0x1.0p-1, 0x1.5555555555555p-5, -0x1.6c16c16c16c17p-10,
+                               0x1.a01a01a01a01ap-16, -0x1.27e4fb7789f5cp-22, 0x1.1eed8eff8d898p-29,
+                               -0x1.93974a8c07c9dp-37, 0x1.ae7f3e733b81fp-45, -0x1.6827863b97d97p-53,
+                               0x1.e542ba4020225p-62, -0x1.0ce396db7f853p-70, 0x1.f2cf01972f578p-80,
+                               -0x1.88e85fc6a4e5ap-89, 0x1.0a18a2635085dp-98};
+    // what the first 8 coefficients leave of their exact values
+    constexpr double sl[8] = {-0x1.5555555555555p-57, 0x1.1111111111111p-63, -0x1.a01a01a01a01ap-73,
+                              -0x1.c154f8ddc6c00p-73, 0x1.c062e06d1f209p-80, 0x1.f28e0cc748ebep-87,
+                              -0x1.1d8656b0ee8cbp-97, 0x1.ac981465ddc6cp-103};
+    constexpr double cl[8] = {0.0, 0x1.5555555555555p-59, 0x1.f49f49f49f49fp-65, 0x1.a01a01a01a01ap-76,
+                              -0x1.cbbc05b4fa99ap-76, -0x1.2aec959e14c06p-83, -0x1.05d6f8a2efd1fp-92,
+                              0x1.1d8656b0ee8cbp-101};
     const double m = rint(2.0 * x.hi);                 // x = m/2 + r, |r| <= 1/4 (+ rounding)
     const dd r = dd_two_sum(x.hi - 0.5 * m, x.lo);     // x.hi - m/2 is exact
     const dd th = dd_mul(dd{kPiHi, kPiLo}, r);
     const dd t2 = dd_mul(th, th);
-    // sin th = sum_k (-1)^k th^(2k+1) / (2k+1)!,  cos th = sum_k (-1)^k th^(2k) / (2k)!;
-    // |th| <= pi/4 + tiny, so 14 terms each reach 2^-106 relative
-    dd ts = th, ss = th, tc = dd_of(1.0), sc = dd_of(1.0);
-    for (int k = 1; k <= 14; ++k) {
-        ts = dd_div_d(dd_neg(dd_mul(ts, t2)), (double)((2 * k) * (2 * k + 1)));
-        tc = dd_div_d(dd_neg(dd_mul(tc, t2)), (double)((2 * k - 1) * (2 * k)));
-        ss = dd_add(ss, ts);
-        sc = dd_add(sc, tc);
+    double ts = sh[13], tc = ch[13];
+#pragma unroll
+    for (int k = 12; k >= K; --k) {
+        ts = fma(ts, t2.hi, sh[k]);
+        tc = fma(tc, t2.hi, ch[k]);
     }
+    dd ps = dd_of(ts), pc = dd_of(tc);
+#pragma unroll
+    for (int k = K - 1; k >= 0; --k) {
+        ps = dd_add(dd{sh[k], sl[k]}, dd_mul(t2, ps));
+        pc = dd_add(dd{ch[k], cl[k]}, dd_mul(t2, pc));
+    }
+    const dd ss = dd_add(th, dd_mul(th, dd_mul(t2, ps)));
+    const dd sc = dd_add(dd_of(1.0), dd_mul(t2, pc));
     long long qd = (long long)m % 4;
     if (qd < 0) qd += 4;
     switch (qd) {                                       // sin/cos of th + qd pi/2
@@ -119,6 +143,8 @@ FIO_DD_FN void dd_sincospi(dd x, dd &s, dd &c) {
         default: s = dd_neg(sc); c = ss; break;
     }
 }
+
+FIO_DD_FN void dd_sincospi(dd x, dd &s, dd &c) { dd_sincospi_k<8>(x, s, c); }
 
 FIO_DD_FN dd dd_sinpi(dd x) {
     dd s, c;
@@ -135,7 +161,7 @@ FIO_DD_FN dd dd_cospi(dd x) {
 // exp(2 pi i f) for a double-double f, rounded once per component
 FIO_DD_FN double2 dd_expi2pi(dd f) {
     dd s, c;
-    dd_sincospi(dd_ldexp(dd_frac(f), 2.0), s, c);
+    dd_sincospi_k<5>(dd_ldexp(dd_frac(f), 2.0), s, c);
     double2 e;
     e.x = dd_val(c);
     e.y = dd_val(s);
