@@ -477,6 +477,7 @@ static fio_status bf_new(const fio_bf_desc *desc, fio_bf_t *out, fio_bf_s **bfp)
 }
 
 extern "C" fio_status fio_bf_build(const fio_bf_desc *desc, void *stream, fio_bf_t *out) {
+    PoolScope scope;
     fio_bf_s *bf = nullptr;
     fio_status st = bf_new(desc, out, &bf);
     if (st != FIO_OK) return st;
@@ -499,6 +500,7 @@ extern "C" fio_status fio_bf_build(const fio_bf_desc *desc, void *stream, fio_bf
 extern "C" fio_status fio_bf_import(const fio_bf_desc *desc, const void *host_factors, size_t count, void *stream,
                                     fio_bf_t *out) {
     if (!host_factors) return FIO_ERR_ARG;
+    PoolScope scope;
     fio_bf_s *bf = nullptr;
     fio_status st = bf_new(desc, out, &bf);
     if (st != FIO_OK) return st;
@@ -761,7 +763,10 @@ extern "C" fio_status fio_bf_autotune(fio_bf_t bf, const void *X, long ldx, void
     });
 }
 
-extern "C" void fio_bf_destroy(fio_bf_t bf) { delete bf; }
+extern "C" void fio_bf_destroy(fio_bf_t bf) {
+    PoolScope scope;
+    delete bf;
+}
 
 extern "C" void fio_set_fused(int on) { set_fused_disabled(on == 0); }
 extern "C" void fio_set_leaf_fused(int on) { g_leaf_fused_off = on == 0; }

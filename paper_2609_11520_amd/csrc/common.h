@@ -5,6 +5,8 @@
 #include <cstddef>
 #include <cstdint>
 #include <cstdio>
+#include <cstring>
+#include <memory>
 #include <mutex>
 #include <utility>
 #include <vector>
@@ -78,6 +80,17 @@ inline unsigned grid1d(size_t threads, unsigned block) {
     return (unsigned)((threads + block - 1) / block);
 }
 
+// Device memory for DevBuf.  Inside a PoolScope (the calls that build or destroy a handle) blocks come from, and
+// go to, a pool of the process (pool.cpp); elsewhere they are allocated and freed.
+void *dev_alloc(size_t bytes, size_t *cap, int *dev);
+void dev_free(void *p, size_t cap, int dev);
+struct PoolScope {
+    PoolScope();
+    ~PoolScope();
+    PoolScope(const PoolScope &) = delete;
+    PoolScope &operator=(const PoolScope &) = delete;
+};
+
 // RAII device buffer
 struct DevBuf {
     void *p = nullptr;
@@ -86,14 +99,13 @@ struct DevBuf {
     explicit DevBuf(size_t b) { alloc(b); }
     void alloc(size_t b) {
         release();
-        if (b) FIO_HIP(hipMalloc(&p, b));
-        bytes = b;
+        if (b) p = dev_alloc(b, &bytes, &dev);
     }
     void ensure(size_t b) {
         if (b > bytes) alloc(b);
     }
     void release() {
-        if (p) (void)hipFree(p);
+        if (p) dev_free(p, bytes, dev);
         p = nullptr;
         bytes = 0;
     }
@@ -104,7 +116,54 @@ struct DevBuf {
     void swap(DevBuf &o) {
         std::swap(p, o.p);
         std::swap(bytes, o.bytes);
+        std::swap(dev, o.dev);
     }
+
+  private:
+    int dev = 0;
+};
+
+// Device copies of the small tables (offsets, descriptor lists) that the launches of one host function read.
+// They are placed in a few blocks and sent together by flush(), and both sides live until the object
+// dies, so no launch waits for an allocation, a copy or a free of its own.
+struct Uploads {
+    explicit Uploads(hipStream_t st) : s(st) {}
+    ~Uploads() { (void)hipStreamSynchronize(s); }
+    Uploads(const Uploads &) = delete;
+    Uploads &operator=(const Uploads &) = delete;
+    template <typename T> const T *put(const std::vector<T> &v) {
+        const size_t bytes = v.size() * sizeof(T), need = (bytes + 255) & ~(size_t)255;
+        if (blocks.empty() || blocks.back()->used + need > blocks.back()->dev.bytes) {
+            flush();
+            const size_t size = need > kBlock ? need : kBlock;
+            blocks.push_back(std::make_unique<Block>(size));
+        }
+        Block &b = *blocks.back();
+        if (bytes) std::memcpy(b.host.get() + b.used, v.data(), bytes);
+        const T *d = reinterpret_cast<const T *>(b.dev.as<char>() + b.used);
+        b.used += need;
+        return d;
+    }
+    // sends what was put since the last flush
+    void flush() {
+        if (blocks.empty()) return;
+        Block &b = *blocks.back();
+        if (b.used > b.sent)
+            FIO_HIP(hipMemcpyAsync(b.dev.as<char>() + b.sent, b.host.get() + b.sent, b.used - b.sent,
+                                   hipMemcpyHostToDevice, s));
+        b.sent = b.used;
+    }
+
+  private:
+    static constexpr size_t kBlock = (size_t)1 << 20;
+    struct Block {
+        DevBuf dev;
+        std::unique_ptr<char[]> host;
+        size_t used = 0, sent = 0;
+        explicit Block(size_t size) : dev(size), host(new char[size]) {}
+    };
+    hipStream_t s;
+    std::vector<std::unique_ptr<Block>> blocks;
 };
 
 // Runs f() and maps library exceptions to status codes.
@@ -134,10 +193,10 @@ void zgemm_vbatched(const ZgemmDesc *d_descs, int count, int maxM, int maxN, boo
 // a single GEMM whose descriptor travels as a kernel argument (no device copy needed)
 void zgemm_one(const ZgemmDesc &d, bool conjA, double2 alpha, double2 beta, hipStream_t s);
 
-// Host-side helper that keeps a device copy of a descriptor list.
+// A descriptor list built on the host
 struct ZgemmBatch {
     std::vector<ZgemmDesc> h;
-    DevBuf d;
+    const ZgemmDesc *d = nullptr;
     int maxM = 0, maxN = 0;
     void add(const double2 *A, int lda, const double2 *B, int ldb, double2 *C, int ldc, int M, int N, int K) {
         if (M <= 0 || N <= 0) return;
@@ -145,14 +204,10 @@ struct ZgemmBatch {
         if (M > maxM) maxM = M;
         if (N > maxN) maxN = N;
     }
-    void upload(hipStream_t s) {
+    void put(Uploads &up) { d = up.put(h); }
+    void run(bool conjA, double2 alpha, double2 beta, hipStream_t s) const {
         if (h.empty()) return;
-        d.ensure(h.size() * sizeof(ZgemmDesc));
-        FIO_HIP(hipMemcpyAsync(d.p, h.data(), h.size() * sizeof(ZgemmDesc), hipMemcpyHostToDevice, s));
-    }
-    void run(bool conjA, double2 alpha, double2 beta, hipStream_t s) {
-        if (h.empty()) return;
-        zgemm_vbatched(d.as<ZgemmDesc>(), (int)h.size(), maxM, maxN, conjA, alpha, beta, s);
+        zgemm_vbatched(d, (int)h.size(), maxM, maxN, conjA, alpha, beta, s);
     }
 };
 

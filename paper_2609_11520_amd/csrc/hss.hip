@@ -15,6 +15,7 @@
 #include "hss.h"
 #include "hss_qr.h"
 
+#include <algorithm>
 #include <cmath>
 
 namespace fio {
@@ -677,12 +678,6 @@ static double sumsq(const double2 *x, size_t n, hipStream_t s) {
     return t;
 }
 
-template <typename T> static DevBuf *upload(const std::vector<T> &v, hipStream_t s) {
-    DevBuf *b = new DevBuf(v.size() * sizeof(T) + 8);
-    FIO_HIP(hipMemcpyAsync(b->p, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice, s));
-    return b;
-}
-
 // Levels whose largest node has at least this many rows take the level-wide path: at 64 rows (1024 leaves
 // of N = 2^16) the construction takes 25.8 ms with it and 29.9 ms with one workgroup per node, 2D n = 32
 // (nodes of 64 to 424 rows) 79 and 131 ms; below 64 rows the two measure the same.
@@ -691,14 +686,15 @@ static int g_big_node = kBigNode;
 
 static unsigned cdiv(long a, long b) { return (unsigned)(a <= 0 ? 0 : (a + b - 1) / b); }
 
-// device buffers of the level steps, kept over the levels of a construction
+// device buffers of the level steps, kept over the levels of a construction; rk: the ranks, read back with the
+// last pivot (nonroot)
 struct BigWork {
     DevBuf B, nrm, tauW, done, Rinv;
     WyWork wy;
 };
 
 static void basis_big(const NodeArgs &na, const std::vector<int> &ms, int nn, int mmax, int sl, bool root, BigWork &w,
-                      hipStream_t s) {
+                      Uploads &up, std::vector<int> &rk, hipStream_t s) {
     BigArgs b;
     b.n = na;
     b.bstride = (size_t)2 * sl * mmax;
@@ -722,7 +718,7 @@ static void basis_big(const NodeArgs &na, const std::vector<int> &ms, int nn, in
         double2 *B = b.B + b.bstride * j;
         qn[j] = WyNode{B, B, sl, sl, sl, ms[j], 2 * ms[j]};
     }
-    wy_qr(qn, w.wy, s);
+    wy_qr(qn, w.wy, up, s);
     k_big_triinv<<<dim3((unsigned)b.ntri, y), 64, 0, s>>>(b);
     for (int kb = b.ntri - 1; kb >= 0; --kb) k_big_trisolve<<<dim3(cdiv(mmax, 32), y), 256, 0, s>>>(b, kb);
     k_big_pack<false><<<dim3(cdiv(sl, 32), cdiv(mmax, 32), y), 256, 0, s>>>(b);
@@ -755,7 +751,7 @@ static void basis_big(const NodeArgs &na, const std::vector<int> &ms, int nn, in
             if (all) break;
         }
     }
-    std::vector<int> rk(nn);
+    rk.resize(nn);
     FIO_HIP(hipMemcpyAsync(rk.data(), na.rank_out, nn * sizeof(int), hipMemcpyDeviceToHost, s));
     FIO_HIP(hipStreamSynchronize(s));
     // U = H_0 ... H_{r-1} [I_r; 0]
@@ -766,10 +762,9 @@ static void basis_big(const NodeArgs &na, const std::vector<int> &ms, int nn, in
         const int m = ms[j], r = m > 0 ? rk[j] : 0;
         un[j] = WyNode{Z + (size_t)m * m, Z + (size_t)m * sl, m, m, m, r, r};
     }
-    wy_factors(un, b.tauW, b.ldt, w.wy, s);
-    wy_apply(un, w.wy, true, s);
+    wy_factors(un, b.tauW, b.ldt, w.wy, up, s);
+    wy_apply(un, w.wy, true, up, s);
     FIO_HIP(hipGetLastError());
-    FIO_HIP(hipStreamSynchronize(s));    // the node lists are released here
 }
 
 void hss_layout_level(hss_s *h, int l) {
@@ -801,8 +796,8 @@ void hss_layout_B(hss_s *h) {
 }
 
 // X_out (rows sum m_lv) = diag(U_(lv,j)) X_in (rows sum r_lv), or the projection with U^*.
-static void lift_level(hss_s *h, int lv, const double2 *in, long ldin, double2 *out, long ldout, int ncols,
-                       bool project, hipStream_t s) {
+static ZgemmBatch lift_level(hss_s *h, int lv, const double2 *in, long ldin, double2 *out, long ldout, int ncols,
+                             bool project, Uploads &up) {
     ZgemmBatch zb;
     long ro = 0, mo = 0;
     for (int j = 0; j < h->nodes(lv); ++j) {
@@ -814,9 +809,8 @@ static void lift_level(hss_s *h, int lv, const double2 *in, long ldin, double2 *
         ro += r;
         mo += m;
     }
-    zb.upload(s);
-    zb.run(project, zc(1.0), zc(0.0), s);
-    FIO_HIP(hipStreamSynchronize(s));   // the descriptor list is freed on return
+    zb.put(up);
+    return zb;
 }
 
 static long level_rows_m(const hss_s *h, int lv) {
@@ -832,37 +826,35 @@ static long level_rows_r(const hss_s *h, int lv) {
 
 // Omega_big = U^[Lh] ... U^[l+1] Omega (N x ncols); Y = U^[l+1]* ... U^[Lh]* Y_big.
 static void lift_all(hss_s *h, int l, const double2 *Om, long R, double2 *t0, double2 *t1, double2 *out, int ncols,
-                     hipStream_t s) {
-    if (l == h->Lh) {
-        FIO_HIP(hipMemcpyAsync(out, Om, (size_t)R * ncols * sizeof(double2), hipMemcpyDeviceToDevice, s));
-        return;
-    }
+                     Uploads &up, hipStream_t s) {
     const double2 *cur = Om;
     long ldc = R;
+    std::vector<ZgemmBatch> chain;
     for (int lv = l + 1; lv <= h->Lh; ++lv) {
         long rows = level_rows_m(h, lv);
         double2 *dst = (lv == h->Lh) ? out : ((lv - l) % 2 ? t0 : t1);
-        lift_level(h, lv, cur, ldc, dst, rows, ncols, false, s);
+        chain.push_back(lift_level(h, lv, cur, ldc, dst, rows, ncols, false, up));
         cur = dst;
         ldc = rows;
     }
+    up.flush();
+    for (const ZgemmBatch &zb : chain) zb.run(false, zc(1.0), zc(0.0), s);
 }
 
 static void project_all(hss_s *h, int l, const double2 *Yb, double2 *t0, double2 *t1, double2 *out, long R,
-                        int ncols, hipStream_t s) {
-    if (l == h->Lh) {
-        FIO_HIP(hipMemcpyAsync(out, Yb, (size_t)R * ncols * sizeof(double2), hipMemcpyDeviceToDevice, s));
-        return;
-    }
+                        int ncols, Uploads &up, hipStream_t s) {
     const double2 *cur = Yb;
     long ldc = h->N;
+    std::vector<ZgemmBatch> chain;
     for (int lv = h->Lh; lv >= l + 1; --lv) {
         long rows = level_rows_r(h, lv);
         double2 *dst = (lv == l + 1) ? out : ((h->Lh - lv) % 2 ? t1 : t0);
-        lift_level(h, lv, cur, ldc, dst, rows, ncols, true, s);
+        chain.push_back(lift_level(h, lv, cur, ldc, dst, rows, ncols, true, up));
         cur = dst;
         ldc = rows;
     }
+    up.flush();
+    for (const ZgemmBatch &zb : chain) zb.run(true, zc(1.0), zc(0.0), s);
 }
 
 struct Sampler {
@@ -893,8 +885,9 @@ static fio_status build_impl(long n, const hss_opts *o, const Sampler &sm, hipSt
     std::vector<std::vector<size_t>> doff(Lh + 1);
     fio_status st = guarded([&] {
         double g = o->norm_est;
-        DevBuf Om, Ob, Yb, Y, t0, t1, scratch;
+        DevBuf Om, Ob, Yb, Y, t0, t1, scratch, rk, Dcur, Dnext, tmp;
         BigWork bw;
+        Uploads up(s);
         for (int l = Lh; l >= 0; --l) {
             const bool root = (l == 0);
             if (!root) hss_layout_level(h, l);
@@ -943,15 +936,26 @@ static fio_status build_impl(long n, const hss_opts *o, const Sampler &sm, hipSt
                 h->samples[l] = sl;
                 Om.ensure((size_t)R * sl * sizeof(double2));
                 if (sm.omega(sm.octx, l, R, sl, Om.p, s) != 0) throw Err{FIO_ERR_CALLBACK};
-                const size_t big = (size_t)n * sl * sizeof(double2);
-                Ob.ensure(big);
-                Yb.ensure(big);
-                t0.ensure(big);
-                t1.ensure(big);
                 Y.ensure((size_t)R * sl * sizeof(double2));
-                lift_all(h, l, Om.as<double2>(), R, t0.as<double2>(), t1.as<double2>(), Ob.as<double2>(), sl, s);
-                if (sm.matvec(sm.mctx, Ob.p, n, Yb.p, n, sl, s) != 0) throw Err{FIO_ERR_CALLBACK};
-                project_all(h, l, Yb.as<double2>(), t0.as<double2>(), t1.as<double2>(), Y.as<double2>(), R, sl, s);
+                if (l == Lh) {
+                    // the leaf level's samples are those of H itself
+                    if (sm.matvec(sm.mctx, Om.p, n, Y.p, n, sl, s) != 0) throw Err{FIO_ERR_CALLBACK};
+                } else {
+                    const size_t big = (size_t)n * sl * sizeof(double2);
+                    Ob.ensure(big);
+                    Yb.ensure(big);
+                    long rows = 1;                       // of the vectors between this level and the leaves
+                    for (int lv = l + 1; lv <= Lh; ++lv) {
+                        if (lv < Lh) rows = std::max(rows, level_rows_m(h, lv));
+                        rows = std::max(rows, level_rows_r(h, lv));
+                    }
+                    t0.ensure((size_t)rows * sl * sizeof(double2));
+                    t1.ensure((size_t)rows * sl * sizeof(double2));
+                    lift_all(h, l, Om.as<double2>(), R, t0.as<double2>(), t1.as<double2>(), Ob.as<double2>(), sl, up, s);
+                    if (sm.matvec(sm.mctx, Ob.p, n, Yb.p, n, sl, s) != 0) throw Err{FIO_ERR_CALLBACK};
+                    project_all(h, l, Yb.as<double2>(), t0.as<double2>(), t1.as<double2>(), Y.as<double2>(), R, sl, up,
+                                s);
+                }
                 if (l == Lh && !(o->norm_est > 0.0)) {
                     double ny = sumsq(Y.as<double2>(), (size_t)R * sl, s);
                     double no = sumsq(Om.as<double2>(), (size_t)R * sl, s);
@@ -963,14 +967,13 @@ static fio_status build_impl(long n, const hss_opts *o, const Sampler &sm, hipSt
                 scratch.ensure(stride * nn * sizeof(double2));
                 std::vector<size_t> uo(nn, 0);
                 if (!root) uo = h->uoff[l];
-                DevBuf *dmo = upload(mo, s), *dms = upload(ms, s), *duo = upload(uo, s), *ddo = upload(doff[l], s);
-                DevBuf rk(nn * sizeof(int));
+                rk.ensure(nn * sizeof(int));
                 NodeArgs na;
                 na.Om = Om.as<double2>();
                 na.Y = Y.as<double2>();
                 na.ldR = R;
-                na.moff = dmo->as<long>();
-                na.msz = dms->as<int>();
+                na.moff = up.put(mo);
+                na.msz = up.put(ms);
                 na.s = sl;
                 na.tol_abs = o->tol * g;
                 na.cap = o->rank_cap;
@@ -978,21 +981,24 @@ static fio_status build_impl(long n, const hss_opts *o, const Sampler &sm, hipSt
                 na.stride = stride;
                 na.rank_out = rk.as<int>();
                 na.Uslot = root ? nullptr : h->Ubuf[l]->as<double2>();
-                na.uoff = duo->as<size_t>();
+                na.uoff = up.put(uo);
                 na.Dres = Dres[l]->as<double2>();
-                na.doff = ddo->as<size_t>();
+                na.doff = up.put(doff[l]);
+                up.flush();
                 na.root = root ? 1 : 0;
                 na.lead = lead;
-                if (!spread) {
+                if (spread) {
+                    basis_big(na, ms, nn, mmax, sl, root, bw, up, h->rank[l], s);
+                } else {
                     k_node_basis<<<nn, node_threads(mmax), 0, s>>>(na);
                     FIO_HIP(hipGetLastError());
-                } else {
-                    basis_big(na, ms, nn, mmax, sl, root, bw, s);
+                    if (!root) {
+                        h->rank[l].assign(nn, 0);
+                        FIO_HIP(hipMemcpyAsync(h->rank[l].data(), rk.p, nn * sizeof(int), hipMemcpyDeviceToHost, s));
+                        FIO_HIP(hipStreamSynchronize(s));
+                    }
                 }
                 if (!root) {
-                    h->rank[l].assign(nn, 0);
-                    FIO_HIP(hipMemcpyAsync(h->rank[l].data(), rk.p, nn * sizeof(int), hipMemcpyDeviceToHost, s));
-                    FIO_HIP(hipStreamSynchronize(s));
                     // D-breve = X + U (X U)^*, X = T - U (U^* T), for all nodes of the level
                     ZgemmBatch g1, g2, g3, g4;
                     double2 *sc = scratch.as<double2>();
@@ -1008,10 +1014,8 @@ static fio_status build_impl(long n, const hss_opts *o, const Sampler &sm, hipSt
                         g3.add(T, m, U, m, X, m, m, r, m);        // X slot = X U   (m x r)
                         g4.add(U, m, P, m, T, m, m, m, r);        // T += U (X U)^* (D-breve)
                     }
-                    g1.upload(s);
-                    g2.upload(s);
-                    g3.upload(s);
-                    g4.upload(s);
+                    for (ZgemmBatch *b : {&g1, &g2, &g3, &g4}) b->put(up);
+                    up.flush();
                     g1.run(true, zc(1.0, 0.0), zc(0.0, 0.0), s);
                     g2.run(false, zc(-1.0, 0.0), zc(1.0, 0.0), s);
                     g3.run(false, zc(1.0, 0.0), zc(0.0, 0.0), s);
@@ -1022,13 +1026,7 @@ static fio_status build_impl(long n, const hss_opts *o, const Sampler &sm, hipSt
                     g4.run(false, zc(1.0, 0.0), zc(1.0, 0.0), s);
                     k_node_finish<<<nn, node_threads(mmax), 0, s>>>(na);
                     FIO_HIP(hipGetLastError());
-                    FIO_HIP(hipStreamSynchronize(s));   // the descriptor lists are released here
                 }
-                FIO_HIP(hipStreamSynchronize(s));
-                delete dmo;
-                delete dms;
-                delete duo;
-                delete ddo;
                 h->drawn[l] += sl;
                 if (root || !o->adaptive || guess >= mmax) break;
                 int rl = 0;
@@ -1043,7 +1041,6 @@ static fio_status build_impl(long n, const hss_opts *o, const Sampler &sm, hipSt
         h->gain = g;
         // postprocessing (Section 3.3), top down
         hss_layout_B(h);
-        DevBuf Dcur, Dnext, tmp;
         // level-0 "D" is H0, stored in Dres[0]
         const double2 *dpar = Dres[0]->as<double2>();
         std::vector<size_t> dpoff = {0};
@@ -1062,34 +1059,29 @@ static fio_status build_impl(long n, const hss_opts *o, const Sampler &sm, hipSt
             if (l + 1 == Lh) {
                 dout = h->Dbuf.as<double2>();
             } else {
-                Dnext.alloc(tot * sizeof(double2) + 16);
+                Dnext.ensure(tot * sizeof(double2) + 16);
                 dout = Dnext.as<double2>();
             }
             tmp.ensure(2 * tmax * nc * sizeof(double2) + 16);
             std::vector<size_t> bo = h->boff[l];
-            DevBuf *d1 = upload(dpoff, s), *d2 = upload(mpar, s), *d3 = upload(h->rank[l + 1], s),
-                   *d4 = upload(doff[l + 1], s), *d5 = upload(h->m[l + 1], s), *d6 = upload(h->uoff[l + 1], s),
-                   *d7 = upload(dooff, s), *d8 = upload(bo, s);
             PostArgs pa;
             pa.Dpar = dpar;
-            pa.dpoff = d1->as<size_t>();
-            pa.mpar = d2->as<int>();
-            pa.rch = d3->as<int>();
+            pa.dpoff = up.put(dpoff);
+            pa.mpar = up.put(mpar);
+            pa.rch = up.put(h->rank[l + 1]);
             pa.Dres = Dres[l + 1]->as<double2>();
-            pa.droff = d4->as<size_t>();
-            pa.mch = d5->as<int>();
+            pa.droff = up.put(doff[l + 1]);
+            pa.mch = up.put(h->m[l + 1]);
             pa.Uslot = h->Ubuf[l + 1]->as<double2>();
-            pa.uoff = d6->as<size_t>();
+            pa.uoff = up.put(h->uoff[l + 1]);
             pa.Dout = dout;
-            pa.dooff = d7->as<size_t>();
+            pa.dooff = up.put(dooff);
             pa.Bout = h->Bbuf.as<double2>();
-            pa.boff = d8->as<size_t>();
+            pa.boff = up.put(bo);
             pa.tmp = tmp.as<double2>();
             pa.tstride = 2 * tmax;
             int mcmax = 0;
             for (int c = 0; c < nc; ++c) mcmax = h->m[l + 1][c] > mcmax ? h->m[l + 1][c] : mcmax;
-            k_post_prep<<<nc, node_threads(mcmax), 0, s>>>(pa);
-            FIO_HIP(hipGetLastError());
             ZgemmBatch g1, g2;
             for (int c = 0; c < nc; ++c) {
                 const int par = c >> 1, mc = h->m[l + 1][c], r = h->rank[l + 1][c], mp = mpar[par];
@@ -1100,17 +1092,19 @@ static fio_status build_impl(long n, const hss_opts *o, const Sampler &sm, hipSt
                 g1.add(Uc, mc, dpar + dpoff[par] + o + (size_t)o * mp, mp, T, mc, mc, r, r);   // T = U_c A
                 g2.add(T, mc, UcH, r, dout + dooff[c], mc, mc, mc, r);                         // D_c += T U_c^*
             }
-            g1.upload(s);
-            g2.upload(s);
+            g1.put(up);
+            g2.put(up);
+            up.flush();
+            k_post_prep<<<nc, node_threads(mcmax), 0, s>>>(pa);
+            FIO_HIP(hipGetLastError());
             g1.run(false, zc(1.0, 0.0), zc(0.0, 0.0), s);
             g2.run(false, zc(1.0, 0.0), zc(1.0, 0.0), s);
-            FIO_HIP(hipStreamSynchronize(s));
-            for (DevBuf *d : {d1, d2, d3, d4, d5, d6, d7, d8}) delete d;
             Dcur.swap(Dnext);
             dpar = Dcur.as<double2>();
             dpoff = dooff;
             mpar = h->m[l + 1];
         }
+        FIO_HIP(hipStreamSynchronize(s));
         return h->rank_capped ? FIO_WARN_RANK_CAP : FIO_OK;
     });
     for (auto *d : Dres) delete d;
@@ -1128,6 +1122,7 @@ using namespace fio;
 
 extern "C" fio_status hss_build_from_samples(long n, const hss_opts *opts, hss_matvec_fn matvec, void *matvec_ctx,
                                              hss_omega_fn omega, void *omega_ctx, void *stream, hss_t *out) {
+    PoolScope scope;
     Sampler sm{matvec, matvec_ctx, omega, omega_ctx};
     return build_impl(n, opts, sm, as_stream(stream), out);
 }
@@ -1145,11 +1140,10 @@ int bf_gram_matvec(void *ctx, const void *X, long ldx, void *Y, long ldy, int nc
     BfGram *g = static_cast<BfGram *>(ctx);
     fio_status st = guarded([&] {
         hipStream_t s = as_stream(stream);
-        // 2D: the HSS tree runs over the Morton order of the frequencies, and the sample
-        // blocks are applied in chunks of 64 columns (the 2D coefficient buffers hold
-        // 81 N entries per column)
+        // 2D: the HSS tree runs over the Morton order of the frequencies.  The sample blocks are applied in
+        // even chunks of at most 64 columns (the coefficient buffers hold 9 N entries per column, in 2D 81 N)
         const bool fint = g->bf->dim == 2;
-        const int chunk = fint ? 64 : ncols;
+        const int chunk = fint ? 64 : (ncols + (ncols + 63) / 64 - 1) / ((ncols + 63) / 64);
         const int c1 = ncols < chunk ? ncols : chunk;
         g->ws.ensure(bf_ws_bytes(g->bf, c1, g->prec));
         g->tmp.ensure((size_t)g->bf->N * c1 * sizeof(double2));
@@ -1170,6 +1164,7 @@ extern "C" fio_status fio_hss_build(fio_bf_t bf, const hss_opts *opts, hss_omega
                                     void *stream, hss_t *out) {
     FIO_CHECK_ARG(bf && opts);
     FIO_CHECK_ARG(opts->sample_prec == FIO_PREC_FP64 || (opts->sample_prec == FIO_PREC_FP32 && bf->f32.p));
+    PoolScope scope;
     BfGram g;
     g.bf = bf;
     g.prec = (fio_prec)opts->sample_prec;
@@ -1241,6 +1236,7 @@ extern "C" fio_status hss_export(hss_t h, void *host_out, size_t count, void *st
 
 extern "C" fio_status hss_import(long n, int leaf, const int *ranks, const void *host_gen, size_t count, void *stream,
                                  hss_t *out) {
+    PoolScope scope;
     FIO_CHECK_ARG(ranks && host_gen && out && leaf >= 1 && leaf <= kMaxM);
     int Lh = 0;
     while (((long)leaf << Lh) < n) ++Lh;
@@ -1307,16 +1303,22 @@ extern "C" fio_status hss_matvec(hss_t h, const void *X, long ldx, void *Y, long
         }
         const double2 *x = (const double2 *)X;
         double2 *y = (double2 *)Y;
+        Uploads up(s);
+        auto lift = [&](int lv, const double2 *in, long ldin, double2 *out, long ldout, bool project) {
+            const ZgemmBatch zb = lift_level(h, lv, in, ldin, out, ldout, nrhs, project, up);
+            up.flush();
+            zb.run(project, zc(1.0), zc(0.0), s);
+        };
         // upward
-        lift_level(h, Lh, x, ldx, xh[Lh]->as<double2>(), rtot[Lh], nrhs, true, s);
+        lift(Lh, x, ldx, xh[Lh]->as<double2>(), rtot[Lh], true);
         for (int l = Lh - 1; l >= 1; --l)
-            lift_level(h, l, xh[l + 1]->as<double2>(), rtot[l + 1], xh[l]->as<double2>(), rtot[l], nrhs, true, s);
+            lift(l, xh[l + 1]->as<double2>(), rtot[l + 1], xh[l]->as<double2>(), rtot[l], true);
         // downward: children of level l
         for (int l = 0; l < Lh; ++l) {
             double2 *yc = yh[l + 1]->as<double2>();
             const double2 *xc = xh[l + 1]->as<double2>();
             long ldc = rtot[l + 1];
-            if (l > 0) lift_level(h, l, yh[l]->as<double2>(), rtot[l], yc, ldc, nrhs, false, s);
+            if (l > 0) lift(l, yh[l]->as<double2>(), rtot[l], yc, ldc, false);
             ZgemmBatch b1, b2;
             long ro = 0;
             for (int j = 0; j < h->nodes(l); ++j) {
@@ -1331,11 +1333,11 @@ extern "C" fio_status hss_matvec(hss_t h, const void *X, long ldx, void *Y, long
                 FIO_HIP(hipMemsetAsync(yc, 0, (size_t)ldc * nrhs * sizeof(double2), s));
                 beta = zc(1.0);
             }
-            b1.upload(s);
+            b1.put(up);
+            b2.put(up);
+            up.flush();
             b1.run(false, zc(1.0), beta, s);
-            b2.upload(s);
             b2.run(true, zc(1.0), beta, s);
-            FIO_HIP(hipStreamSynchronize(s));
         }
         // leaves: y = D x + U yhat
         ZgemmBatch bd, bu;
@@ -1347,9 +1349,10 @@ extern "C" fio_status hss_matvec(hss_t h, const void *X, long ldx, void *Y, long
                    nrhs, r);
             ro += r;
         }
-        bd.upload(s);
+        bd.put(up);
+        bu.put(up);
+        up.flush();
         bd.run(false, zc(1.0), zc(0.0), s);
-        bu.upload(s);
         bu.run(false, zc(1.0), zc(1.0), s);
         FIO_HIP(hipStreamSynchronize(s));
         for (int l = 1; l <= Lh; ++l) {
@@ -1360,6 +1363,9 @@ extern "C" fio_status hss_matvec(hss_t h, const void *X, long ldx, void *Y, long
     });
 }
 
-extern "C" void hss_destroy(hss_t h) { delete h; }
+extern "C" void hss_destroy(hss_t h) {
+    PoolScope scope;
+    delete h;
+}
 
 extern "C" void fio_hss_set_big_node(int rows) { fio::g_big_node = rows > 0 ? rows : fio::kBigNode; }

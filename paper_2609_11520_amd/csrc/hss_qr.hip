@@ -381,9 +381,9 @@ Extent extent(const std::vector<WyNode> &nodes) {
     return e;
 }
 
-void upload_nodes(const std::vector<WyNode> &nodes, WyWork &w, int nmax, int kmax, hipStream_t s) {
-    w.nodes.ensure(nodes.size() * sizeof(WyNode));
-    FIO_HIP(hipMemcpyAsync(w.nodes.p, nodes.data(), nodes.size() * sizeof(WyNode), hipMemcpyHostToDevice, s));
+void upload_nodes(const std::vector<WyNode> &nodes, WyWork &w, int nmax, int kmax, Uploads &up) {
+    w.nodes = up.put(nodes);
+    up.flush();
     w.block = nmax <= 2048 ? 8 : nmax <= kWyMaxRows ? 4 : 1;
     w.kt = (kmax + kWyBlock - 1) / kWyBlock * kWyBlock;
     w.tau.ensure(nodes.size() * (size_t)w.kt * sizeof(double));
@@ -392,7 +392,7 @@ void upload_nodes(const std::vector<WyNode> &nodes, WyWork &w, int nmax, int kma
 
 void update(const WyWork &w, int nn, int j0, int cmode, int ncols, bool fwd, hipStream_t s) {
     if (ncols <= 0) return;
-    const WyNode *nodes = w.nodes.as<WyNode>();
+    const WyNode *nodes = w.nodes;
     const double2 *T = w.T.as<double2>();
     // 4 columns per wave read V less often; 2 fill the card when there are few
     if ((long)ncols * nn >= 16384) {
@@ -412,12 +412,12 @@ void update(const WyWork &w, int nn, int j0, int cmode, int ncols, bool fwd, hip
 
 }  // namespace
 
-void wy_qr(const std::vector<WyNode> &nodes, WyWork &w, hipStream_t s) {
+void wy_qr(const std::vector<WyNode> &nodes, WyWork &w, Uploads &up, hipStream_t s) {
     const Extent e = extent(nodes);
     const int nn = (int)nodes.size();
     if (e.k == 0) return;
-    upload_nodes(nodes, w, e.n, e.k, s);
-    const WyNode *dn = w.nodes.as<WyNode>();
+    upload_nodes(nodes, w, e.n, e.k, up);
+    const WyNode *dn = w.nodes;
     for (int j0 = 0; j0 < e.k; j0 += w.block) {
         const int rows = e.n - j0;
         double *tau = w.tau.as<double>();
@@ -434,19 +434,20 @@ void wy_qr(const std::vector<WyNode> &nodes, WyWork &w, hipStream_t s) {
     FIO_HIP(hipGetLastError());
 }
 
-void wy_factors(const std::vector<WyNode> &nodes, const double *tau, int ldtau, WyWork &w, hipStream_t s) {
+void wy_factors(const std::vector<WyNode> &nodes, const double *tau, int ldtau, WyWork &w, Uploads &up,
+                hipStream_t s) {
     const Extent e = extent(nodes);
     if (e.k == 0) return;
-    upload_nodes(nodes, w, e.n, e.k, s);
+    upload_nodes(nodes, w, e.n, e.k, up);
     k_wy_factors<<<dim3((unsigned)(w.kt / w.block), (unsigned)nodes.size()), 256, 0, s>>>(
-        w.nodes.as<WyNode>(), tau, ldtau, w.block, w.kt, w.T.as<double2>());
+        w.nodes, tau, ldtau, w.block, w.kt, w.T.as<double2>());
     FIO_HIP(hipGetLastError());
 }
 
-void wy_apply(const std::vector<WyNode> &nodes, WyWork &w, bool unit, hipStream_t s) {
+void wy_apply(const std::vector<WyNode> &nodes, WyWork &w, bool unit, Uploads &up, hipStream_t s) {
     const Extent e = extent(nodes);
     if (e.k == 0) return;
-    upload_nodes(nodes, w, e.n, e.k, s);
+    upload_nodes(nodes, w, e.n, e.k, up);
     for (int j0 = w.kt - w.block; j0 >= 0; j0 -= w.block)
         update(w, (int)nodes.size(), j0, unit ? 1 : 0, e.nc - (unit ? j0 : 0), false, s);
     FIO_HIP(hipGetLastError());

@@ -457,17 +457,18 @@ __global__ void __launch_bounds__(256) k_fact_rows(const TriNode *__restrict__ n
 // device buffers of the level steps, kept over the levels of a factorization
 struct UlvWork {
     WyWork wy;
-    DevBuf nodes, Li;
+    DevBuf Li;
+    Uploads up;
+    explicit UlvWork(hipStream_t s) : up(s) {}
 };
 
 // the row sweep over all nodes of a list (mmax, kmax: the largest m and k)
 static void fact_sweep(const std::vector<TriNode> &nodes, int mmax, int kmax, bool unit, int *fail, UlvWork &w,
                        hipStream_t s) {
     const unsigned nn = (unsigned)nodes.size();
-    w.nodes.ensure(nn * sizeof(TriNode));
     w.Li.ensure((size_t)nn * kFact * kFact * sizeof(double2));
-    FIO_HIP(hipMemcpyAsync(w.nodes.p, nodes.data(), nn * sizeof(TriNode), hipMemcpyHostToDevice, s));
-    const TriNode *d = w.nodes.as<TriNode>();
+    const TriNode *d = w.up.put(nodes);
+    w.up.flush();
     double2 *Li = w.Li.as<double2>();
     for (int k0 = 0; k0 < kmax; k0 += kFact) {
         k_fact_diag<<<nn, 256, 0, s>>>(d, k0, Li, fail);
@@ -497,11 +498,10 @@ static void ulv_phase0_big(const FactArgs &fa, const std::vector<int> &ms, const
         un[j] = WyNode{Uw, Uw, ms[j], ms[j], ms[j], rs[j], rs[j]};
         qn[j] = WyNode{Uw, Uw + (size_t)2 * ms[j] * ms[j], ms[j], ms[j], ms[j], rs[j], ms[j]};
     }
-    wy_qr(un, w.wy, s);
-    wy_apply(qn, w.wy, true, s);
+    wy_qr(un, w.wy, w.up, s);
+    wy_apply(qn, w.wy, true, w.up, s);
     k_ubig_finish<<<dim3(16, y), 256, 0, s>>>(fa);
     FIO_HIP(hipGetLastError());
-    FIO_HIP(hipStreamSynchronize(s));   // the node lists are released here
 }
 
 static void ulv_phase1_big(const FactArgs &fa, const std::vector<int> &ms, const std::vector<int> &rs,
@@ -517,7 +517,6 @@ static void ulv_phase1_big(const FactArgs &fa, const std::vector<int> &ms, const
     const unsigned t = (unsigned)((mmax + 31) / 32);
     k_fact_prep<<<dim3(t, t, (unsigned)ms.size()), 256, 0, s>>>(fa);
     fact_sweep(tn, mmax, kmax, false, fa.fail, w, s);
-    FIO_HIP(hipStreamSynchronize(s));   // the node list is released here
 }
 
 // Merge of eq. ulv_merge for every parent (one workgroup per parent):
@@ -586,7 +585,6 @@ static void ulv_root_factor(double2 *D, int m, double2 *Linv, int *fail, UlvWork
     k_root_eye<<<256, 256, 0, s>>>(Linv, m);
     const std::vector<TriNode> tn{TriNode{D, Linv, m, m}};
     fact_sweep(tn, m, m, true, fail, w, s);
-    FIO_HIP(hipStreamSynchronize(s));     // the node list is released here
 }
 
 // One level of the ULV solve.  UP: z = W y_tau, rows < k to Bh, rows >= k to the parent's
@@ -966,8 +964,9 @@ static fio_status factor_impl(hss_s *h, hipStream_t s, hss_ulv_t *out) {
         DevBuf failb(sizeof(int));
         FIO_HIP(hipMemsetAsync(failb.p, 0, sizeof(int), s));
         // level-by-level factorization
-        DevBuf Dcur, Ucur, D22, U2, scr, tmp;
-        UlvWork uw;
+        DevBuf Dcur, Ucur, Dn, Un, D22, U2, scr, tmp;
+        UlvWork uw(s);
+        Uploads &up = uw.up;
         const double2 *Din = h->Dbuf.as<double2>();
         std::vector<size_t> din_off(h->nodes(Lh)), uin_off = h->uoff[Lh];
         for (int j = 0; j < h->nodes(Lh); ++j) din_off[j] = (size_t)j * h->leaf * h->leaf;
@@ -986,31 +985,25 @@ static fio_status factor_impl(hss_s *h, hipStream_t s, hss_ulv_t *out) {
                 sctot += (size_t)3 * m * m;
                 if (m > kUlvMaxM) throw Err{FIO_ERR_UNSUPPORTED};
             }
-            D22.alloc(stot * sizeof(double2) + 16);
-            U2.alloc(stot * sizeof(double2) + 16);
-            scr.alloc(sctot * sizeof(double2) + 16);
-            std::vector<char> blob;
-            size_t o_doff = put(blob, din_off), o_uoff = put(blob, uin_off), o_m = put(blob, f->m[l]),
-                   o_r = put(blob, f->r[l]), o_w = put(blob, f->woff[l]), o_s = put(blob, soff),
-                   o_sc = put(blob, scoff);
-            DevBuf meta(blob.size());
-            FIO_HIP(hipMemcpyAsync(meta.p, blob.data(), blob.size(), hipMemcpyHostToDevice, s));
-            char *mb = meta.as<char>();
+            D22.ensure(stot * sizeof(double2) + 16);
+            U2.ensure(stot * sizeof(double2) + 16);
+            scr.ensure(sctot * sizeof(double2) + 16);
             FactArgs fa;
             fa.D = Din;
-            fa.doff = (const size_t *)(mb + o_doff);
+            fa.doff = up.put(din_off);
             fa.U = Uin;
-            fa.uoff = (const size_t *)(mb + o_uoff);
-            fa.msz = (const int *)(mb + o_m);
-            fa.rsz = (const int *)(mb + o_r);
+            fa.uoff = up.put(uin_off);
+            fa.msz = up.put(f->m[l]);
+            fa.rsz = up.put(f->r[l]);
             fa.W = f->W.as<double2>();
-            fa.woff = (const size_t *)(mb + o_w);
+            fa.woff = up.put(f->woff[l]);
             fa.D22 = D22.as<double2>();
             fa.U2 = U2.as<double2>();
-            fa.soff = (const size_t *)(mb + o_s);
+            fa.soff = up.put(soff);
             fa.scratch = scr.as<double2>();
-            fa.scoff = (const size_t *)(mb + o_sc);
+            fa.scoff = up.put(scoff);
             fa.fail = failb.as<int>();
+            up.flush();
             if (mlev < g_ulv_big) {
                 k_ulv_node<0><<<nn, ulv_threads(mlev), 0, s>>>(fa);
                 FIO_HIP(hipGetLastError());
@@ -1028,11 +1021,11 @@ static fio_status factor_impl(hss_s *h, hipStream_t s, hss_ulv_t *out) {
                     g1.add(Q, m, Din + din_off[j], m, W + f->woff[l][j], m, m, m, m);
                     g2.add(W + f->woff[l][j], m, Q, m, T, m, m, m, m);
                 }
-                g1.upload(s);
-                g2.upload(s);
+                g1.put(up);
+                g2.put(up);
+                up.flush();
                 g1.run(true, zc(1.0, 0.0), zc(0.0, 0.0), s);
                 g2.run(false, zc(1.0, 0.0), zc(0.0, 0.0), s);
-                FIO_HIP(hipStreamSynchronize(s));   // the descriptor lists are released here
             }
             if (mlev < g_ulv_big) {
                 k_ulv_node<1><<<nn, ulv_threads(mlev), 0, s>>>(fa);
@@ -1055,11 +1048,11 @@ static fio_status factor_impl(hss_s *h, hipStream_t s, hss_ulv_t *out) {
                     g3.add(X, m, X, m, D22b + soff[j], r, r, r, k);
                     g4.add(X, m, W + f->woff[l][j], m, W + f->woff[l][j] + k, m, r, m, k);
                 }
-                g3.upload(s);
-                g4.upload(s);
+                g3.put(up);
+                g4.put(up);
+                up.flush();
                 g3.run(true, zc(-1.0, 0.0), zc(1.0, 0.0), s);
                 g4.run(true, zc(-1.0, 0.0), zc(1.0, 0.0), s);
-                FIO_HIP(hipStreamSynchronize(s));   // the descriptor lists are released here
             }
             // merge into level l-1
             const int np = h->nodes(l - 1);
@@ -1079,33 +1072,26 @@ static fio_status factor_impl(hss_s *h, hipStream_t s, hss_ulv_t *out) {
                 uooff[j] = ut;
                 ut += (size_t)m * rpar[j];
             }
-            DevBuf Dn(dt * sizeof(double2) + 16), Un(ut * sizeof(double2) + 16);
-            tmp.alloc(tt * sizeof(double2) + 16);
-            std::vector<char> blob2;
-            std::vector<size_t> boff = h->boff[l - 1];
-            size_t q_s = put(blob2, soff), q_r = put(blob2, f->r[l]), q_b = put(blob2, boff), q_up = put(blob2, upoff),
-                   q_rp = put(blob2, rpar), q_do = put(blob2, dooff), q_uo = put(blob2, uooff), q_t = put(blob2, toff);
-            DevBuf meta2(blob2.size());
-            FIO_HIP(hipMemcpyAsync(meta2.p, blob2.data(), blob2.size(), hipMemcpyHostToDevice, s));
-            char *m2 = meta2.as<char>();
+            Dn.ensure(dt * sizeof(double2) + 16);
+            Un.ensure(ut * sizeof(double2) + 16);
+            tmp.ensure(tt * sizeof(double2) + 16);
+            const std::vector<size_t> &boff = h->boff[l - 1];
             MergeArgs ma;
             ma.D22 = D22.as<double2>();
             ma.U2 = U2.as<double2>();
-            ma.soff = (const size_t *)(m2 + q_s);
-            ma.rch = (const int *)(m2 + q_r);
+            ma.soff = fa.soff;
+            ma.rch = fa.rsz;
             ma.B = h->Bbuf.as<double2>();
-            ma.boff = (const size_t *)(m2 + q_b);
+            ma.boff = up.put(boff);
             ma.Upar = (l - 1 >= 1) ? h->Ubuf[l - 1]->as<double2>() : nullptr;
-            ma.upoff = (const size_t *)(m2 + q_up);
-            ma.rpar = (const int *)(m2 + q_rp);
+            ma.upoff = up.put(upoff);
+            ma.rpar = up.put(rpar);
             ma.Dout = Dn.as<double2>();
-            ma.dooff = (const size_t *)(m2 + q_do);
+            ma.dooff = up.put(dooff);
             ma.Uout = Un.as<double2>();
-            ma.uooff = (const size_t *)(m2 + q_uo);
+            ma.uooff = up.put(uooff);
             ma.tmp = tmp.as<double2>();
-            ma.toff = (const size_t *)(m2 + q_t);
-            k_ulv_merge_prep<<<np, ulv_threads(mlev), 0, s>>>(ma);
-            FIO_HIP(hipGetLastError());
+            ma.toff = up.put(toff);
             {
                 ZgemmBatch g1, g2, g3, g4;
                 const double2 *U2b = U2.as<double2>();
@@ -1124,15 +1110,14 @@ static fio_status factor_impl(hss_s *h, hipStream_t s, hss_ulv_t *out) {
                         g4.add(Ub, r2, Up + r1, m, Uo + r1, m, r2, rp, r2);                  // rows of a2
                     }
                 }
-                for (ZgemmBatch *g : {&g1, &g2, &g3, &g4}) g->upload(s);
+                for (ZgemmBatch *g : {&g1, &g2, &g3, &g4}) g->put(up);
+                up.flush();
+                k_ulv_merge_prep<<<np, ulv_threads(mlev), 0, s>>>(ma);
+                FIO_HIP(hipGetLastError());
                 for (ZgemmBatch *g : {&g1, &g2, &g3, &g4}) g->run(false, zc(1.0, 0.0), zc(0.0, 0.0), s);
                 k_ulv_merge_fill<<<np, ulv_threads(mlev), 0, s>>>(ma);
                 FIO_HIP(hipGetLastError());
-                FIO_HIP(hipStreamSynchronize(s));   // the descriptor lists are released here
             }
-            int fail = 0;
-            FIO_HIP(hipMemcpy(&fail, failb.p, sizeof(int), hipMemcpyDeviceToHost));
-            if (fail) throw Err{FIO_ERR_NOT_HPD};
             Dcur.swap(Dn);
             Ucur.swap(Un);
             Din = Dcur.as<double2>();
@@ -1140,12 +1125,12 @@ static fio_status factor_impl(hss_s *h, hipStream_t s, hss_ulv_t *out) {
             din_off = dooff;
             uin_off = uooff;
         }
-        if (f->m0 > 0) {
-            ulv_root_factor(Dcur.as<double2>(), f->m0, f->Linv.as<double2>(), failb.as<int>(), uw, s);
-            int fail = 0;
-            FIO_HIP(hipMemcpy(&fail, failb.p, sizeof(int), hipMemcpyDeviceToHost));
-            if (fail) throw Err{FIO_ERR_NOT_HPD};
-        }
+        if (f->m0 > 0) ulv_root_factor(Dcur.as<double2>(), f->m0, f->Linv.as<double2>(), failb.as<int>(), uw, s);
+        // a level that fails leaves values that are not numbers to the levels above, and one count here
+        int fail = 0;
+        FIO_HIP(hipMemcpyAsync(&fail, failb.p, sizeof(int), hipMemcpyDeviceToHost, s));
+        FIO_HIP(hipStreamSynchronize(s));
+        if (fail) throw Err{FIO_ERR_NOT_HPD};
         // device tables for the solve
         std::vector<char> blob;
         f->meta_woff.assign(Lh + 1, 0);
@@ -1316,6 +1301,7 @@ size_t ulv_ws_bytes_pub(const hss_ulv_s *f, int nrhs) { return ulv_ws_bytes(f, n
 using namespace fio;
 
 extern "C" fio_status hss_ulv_factor(hss_t h, void *stream, hss_ulv_t *out) {
+    PoolScope scope;
     FIO_CHECK_ARG(h && out);
     return factor_impl(h, as_stream(stream), out);
 }
@@ -1350,6 +1336,9 @@ extern "C" fio_status hss_ulv_solve(hss_ulv_t f, const void *Y, long ldy, void *
     });
 }
 
-extern "C" void hss_ulv_destroy(hss_ulv_t f) { delete f; }
+extern "C" void hss_ulv_destroy(hss_ulv_t f) {
+    PoolScope scope;
+    delete f;
+}
 
 extern "C" void fio_ulv_set_big_node(int rows) { fio::g_ulv_big = rows > 0 ? rows : fio::kUlvBig; }
