@@ -94,7 +94,7 @@ struct PoolScope {
 // RAII device buffer
 struct DevBuf {
     void *p = nullptr;
-    size_t bytes = 0;
+    size_t bytes = 0;                             // capacity: at least what was asked for
     DevBuf() = default;
     explicit DevBuf(size_t b) { alloc(b); }
     void alloc(size_t b) {
@@ -133,7 +133,7 @@ struct Uploads {
     Uploads &operator=(const Uploads &) = delete;
     template <typename T> const T *put(const std::vector<T> &v) {
         const size_t bytes = v.size() * sizeof(T), need = (bytes + 255) & ~(size_t)255;
-        if (blocks.empty() || blocks.back()->used + need > blocks.back()->dev.bytes) {
+        if (blocks.empty() || blocks.back()->used + need > blocks.back()->size) {
             flush();
             const size_t size = need > kBlock ? need : kBlock;
             blocks.push_back(std::make_unique<Block>(size));
@@ -159,8 +159,8 @@ struct Uploads {
     struct Block {
         DevBuf dev;
         std::unique_ptr<char[]> host;
-        size_t used = 0, sent = 0;
-        explicit Block(size_t size) : dev(size), host(new char[size]) {}
+        size_t size, used = 0, sent = 0;          // size: of the host side (the device block may be larger)
+        explicit Block(size_t n) : dev(n), host(new char[n]), size(n) {}
     };
     hipStream_t s;
     std::vector<std::unique_ptr<Block>> blocks;

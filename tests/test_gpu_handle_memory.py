@@ -66,3 +66,21 @@ def test_threads_and_bound():
     for n in sizes:
         assert torch.equal(got[n], want[n])
     assert free0 - torch.cuda.mem_get_info()[0] < 8 << 30
+
+
+def test_tables_fill_blocks_larger_than_asked_for():
+    """Offset tables of more than a block (1 MiB), on device blocks kept from buffers of 1.05 to 1.2 MiB."""
+    F = fiohss()
+    import torch
+    step("tables on kept blocks")
+    Y = dev(fi.rhs(9, 1 << 16, 2))
+    want = None
+    for k in (0, 1, 2, 3):
+        # handles with buffers a little above 1 MiB, which the tables of the next construction may take
+        small = [F.HSS.from_bf(F.BF(1 << 10, 9, 2.0 / 16, 1.0 / 16), tol=1e-3, p=p, seed=5) for p in (8, 12, 16, 20)]
+        del small
+        B = F.BF(1 << 16, 9, 2.0 / 16, 1.0 / 16)
+        U = F.ULV(F.HSS.from_bf(B, tol=1e-3, p=10, seed=6, leaf=16))
+        got, _ = F.approx_solve(B, U, Y)
+        want = got if want is None else want
+        assert torch.equal(got, want)
