@@ -42,6 +42,7 @@
 
 #include "bf.h"
 #include "ddmath.h"
+#include "mat4.h"
 #include "timing.h"
 
 namespace fio {
@@ -297,34 +298,6 @@ template <typename T> struct K2Args {
 
 __device__ __forceinline__ double2 to_z(double2 v) { return v; }
 __device__ __forceinline__ double2 to_z(float2 v) { return zc(v.x, v.y); }
-
-// 16 x 16 tile of four reals per lane: lane l holds column l & 15
-template <typename T> struct Mat4;
-template <> struct Mat4<double> {
-    using V = double __attribute__((ext_vector_type(4)));
-    static __device__ __forceinline__ V mac(double a, double b, V c) {
-        return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-    }
-    static __device__ __forceinline__ int row(int lane, int i) { return (lane >> 4) + 4 * i; }
-};
-template <> struct Mat4<float> {
-    using V = float __attribute__((ext_vector_type(4)));
-    static __device__ __forceinline__ V mac(float a, float b, V c) {
-        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-    }
-    static __device__ __forceinline__ int row(int lane, int i) { return 4 * (lane >> 4) + i; }
-};
-
-// the other half of a 16-lane row: lane l gets lane l xor 8
-__device__ __forceinline__ float row_half(float v) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x128, 0xf, 0xf, true));
-}
-__device__ __forceinline__ double row_half(double v) {
-    const long b = __builtin_bit_cast(long, v);
-    const int lo = __builtin_amdgcn_mov_dpp((int)b, 0x128, 0xf, 0xf, true);
-    const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), 0x128, 0xf, 0xf, true);
-    return __builtin_bit_cast(double, ((long)hi << 32) | (unsigned)lo);
-}
 
 // One step of an apply: each wave forms NR x 16 rows of an output block for 8 NC right-hand sides on
 // the matrix cores.  The real and imaginary parts of 8 columns are the 16 columns of one real tile, so that

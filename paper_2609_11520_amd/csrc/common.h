@@ -190,8 +190,6 @@ struct ZgemmDesc {
 };
 void zgemm_vbatched(const ZgemmDesc *d_descs, int count, int maxM, int maxN, bool conjA, double2 alpha,
                     double2 beta, hipStream_t s);
-// a single GEMM whose descriptor travels as a kernel argument (no device copy needed)
-void zgemm_one(const ZgemmDesc &d, bool conjA, double2 alpha, double2 beta, hipStream_t s);
 
 // A descriptor list built on the host
 struct ZgemmBatch {

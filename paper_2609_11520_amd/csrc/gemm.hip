@@ -84,30 +84,6 @@ __global__ void __launch_bounds__(256) k_zgemm_vb(const ZgemmDesc *__restrict__ 
     tile_zgemm<CONJA, BETA>(descs[blockIdx.y], tilesN, alpha, beta);
 }
 
-template <bool CONJA, bool BETA>
-__global__ void __launch_bounds__(256) k_zgemm_one(ZgemmDesc d, int tilesN, double2 alpha, double2 beta) {
-    tile_zgemm<CONJA, BETA>(d, tilesN, alpha, beta);
-}
-
-void zgemm_one(const ZgemmDesc &d, bool conjA, double2 alpha, double2 beta, hipStream_t s) {
-    if (d.M <= 0 || d.N <= 0) return;
-    int tilesM = (d.M + TM - 1) / TM, tilesN = (d.N + TN - 1) / TN;
-    const bool useBeta = !(beta.x == 0.0 && beta.y == 0.0);
-    dim3 grid(tilesM * tilesN, 1);
-    if (conjA) {
-        if (useBeta)
-            k_zgemm_one<true, true><<<grid, 256, 0, s>>>(d, tilesN, alpha, beta);
-        else
-            k_zgemm_one<true, false><<<grid, 256, 0, s>>>(d, tilesN, alpha, beta);
-    } else {
-        if (useBeta)
-            k_zgemm_one<false, true><<<grid, 256, 0, s>>>(d, tilesN, alpha, beta);
-        else
-            k_zgemm_one<false, false><<<grid, 256, 0, s>>>(d, tilesN, alpha, beta);
-    }
-    FIO_HIP(hipGetLastError());
-}
-
 void zgemm_vbatched(const ZgemmDesc *d_descs, int count, int maxM, int maxN, bool conjA, double2 alpha,
                     double2 beta, hipStream_t s) {
     if (count <= 0 || maxM <= 0 || maxN <= 0) return;

@@ -9,9 +9,11 @@
 //   W = [L11^{-1} Q1^*; Q2^* - Dhat21 L11^{-1} Q1^*]
 // so that the bottom-up step is [bhat1; yhat2] = W y_tau and the top-down step is
 // c_tau = W^* [bhat1; chat2]; the root keeps Linv = L_rho^{-1}.  The online solve
-// is therefore 2 Lh + 2 batched small GEMM launches (see k_ulv_level).
+// is therefore one batched product per level and direction (k_ulv_mm), with the levels of small
+// nodes in bands of up to four (k_ulv_band).
 #include "hss.h"
 #include "hss_qr.h"
+#include "mat4.h"
 #include "timing.h"
 
 #include <cmath>
@@ -25,11 +27,9 @@ struct hss_ulv_s {
     std::vector<std::vector<long>> yoff, roff;  // rows of a node in its level vector / parent vector
     std::vector<long> rows;                     // rows of the level-l vector (l = 0..Lh)
     fio::DevBuf W;                              // all W slots
-    fio::DevBuf WH;                             // W^* of every node (same offsets), for narrow solves
     fio::DevBuf Linv;                           // m0 x m0
     fio::DevBuf meta;                           // device copies of the per-level tables
     std::vector<size_t> meta_woff, meta_m, meta_k, meta_yoff, meta_roff;   // byte offsets into meta
-    fio::DevBuf rootdesc;                       // ZgemmDesc[2] for the root (pointers into ws set per call)
     fio::DevBuf ws;
     std::mutex ws_mu;
 };
@@ -588,7 +588,7 @@ static void ulv_root_factor(double2 *D, int m, double2 *Linv, int *fail, UlvWork
 }
 
 // One level of the ULV solve.  UP: z = W y_tau, rows < k to Bh, rows >= k to the parent's
-// vector (Ylo).  DOWN: c_tau = W^* [Bh rows; Ylo rows].  32 x 32 output tiles, K through LDS.
+// vector (Ylo).  DOWN: c_tau = W^* [Bh rows; Ylo rows].
 struct LevelArgs {
     const double2 *W;
     const size_t *woff;
@@ -596,326 +596,474 @@ struct LevelArgs {
     const long *yoff, *roff;
 };
 
-// The solve's output: written, or added to what the output holds (accum != 0: the update
-// f += G~^{-1} y of a refinement step, fused into the last level)
-__device__ __forceinline__ void ulv_store(double2 *p, double2 v, int accum) {
-    if (accum) {
-        const double2 o = *p;
-        v = zc(o.x + v.x, o.y + v.y);
-    }
-    *p = v;
-}
+// the vectors of a level: Y its own (input of UP, output of DOWN; accum != 0 adds, the update f += G~^{-1} y of
+// a refinement step), Bh its eliminated rows, Ylo its parents'
+struct LevelVecs {
+    const double2 *Yin;
+    double2 *Yout, *Bh, *Ylo;
+    long ldy, ldb, ldlo;
+    int nrhs, accum;
+};
 
+// row gm of a node's result, column gc
 template <bool DOWN>
-__global__ void __launch_bounds__(256) k_ulv_level(LevelArgs a, const double2 *__restrict__ Yin, long ldin,
-                                                   double2 *__restrict__ Bh, long ldb, double2 *__restrict__ Ylo,
-                                                   long ldlo, double2 *__restrict__ Yout, long ldout, int nrhs,
-                                                   int tilesN, int accum) {
-    const int node = blockIdx.y;
-    const int m = a.m[node], k = a.k[node];
-    const int tm = blockIdx.x / tilesN, tn = blockIdx.x % tilesN;
-    const int m0 = tm * 32, n0 = tn * 32;
-    if (m0 >= m || n0 >= nrhs) return;
-    const double2 *W = a.W + a.woff[node];
-    const long yo = a.yoff[node], ro = a.roff[node];
-    __shared__ double2 As[16][33];
-    __shared__ double2 Bs[16][33];
-    const int tid = threadIdx.x, tx = tid % 16, ty = tid / 16;
-    double2 acc[2][2];
-#pragma unroll
-    for (int x = 0; x < 2; ++x)
-#pragma unroll
-        for (int y = 0; y < 2; ++y) acc[x][y] = zc(0.0, 0.0);
-    for (int k0 = 0; k0 < m; k0 += 16) {
-        // all four loads of a thread are issued before any is used (no load inside a thread
-        // condition: a thread outside the node or the column block reads W[0] and keeps zero)
-        double2 ta[2], tb[2];
-        int am[2], ak[2], bk[2], bn[2];
-        bool aok[2], bok[2];
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const int e = tid + 256 * q;
-            if (DOWN) {      // op(A) = W^*: element (row, kk) = conj(W(kk, row))
-                ak[q] = e % 16;
-                am[q] = e / 16;
-            } else {
-                am[q] = e % 32;
-                ak[q] = e / 32;
-            }
-            const int gm = m0 + am[q], gk = k0 + ak[q];
-            aok[q] = gm < m && gk < m;
-            ta[q] = W[aok[q] ? (DOWN ? gk + (size_t)gm * m : gm + (size_t)gk * m) : 0];
-            bk[q] = e % 16;
-            bn[q] = e / 16;
-            const int hk = k0 + bk[q], hn = n0 + bn[q];
-            bok[q] = hk < m && hn < nrhs;
-            const double2 *src;
-            if (DOWN)
-                src = !bok[q] ? W : (hk < k ? Bh + (yo + hk) + (size_t)hn * ldb : Ylo + (ro + hk - k) + (size_t)hn * ldlo);
-            else
-                src = !bok[q] ? W : Yin + (yo + hk) + (size_t)hn * ldin;
-            tb[q] = *src;
-        }
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const double2 t = DOWN ? zc(ta[q].x, -ta[q].y) : ta[q];
-            As[ak[q]][am[q]] = aok[q] ? t : zc(0.0, 0.0);
-            Bs[bk[q]][bn[q]] = bok[q] ? tb[q] : zc(0.0, 0.0);
-        }
-        __syncthreads();
-#pragma unroll
-        for (int kk = 0; kk < 16; ++kk) {
-            double2 a0 = As[kk][tx], a1 = As[kk][tx + 16];
-            double2 b0 = Bs[kk][ty], b1 = Bs[kk][ty + 16];
-            cfma(acc[0][0], a0, b0);
-            cfma(acc[0][1], a0, b1);
-            cfma(acc[1][0], a1, b0);
-            cfma(acc[1][1], a1, b1);
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int x = 0; x < 2; ++x) {
-        int gm = m0 + tx + 16 * x;
-        if (gm >= m) continue;
-#pragma unroll
-        for (int y = 0; y < 2; ++y) {
-            int gn = n0 + ty + 16 * y;
-            if (gn >= nrhs) continue;
-            if (DOWN)
-                ulv_store(Yout + (yo + gm) + (size_t)gn * ldout, acc[x][y], accum);
-            else if (gm < k)
-                Bh[(yo + gm) + (size_t)gn * ldb] = acc[x][y];
-            else
-                Ylo[(ro + gm - k) + (size_t)gn * ldlo] = acc[x][y];
-        }
+__device__ __forceinline__ void ulv_put(const LevelVecs &v, long yo, long ro, int k, int gm, int gc, double2 z) {
+    if (DOWN) {
+        double2 *p = v.Yout + (yo + gm) + (size_t)gc * v.ldy;
+        if (v.accum) z = cadd(*p, z);
+        *p = z;
+    } else if (gm < k) {
+        v.Bh[(yo + gm) + (size_t)gc * v.ldb] = z;
+    } else {
+        v.Ylo[(ro + gm - k) + (size_t)gc * v.ldlo] = z;
     }
 }
 
-// The same level product for nodes of at most 64 rows (the leaf level): one workgroup per
-// node and 64 right-hand sides, 4 x 4 outputs per thread, so W and the vector block are read
-// once and every LDS operand read feeds four multiply-adds; the next 16-deep tiles of both
-// operands are fetched into registers while the current ones are used.  Accumulation runs
-// over k in the order of k_ulv_level, so both kernels give identical results.
-template <bool DOWN>
-__global__ void __launch_bounds__(256) k_ulv_level64(LevelArgs a, const double2 *__restrict__ Yin, long ldin,
-                                                     double2 *__restrict__ Bh, long ldb, double2 *__restrict__ Ylo,
-                                                     long ldlo, double2 *__restrict__ Yout, long ldout, int nrhs,
-                                                     int accum) {
-    const int node = blockIdx.y;
-    const int m = a.m[node], k = a.k[node];
-    const int n0 = blockIdx.x * 64;
-    if (m == 0 || n0 >= nrhs) return;
-    const double2 *W = a.W + a.woff[node];
-    const long yo = a.yoff[node], ro = a.roff[node];
-    __shared__ double2 As[16][65];
-    __shared__ double2 Bs[16][65];
-    const int tid = threadIdx.x, tx = tid % 16, ty = tid / 16;
-    double2 acc[4][4];
+// The complex entries of a 16-row tile: lanes of columns 0 .. 7 hold A_r X_r and A_i X_r, the others A_r X_i and
+// A_i X_i (W^* has -A_i); a lane gets the entry of row i, the lane 8 on that of row i + 2.
+template <bool DOWN, typename F>
+__device__ __forceinline__ void ulv_tile(Mat4<double>::V P, Mat4<double>::V Q, int lane, F &&put) {
+    const bool im = (lane & 15) >= 8;
 #pragma unroll
-    for (int x = 0; x < 4; ++x)
-#pragma unroll
-        for (int y = 0; y < 4; ++y) acc[x][y] = zc(0.0, 0.0);
-    // element r of this thread's share of a 16-deep A / B tile, and its LDS slot
-    int amm[4], akk[4], bkk[4], bnn[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int e = tid + 256 * r;
+    for (int i = 0; i < 2; ++i) {
+        const double tp = row_half(im ? P[i] : P[i + 2]), p = im ? P[i + 2] : P[i];
+        double tq = row_half(im ? Q[i] : Q[i + 2]), q = im ? Q[i + 2] : Q[i];
         if (DOWN) {
-            akk[r] = e % 16;
-            amm[r] = e / 16;
-        } else {
-            amm[r] = e % 64;
-            akk[r] = e / 64;
+            tq = -tq;
+            q = -q;
         }
-        bkk[r] = e % 16;
-        bnn[r] = e / 16;
+        put(Mat4<double>::row(lane, i) + (im ? Mat4<double>::row(0, 2) : 0), im ? zc(tp - q, p + tq) : zc(p - tq, tp + q));
     }
-    double2 pa[4], pb[4];
-    // The loads carry no branch: a thread outside the node or the column block reads W[0] (the
-    // node has m >= 1 rows), and the zeroing and the conjugation of the W^* operand happen when
-    // the tile is written to LDS.  With the load inside a thread condition and the conjugation
-    // next to it, the compiler waited for each load before issuing the next.
-    auto a_ok = [&](int k0, int r) { return amm[r] < m && k0 + akk[r] < m; };
-    auto b_ok = [&](int k0, int r) { return k0 + bkk[r] < m && n0 + bnn[r] < nrhs; };
-    auto fetch = [&](int k0) {
+}
+
+// Nodes of more than 64 rows (2D trees have 2 to 32 of them in a level): a workgroup forms 16 NR rows for 8 columns
+// on the matrix cores, entries straight from memory to registers, D steps of 4 inner indices ahead; each of
+// its 8 waves takes an eighth of the inner dimension, summed in order through LDS.
+// 4 nodes of 242 rows, 8 columns: 35.5 -> 8.2 us; a root of 424 rows 137 -> 20 us (one lane per row with
+// partial sums in memory, tiles of 32 x 32 through LDS: 8 to 40 workgroups in all).  The load latency of a
+// wave's 8 to 14 steps bounds it.
+template <bool DOWN, int NR>
+__global__ void __launch_bounds__(512) k_ulv_mm(LevelArgs a, LevelVecs v, int rgroups, int cgroups, unsigned nwork) {
+    using M = Mat4<double>;
+    using V = M::V;
+    constexpr int KS = 8, D = 4;
+    const int lane = threadIdx.x & 63, lr = lane & 15, lk = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // consecutive workgroups run on one XCD, whose L2 then serves the column groups of a node
+    const unsigned work = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    if (work >= nwork) return;
+    const int cg = work % cgroups, rn = work / cgroups, r0 = rn % rgroups * 16 * NR, node = rn / rgroups;
+    const int m = a.m[node], k = a.k[node];
+    if (r0 >= m) return;
+    const long yo = a.yoff[node], ro = a.roff[node];
+    const int c = cg * 8 + (lr & 7), cc = c < v.nrhs ? c : v.nrhs - 1;
+    const int ns = (m + 3) >> 2, per = (ns + KS - 1) / KS, s0 = wave * per;
+    const int s1 = s0 + per < ns ? s0 + per : ns;
+    const double2 *W = a.W + a.woff[node];
+    int row[NR];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int gm = amm[r], gk = k0 + akk[r];
-            pa[r] = W[a_ok(k0, r) ? (DOWN ? gk + (size_t)gm * m : gm + (size_t)gk * m) : 0];
-        }
+    for (int t = 0; t < NR; ++t) {
+        const int r = r0 + 16 * t + lr;
+        row[t] = r < m ? r : m - 1;                 // rows beyond the node repeat its last one and are not stored
+    }
+    const double *y1 = reinterpret_cast<const double *>(DOWN ? v.Bh + yo + (size_t)cc * v.ldb
+                                                             : v.Yin + yo + (size_t)cc * v.ldy) + (lr >> 3);
+    const double *y2 = reinterpret_cast<const double *>(v.Ylo + ro - k + (size_t)cc * v.ldlo) + (lr >> 3);
+    double2 fa[D][NR];
+    double fb[D];
+    auto load = [&](int d, int s) {
+        const int l = 4 * s + lk, lc = l < m ? l : m - 1;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int gk = k0 + bkk[r], gn = n0 + bnn[r];
-            const double2 *src;
-            if (DOWN)
-                src = !b_ok(k0, r) ? W
-                                   : (gk < k ? Bh + (yo + gk) + (size_t)gn * ldb : Ylo + (ro + gk - k) + (size_t)gn * ldlo);
-            else
-                src = !b_ok(k0, r) ? W : Yin + (yo + gk) + (size_t)gn * ldin;
-            pb[r] = *src;
+        for (int t = 0; t < NR; ++t) fa[d][t] = DOWN ? W[lc + (size_t)row[t] * m] : W[row[t] + (size_t)lc * m];
+        const double x = (DOWN && lc >= k ? y2 : y1)[2 * (size_t)lc];
+        fb[d] = l < m ? x : 0.0;
+    };
+    V P[NR], Q[NR];
+#pragma unroll
+    for (int t = 0; t < NR; ++t) P[t] = Q[t] = V{0, 0, 0, 0};
+    auto mac = [&](int d) {
+#pragma unroll
+        for (int t = 0; t < NR; ++t) {
+            P[t] = M::mac(fa[d][t].x, fb[d], P[t]);
+            Q[t] = M::mac(fa[d][t].y, fb[d], Q[t]);
         }
     };
-    fetch(0);
-    for (int k0 = 0; k0 < m; k0 += 16) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const double2 t = DOWN ? zc(pa[r].x, -pa[r].y) : pa[r];
-            As[akk[r]][amm[r]] = a_ok(k0, r) ? t : zc(0.0, 0.0);
-            Bs[bkk[r]][bnn[r]] = b_ok(k0, r) ? pb[r] : zc(0.0, 0.0);
+    for (int d = 0; d < D; ++d)
+        if (s0 + d < s1) load(d, s0 + d);
+    int s = s0;
+    for (; s + D <= s1; s += D) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            mac(d);
+            if (s + d + D < s1) load(d, s + d + D);
         }
-        __syncthreads();
-        // the next tile is fetched while this one is used
-        if (k0 + 16 < m) fetch(k0 + 16);
-#pragma unroll
-        for (int kk = 0; kk < 16; ++kk) {
-            double2 av[4], bv[4];
-#pragma unroll
-            for (int x = 0; x < 4; ++x) av[x] = As[kk][tx + 16 * x];
-#pragma unroll
-            for (int y = 0; y < 4; ++y) bv[y] = Bs[kk][ty + 16 * y];
-#pragma unroll
-            for (int x = 0; x < 4; ++x)
-#pragma unroll
-                for (int y = 0; y < 4; ++y) cfma(acc[x][y], av[x], bv[y]);
-        }
-        __syncthreads();
     }
 #pragma unroll
-    for (int x = 0; x < 4; ++x) {
-        const int gm = tx + 16 * x;
-        if (gm >= m) continue;
+    for (int d = 0; d < D; ++d)
+        if (s + d < s1) mac(d);
+    __shared__ double2 part[KS * NR * 128];
 #pragma unroll
-        for (int y = 0; y < 4; ++y) {
-            const int gn = n0 + ty + 16 * y;
-            if (gn >= nrhs) continue;
-            if (DOWN)
-                ulv_store(Yout + (yo + gm) + (size_t)gn * ldout, acc[x][y], accum);
-            else if (gm < k)
-                Bh[(yo + gm) + (size_t)gn * ldb] = acc[x][y];
-            else
-                Ylo[(ro + gm - k) + (size_t)gn * ldlo] = acc[x][y];
-        }
+    for (int t = 0; t < NR; ++t)
+        ulv_tile<DOWN>(P[t], Q[t], lane, [&](int r, double2 z) { part[(wave * 16 * NR + 16 * t + r) * 8 + (lr & 7)] = z; });
+    __syncthreads();
+    for (int e = threadIdx.x; e < 128 * NR; e += 512) {
+        const int gm = r0 + (e >> 3), gc = cg * 8 + (e & 7);
+        if (gm >= m || gc >= v.nrhs) continue;
+        double2 z = part[e];
+#pragma unroll
+        for (int w = 1; w < KS; ++w) z = cadd(z, part[w * 128 * NR + e]);
+        ulv_put<DOWN>(v, yo, ro, k, gm, gc, z);
     }
 }
 
-// One level of the ULV solve for few right-hand sides on large nodes, in two launches:
-// k_ulv_narrow computes partial products over S slices of the inner dimension, one wave
-// per 64 output rows and slice, lanes on rows, so W (UP) or W^* (DOWN, the stored copy WH)
-// streams coalesced from HBM once; 64-entry pieces of the input vector are staged in LDS
-// and read back as broadcasts.  k_ulv_narrow_sum adds the S partials in a fixed order and
-// scatters the rows like k_ulv_level.  Partial (s, level row, column) at
-// P[(s * rows + row) * 8 + column] for one chunk of 8 columns.
-constexpr int kNarrowCols = 8;
-
-template <bool DOWN>
-__global__ void __launch_bounds__(64) k_ulv_narrow(LevelArgs a, const double2 *__restrict__ WH,
-                                                   const double2 *__restrict__ Yin, long ldin,
-                                                   const double2 *__restrict__ Bh, long ldb,
-                                                   const double2 *__restrict__ Ylo, long ldlo, int nrhs, int c0,
-                                                   int S, long rows, double2 *__restrict__ P) {
-    __shared__ double2 xs[64][kNarrowCols];
-    const int node = blockIdx.y, sl = blockIdx.z;
+// Nodes of at most 64 rows (the leaves): a workgroup takes a node for 8 CW columns, staged in LDS (a column of
+// a node is contiguous, and the vectors' columns are far apart) and written back through it; a wave forms 4 / RG
+// row tiles of 8 columns, W straight from memory.  Inner indices in order, whatever the split.
+// The stream of W bounds it: 4096 leaves of N = 2^18, 8 columns, 268 MB in 61 (down) and 69 us (up); 1024 of
+// N = 2^16, 16 columns: 48 -> 23 us a direction (tiles of 64 x 64 on the vector units before).
+template <bool DOWN, int CW, int RG>
+__global__ void __launch_bounds__(64 * CW * RG) k_ulv_leaf(LevelArgs a, LevelVecs v, int cgroups, unsigned nwork) {
+    using M = Mat4<double>;
+    using V = M::V;
+    constexpr int NR = 4 / RG, NW = CW * RG, LD = 65, NCOL = 8 * CW, D = 2;
+    __shared__ double2 xs[NCOL * LD];
+    const int lane = threadIdx.x & 63, lr = lane & 15, lk = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const unsigned work = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    if (work >= nwork) return;
+    const int node = work / cgroups, c0 = (work - node * cgroups) * NCOL;
     const int m = a.m[node], k = a.k[node];
-    const int r0 = blockIdx.x * 64;
-    if (r0 >= m) return;
-    const int r = r0 + threadIdx.x;
-    const int nc = nrhs - c0 < kNarrowCols ? nrhs - c0 : kNarrowCols;
-    const double2 *Wn = (DOWN ? WH : a.W) + a.woff[node];
+    if (m == 0) return;
     const long yo = a.yoff[node], ro = a.roff[node];
-    const int len = (m + S - 1) / S;
-    const int l0 = sl * len, l1 = l0 + len < m ? l0 + len : m;
-    double2 acc[kNarrowCols];
+    const double2 *W = a.W + a.woff[node];
+    const int r0 = wave / CW * 16 * NR, xc = wave % CW * 8;
+    const int ns = (m + 7) >> 3;
+    int row[NR];
 #pragma unroll
-    for (int c = 0; c < kNarrowCols; ++c) acc[c] = zc(0.0, 0.0);
-    for (int lb = l0; lb < l1; lb += 64) {
-        const int nl = l1 - lb < 64 ? l1 - lb : 64;
-        __syncthreads();
-        {
-            const int l = lb + threadIdx.x;
-            for (int c = 0; c < kNarrowCols; ++c) {
-                double2 v = zc(0.0, 0.0);
-                if ((int)threadIdx.x < nl && c < nc) {
-                    if (DOWN)
-                        v = l < k ? Bh[(yo + l) + (size_t)(c0 + c) * ldb] : Ylo[(ro + l - k) + (size_t)(c0 + c) * ldlo];
-                    else
-                        v = Yin[(yo + l) + (size_t)(c0 + c) * ldin];
+    for (int t = 0; t < NR; ++t) {
+        const int r = r0 + 16 * t + lr;
+        row[t] = r < m ? r : m - 1;
+    }
+    // a step takes 8 inner indices, two per lane, so that W^* uses a whole cache line at once
+    double2 fa[D][2][NR];
+    auto load = [&](int d, int s) {
+#pragma unroll
+        for (int t = 0; t < NR; ++t)
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int l = 8 * s + 2 * lk + u, lc = l < m ? l : m - 1;
+                fa[d][u][t] = DOWN ? W[lc + row[t] * m] : W[row[t] + lc * m];
+            }
+    };
+#pragma unroll
+    for (int d = 0; d < D; ++d)
+        if (d < ns) load(d, d);
+#pragma unroll
+    for (int j = 0; j < NCOL / NW; ++j) {
+        const int l = lane, c = wave + NW * j, gc = c0 + c < v.nrhs ? c0 + c : v.nrhs - 1, lc = l < m ? l : m - 1;
+        const double2 *p = DOWN ? (lc < k ? v.Bh + (yo + lc) + (size_t)gc * v.ldb : v.Ylo + (ro + lc - k) + (size_t)gc * v.ldlo)
+                                : v.Yin + (yo + lc) + (size_t)gc * v.ldy;
+        const double2 x = *p;
+        xs[c * LD + l] = l < m ? x : zc(0.0, 0.0);
+    }
+    __syncthreads();
+    V P[NR], Q[NR];
+#pragma unroll
+    for (int t = 0; t < NR; ++t) P[t] = Q[t] = V{0, 0, 0, 0};
+    const double *xb = reinterpret_cast<const double *>(xs + (xc + (lr & 7)) * LD + 2 * lk) + (lr >> 3);
+    auto mac = [&](int d, int s) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const double x = xb[16 * s + 2 * u];
+#pragma unroll
+            for (int t = 0; t < NR; ++t) {
+                P[t] = M::mac(fa[d][u][t].x, x, P[t]);
+                Q[t] = M::mac(fa[d][u][t].y, x, Q[t]);
+            }
+        }
+    };
+    if (r0 < m) {
+        int s = 0;
+        for (; s + D <= ns; s += D) {
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                mac(d, s + d);
+                if (s + d + D < ns) load(d, s + d + D);
+            }
+        }
+#pragma unroll
+        for (int d = 0; d < D; ++d)
+            if (s + d < ns) mac(d, s + d);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < NR; ++t)
+        ulv_tile<DOWN>(P[t], Q[t], lane, [&](int r, double2 z) { xs[(xc + (lr & 7)) * LD + r0 + 16 * t + r] = z; });
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < NCOL / NW; ++j) {
+        const int c = wave + NW * j;
+        if (lane < m && c0 + c < v.nrhs) ulv_put<DOWN>(v, yo, ro, k, lane, c0 + c, xs[c * LD + lane]);
+    }
+}
+
+// The same for more than 16 columns, 32 per workgroup: W goes through LDS in two halves of 32 inner indices, which
+// the 8 waves (4 column groups, 2 pairs of row tiles) share.  Lanes of a matrix tile run along the rows of
+// its operand first, so W^* from memory costs four times the cache accesses of W (4096 leaves, 64 columns:
+// up 236, down 304 us with k_ulv_leaf's loads; 228 and 255 here, where the matrix rate allows 115 and the
+// 0.8 GB moved 160).
+template <bool DOWN>
+__global__ void __launch_bounds__(512) k_ulv_leaf32(LevelArgs a, LevelVecs v, int cgroups, unsigned nwork) {
+    using M = Mat4<double>;
+    using V = M::V;
+    constexpr int NR = 2, LD = 65, LW = 33;
+    __shared__ double2 xs[32 * LD], ws[64 * LW];               // [column][row], [result row][inner index]
+    const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lk = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const unsigned work = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    if (work >= nwork) return;
+    const int node = work / cgroups, c0 = (work - node * cgroups) * 32;
+    const int m = a.m[node], k = a.k[node];
+    if (m == 0) return;
+    const long yo = a.yoff[node], ro = a.roff[node];
+    const double2 *W = a.W + a.woff[node];
+    const int r0 = (wave >> 2) * 16 * NR, xc = (wave & 3) * 8;
+    const int ns = (m + 7) >> 3;
+    // entry j of the thread in a half of W, consecutive lanes along a column, and its place
+    auto wat = [&](int half, int j) {
+        const int i = DOWN ? (tid >> 5) + 16 * j : lane, l = 32 * half + (DOWN ? tid & 31 : (tid >> 6) + 8 * j);
+        const int ic = i < m ? i : m - 1, lc = l < m ? l : m - 1;
+        return W[DOWN ? lc + ic * m : ic + lc * m];
+    };
+    auto wput = [&](int j, double2 w) {
+        ws[DOWN ? ((tid >> 5) + 16 * j) * LW + (tid & 31) : lane * LW + (tid >> 6) + 8 * j] = w;
+    };
+    auto xat = [&](int j) {
+        const int c = wave + 8 * j, gc = c0 + c < v.nrhs ? c0 + c : v.nrhs - 1, lc = lane < m ? lane : m - 1;
+        return *(DOWN ? (lc < k ? v.Bh + (yo + lc) + (size_t)gc * v.ldb : v.Ylo + (ro + lc - k) + (size_t)gc * v.ldlo)
+                      : v.Yin + (yo + lc) + (size_t)gc * v.ldy);
+    };
+    auto xput = [&](int j, double2 x) { xs[(wave + 8 * j) * LD + lane] = lane < m ? x : zc(0.0, 0.0); };
+    double2 w0 = wat(0, 0), w1 = wat(0, 1), w2 = wat(0, 2), w3 = wat(0, 3);
+    {
+        const double2 x0 = xat(0), x1 = xat(1), x2 = xat(2), x3 = xat(3);
+        wput(0, w0);
+        wput(1, w1);
+        wput(2, w2);
+        wput(3, w3);
+        xput(0, x0);
+        xput(1, x1);
+        xput(2, x2);
+        xput(3, x3);
+    }
+    __syncthreads();
+    V P[NR], Q[NR];
+#pragma unroll
+    for (int t = 0; t < NR; ++t) P[t] = Q[t] = V{0, 0, 0, 0};
+    const double *xb = reinterpret_cast<const double *>(xs + (xc + (lr & 7)) * LD + 2 * lk) + (lr >> 3);
+    const double2 *wb = ws + (r0 + lr) * LW + 2 * lk;
+    auto half = [&](int h) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if (4 * h + q >= ns) break;
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const double x = xb[16 * (4 * h + q) + 2 * u];
+#pragma unroll
+                for (int t = 0; t < NR; ++t) {
+                    const double2 w = wb[16 * t * LW + 8 * q + u];
+                    P[t] = M::mac(w.x, x, P[t]);
+                    Q[t] = M::mac(w.y, x, Q[t]);
                 }
-                xs[threadIdx.x][c] = v;
             }
+        }
+    };
+    // the second half is on its way while the first is used
+    w0 = wat(1, 0);
+    w1 = wat(1, 1);
+    w2 = wat(1, 2);
+    w3 = wat(1, 3);
+    half(0);
+    __syncthreads();
+    if (m > 32) {
+        wput(0, w0);
+        wput(1, w1);
+        wput(2, w2);
+        wput(3, w3);
+        __syncthreads();
+        half(1);
+        __syncthreads();
+    }
+#pragma unroll
+    for (int t = 0; t < NR; ++t)
+        ulv_tile<DOWN>(P[t], Q[t], lane, [&](int r, double2 z) { xs[(xc + (lr & 7)) * LD + r0 + 16 * t + r] = z; });
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int c = wave + 8 * j;
+        if (lane < m && c0 + c < v.nrhs) ulv_put<DOWN>(v, yo, ro, k, lane, c0 + c, xs[c * LD + lane]);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Bands: consecutive levels whose nodes have at most kBandRows rows (the upper levels of 1D trees, 8 rows
+// at rank 4) in one launch.  A workgroup takes the subtree below one node of the band's top level (or,
+// at the top of the tree, all its nodes and the root: up, root and down in one launch) for 8 columns.
+// Its W, vectors and tables are read into LDS at once; the levels then run one barrier apart.  A launch
+// per level is 4.7 us whatever it does: N = 2^14, 5 columns, the 7 upper levels and the root took
+// 75 us of a solve, 33 us in 3 launches.
+constexpr int kBandRows = 8, kBandLevels = 4, kBandNodes = 30, kBandRoot = 2 * kBandRows;
+
+struct BandArgs {
+    LevelArgs lv[kBandLevels];   // levels la .. la + nlev - 1
+    int nlev;
+    const double2 *Yin;          // vectors of the lowest level (UP)
+    double2 *Yout;               // vectors of the lowest level (DOWN)
+    long ldin, ldout;
+    double2 *Bh[kBandLevels];
+    long ldb[kBandLevels];
+    double2 *Ylo;                // vectors of the level above (not TOP)
+    long ldlo;
+    const double2 *Linv;         // TOP
+    int m0, nrhs, accum;
+};
+
+enum BandMode { BAND_UP, BAND_DOWN, BAND_TOP };
+
+template <int MODE> __global__ void __launch_bounds__(256) k_ulv_band(BandArgs a) {
+    constexpr int NN = MODE == BAND_TOP ? kBandNodes : kBandNodes / 2;
+    __shared__ double2 Ws[NN][64];                             // column-major 8 x 8
+    __shared__ double2 ys[NN][64];                             // [row][column]
+    __shared__ double2 bs[MODE == BAND_UP ? 1 : NN][64];
+    __shared__ double2 rs[kBandRoot][8], rt[MODE == BAND_TOP ? kBandRoot : 1][8];
+    __shared__ double2 Ls[MODE == BAND_TOP ? kBandRoot * kBandRoot : 1];
+    __shared__ int sm[NN], sk[NN], so[NN], slev[NN];           // rows, eliminated rows, row of the rest in the parent
+    __shared__ long syo[NN];
+    __shared__ size_t swo[NN];
+    __shared__ long sro;
+    const int tid = threadIdx.x, c0 = blockIdx.y * 8, top = MODE == BAND_TOP ? 2 : 1;
+    const int nodes = top * ((1 << a.nlev) - 1);
+    if (tid < nodes) {
+        // node tid: level i, the j-th of the subtree there
+        int i = 0;
+        while (tid >= top * ((2 << i) - 1)) ++i;
+        const int j = tid - top * ((1 << i) - 1), g = MODE == BAND_TOP ? j : ((int)blockIdx.x << i) + j;
+        const LevelArgs &L = a.lv[i];
+        slev[tid] = i;
+        sm[tid] = L.m[g];
+        sk[tid] = L.k[g];
+        swo[tid] = L.woff[g];
+        syo[tid] = L.yoff[g];
+        // within the parent's rows: the first child's start there, the second's follow the first's
+        so[tid] = i > 0 || MODE == BAND_TOP ? ((g & 1) ? L.m[g - 1] - L.k[g - 1] : 0) : 0;
+        if (MODE != BAND_TOP && i == 0) sro = L.roff[g];
+    }
+    __syncthreads();
+    const int low = top * ((1 << (a.nlev - 1)) - 1);          // first node of the lowest level
+#pragma unroll 4
+    for (int e = tid; e < nodes * 64; e += 256) {
+        // entries outside the node read its first one (the load has no condition of its own)
+        const int n = e >> 6, r = e & 7, q = (e >> 3) & 7, m = sm[n];
+        const bool in = r < m && q < m;
+        const double2 w = a.lv[0].W[in ? swo[n] + r + (size_t)q * m : 0];
+        Ws[n][e & 63] = in ? w : zc(0.0, 0.0);
+    }
+    for (int e = (MODE != BAND_DOWN ? low : 0) * 64 + tid; e < nodes * 64; e += 256) {
+        const int n = e >> 6, r = e & 7, q = (e >> 3) & 7, m = sm[n];
+        // vectors: rows on neighbouring lanes
+        const int c = c0 + q;
+        if (MODE != BAND_DOWN && n >= low) {
+            double2 y = zc(0.0, 0.0);
+            if (r < m && c < a.nrhs) y = a.Yin[syo[n] + r + (size_t)c * a.ldin];
+            ys[n][r * 8 + q] = y;
+        }
+        if (MODE == BAND_DOWN) {
+            double2 b = zc(0.0, 0.0);
+            if (r < sk[n] && c < a.nrhs) b = a.Bh[slev[n]][syo[n] + r + (size_t)c * a.ldb[slev[n]]];
+            bs[n][r * 8 + q] = b;
+        }
+    }
+    if (MODE == BAND_DOWN) {
+        if (tid < 64) {
+            const int r = tid & 7, q = tid >> 3;
+            double2 y = zc(0.0, 0.0);
+            if (r < sm[0] - sk[0] && c0 + q < a.nrhs) y = a.Ylo[sro + r + (size_t)(c0 + q) * a.ldlo];
+            rs[r][q] = y;
+        }
+    }
+    if (MODE == BAND_TOP)
+        for (int e = tid; e < a.m0 * a.m0; e += 256) Ls[e] = a.Linv[e];
+    __syncthreads();
+    if (MODE != BAND_DOWN) {
+        for (int i = a.nlev - 1; i >= 0; --i) {
+            const int first = top * ((1 << i) - 1), cnt = top << i;
+            for (int e = tid; e < cnt * 64; e += 256) {
+                const int j = e >> 6, n = first + j, r = (e >> 3) & 7, q = e & 7, m = sm[n], k = sk[n];
+                if (r >= m) continue;
+                double2 z = zc(0.0, 0.0);
+#pragma unroll
+                for (int l = 0; l < 8; ++l) {
+                    // W is zero from column m on, the rows there may hold anything
+                    const double2 y = ys[n][l * 8 + q];
+                    cfma(z, Ws[n][l * 8 + r], zc(l < m ? y.x : 0.0, l < m ? y.y : 0.0));
+                }
+                if (r < k) {
+                    if (MODE == BAND_TOP)
+                        bs[n][r * 8 + q] = z;
+                    else if (c0 + q < a.nrhs)
+                        a.Bh[i][syo[n] + r + (size_t)(c0 + q) * a.ldb[i]] = z;
+                } else if (i > 0) {
+                    ys[top * ((1 << (i - 1)) - 1) + (j >> 1)][(so[n] + r - k) * 8 + q] = z;
+                } else if (MODE == BAND_TOP) {
+                    rs[so[n] + r - k][q] = z;
+                } else if (c0 + q < a.nrhs) {
+                    a.Ylo[sro + r - k + (size_t)(c0 + q) * a.ldlo] = z;
+                }
+            }
+            __syncthreads();
+        }
+    }
+    if (MODE == BAND_UP) return;
+    if (MODE == BAND_TOP) {
+        // Y0 <- Linv^* Linv Y0
+        const int r = tid >> 3, q = tid & 7, m = a.m0;
+        double2 z = zc(0.0, 0.0);
+        if (r < m)
+            for (int l = 0; l < m; ++l) cfma(z, Ls[r + l * m], rs[l][q]);
+        if (r < m) rt[r][q] = z;
+        __syncthreads();
+        z = zc(0.0, 0.0);
+        if (r < m)
+            for (int l = 0; l < m; ++l) cfmac(z, Ls[l + r * m], rt[l][q]);
+        if (r < m) rs[r][q] = z;
+        __syncthreads();
+    }
+    for (int i = 0; i < a.nlev; ++i) {
+        const int first = top * ((1 << i) - 1), cnt = top << i;
+        for (int e = tid; e < cnt * 64; e += 256) {
+            const int j = e >> 6, n = first + j, r = (e >> 3) & 7, q = e & 7, m = sm[n], k = sk[n];
+            if (r >= m) continue;
+            const double2 *up = i > 0 ? &ys[top * ((1 << (i - 1)) - 1) + (j >> 1)][so[n] * 8 + q] : &rs[so[n]][q];
+            const double2 *bn = &bs[n][q];
+            double2 z = zc(0.0, 0.0);
+#pragma unroll
+            for (int l = 0; l < 8; ++l) {
+                const double2 y = l >= k && l < m ? up[(l - k) * 8] : bn[l * 8];
+                cfmac(z, Ws[n][r * 8 + l], zc(l < m ? y.x : 0.0, l < m ? y.y : 0.0));
+            }
+            ys[n][r * 8 + q] = z;
         }
         __syncthreads();
-        if (r < m) {
-            for (int j = 0; j < nl; ++j) {
-                const double2 w = Wn[r + (size_t)(lb + j) * m];
-#pragma unroll
-                for (int c = 0; c < kNarrowCols; ++c) cfma(acc[c], w, xs[j][c]);
-            }
+    }
+    for (int e = tid; e < (nodes - low) * 64; e += 256) {
+        const int n = low + (e >> 6), r = e & 7, q = (e >> 3) & 7;
+        if (r < sm[n] && c0 + q < a.nrhs) {
+            double2 *p = a.Yout + syo[n] + r + (size_t)(c0 + q) * a.ldout;
+            const double2 y = ys[n][r * 8 + q];
+            *p = a.accum ? cadd(*p, y) : y;
         }
     }
-    if (r < m) {
-        double2 *pp = P + ((size_t)sl * rows + yo + r) * kNarrowCols;
-#pragma unroll
-        for (int c = 0; c < kNarrowCols; ++c) pp[c] = acc[c];
-    }
-}
-
-template <bool DOWN>
-__global__ void k_ulv_narrow_sum(LevelArgs a, const double2 *__restrict__ P, int S, long rows, int nrhs, int c0,
-                                 double2 *__restrict__ Bh, long ldb, double2 *__restrict__ Ylo, long ldlo,
-                                 double2 *__restrict__ Yout, long ldout, int accum) {
-    const int node = blockIdx.y;
-    const int m = a.m[node], k = a.k[node];
-    const long yo = a.yoff[node], ro = a.roff[node];
-    const int nc = nrhs - c0 < kNarrowCols ? nrhs - c0 : kNarrowCols;
-    for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < m * kNarrowCols; e += gridDim.x * blockDim.x) {
-        const int r = e / kNarrowCols, c = e % kNarrowCols;
-        if (c >= nc) continue;
-        double2 v = zc(0.0, 0.0);
-        for (int q = 0; q < S; ++q) v = cadd(v, P[((size_t)q * rows + yo + r) * kNarrowCols + c]);
-        if (DOWN)
-            ulv_store(Yout + (yo + r) + (size_t)(c0 + c) * ldout, v, accum);
-        else if (r < k)
-            Bh[(yo + r) + (size_t)(c0 + c) * ldb] = v;
-        else
-            Ylo[(ro + r - k) + (size_t)(c0 + c) * ldlo] = v;
-    }
-}
-
-// WH = W^* for every node of a level
-__global__ void k_ulv_wh(const double2 *W, double2 *WH, const size_t *woff, const int *msz) {
-    const int node = blockIdx.y, m = msz[node];
-    const double2 *Wn = W + woff[node];
-    double2 *Hn = WH + woff[node];
-    for (long e = blockIdx.x * (long)blockDim.x + threadIdx.x; e < (long)m * m; e += (long)gridDim.x * blockDim.x) {
-        const int i = (int)(e % m), j = (int)(e / m);
-        const double2 v = Wn[j + (size_t)i * m];
-        Hn[e] = zc(v.x, -v.y);
-    }
-}
-
-// levels whose largest node has at least this many rows use k_ulv_narrow for <= 16 columns
-constexpr int kNarrowMinRows = 128, kNarrowMaxCols = 16;
-
-// inner-dimension slices of a level: about 2048 waves in flight, at least 64 entries per slice,
-// and at most 4 N partial rows
-static int narrow_slices(long rows, int mmax) {
-    const long waves = (rows + 63) / 64;
-    long S = (2048 + waves - 1) / waves;
-    if (S > mmax / 64) S = mmax / 64;
-    if (S > 32) S = 32;
-    return S < 1 ? 1 : (int)S;
-}
-
-static size_t narrow_part_rows(const hss_ulv_s *f) {
-    size_t mx = 0;
-    for (int l = 1; l <= f->Lh; ++l) {
-        int mm = 0;
-        for (int v : f->m[l]) mm = v > mm ? v : mm;
-        const size_t need = (size_t)narrow_slices(f->rows[l], mm) * f->rows[l];
-        mx = need > mx ? need : mx;
-    }
-    return mx;
 }
 
 template <typename T> static size_t put(std::vector<char> &blob, const std::vector<T> &v) {
@@ -1138,6 +1286,11 @@ static fio_status factor_impl(hss_s *h, hipStream_t s, hss_ulv_t *out) {
         f->meta_k.assign(Lh + 1, 0);
         f->meta_yoff.assign(Lh + 1, 0);
         f->meta_roff.assign(Lh + 1, 0);
+        // level 0: the root as one node of Linv without eliminated rows
+        f->meta_woff[0] = put(blob, std::vector<size_t>{0});
+        f->meta_m[0] = put(blob, std::vector<int>{f->m0});
+        f->meta_k[0] = put(blob, std::vector<int>{0});
+        f->meta_yoff[0] = f->meta_roff[0] = put(blob, std::vector<long>{0});
         for (int l = 1; l <= Lh; ++l) {
             f->meta_woff[l] = put(blob, f->woff[l]);
             f->meta_m[l] = put(blob, f->m[l]);
@@ -1147,24 +1300,6 @@ static fio_status factor_impl(hss_s *h, hipStream_t s, hss_ulv_t *out) {
         }
         f->meta.alloc(blob.size() + 16);
         FIO_HIP(hipMemcpy(f->meta.p, blob.data(), blob.size(), hipMemcpyHostToDevice));
-        // W^* copies for the levels that the narrow solve kernel serves
-        bool any = false;
-        for (int l = 1; l <= Lh; ++l)
-            for (int v : f->m[l]) any = any || v >= kNarrowMinRows;
-        if (any) {
-            f->WH.alloc(wtot * sizeof(double2) + 16);
-            const char *mb = f->meta.as<char>();
-            for (int l = 1; l <= Lh; ++l) {
-                int ml = 0;
-                for (int v : f->m[l]) ml = v > ml ? v : ml;
-                if (ml < kNarrowMinRows) continue;
-                k_ulv_wh<<<dim3(64, (unsigned)f->m[l].size()), 256, 0, s>>>(
-                    f->W.as<double2>(), f->WH.as<double2>(), (const size_t *)(mb + f->meta_woff[l]),
-                    (const int *)(mb + f->meta_m[l]));
-            }
-            FIO_HIP(hipGetLastError());
-            FIO_HIP(hipStreamSynchronize(s));
-        }
         return FIO_OK;
     });
     if (st != FIO_OK) {
@@ -1181,9 +1316,32 @@ static size_t ulv_ws_bytes(const hss_ulv_s *f, int nrhs) {
     for (int l = 0; l < f->Lh; ++l) rows += f->rows[l];
     for (int l = 1; l <= f->Lh; ++l) rows += f->rows[l];
     rows += f->m0;
-    size_t part = 0;
-    if (f->WH.p && nrhs <= kNarrowMaxCols) part = narrow_part_rows(f) * kNarrowCols;   // entries
-    return (rows + 8 * (size_t)(f->Lh + 2)) * (size_t)nrhs * sizeof(double2) + part * sizeof(double2) + 8192;
+    return (rows + 8 * (size_t)(f->Lh + 2)) * (size_t)nrhs * sizeof(double2) + 8192;
+}
+
+// One level of nn nodes of at most mmax rows.  Both kernels sum a column in an order that depends on the level
+// alone; the rows and columns of a workgroup only split the work: the wider tile that still gives 2
+// workgroups per CU, and no more columns than there are.
+template <bool DOWN> static void ulv_level(const LevelArgs &a, const LevelVecs &v, int nn, int mmax, hipStream_t s) {
+    auto wgs = [](long n) {
+        if (n > (1L << 31)) throw Err{FIO_ERR_UNSUPPORTED};
+        return dim3((unsigned)((n + 7) / 8 * 8));
+    };
+    const int rt = (mmax + 15) / 16, c8 = (v.nrhs + 7) / 8, c16 = (v.nrhs + 15) / 16, c32 = (v.nrhs + 31) / 32;
+    if (mmax > 64) {
+        const int r2 = (rt + 1) / 2;
+        const long n2 = (long)nn * c8 * r2, n1 = (long)nn * c8 * rt;
+        if (n2 >= 512)
+            k_ulv_mm<DOWN, 2><<<wgs(n2), 512, 0, s>>>(a, v, r2, c8, (unsigned)n2);
+        else
+            k_ulv_mm<DOWN, 1><<<wgs(n1), 512, 0, s>>>(a, v, rt, c8, (unsigned)n1);
+    } else if (v.nrhs > 16 && (long)nn * c32 >= 512) {
+        k_ulv_leaf32<DOWN><<<wgs((long)nn * c32), 512, 0, s>>>(a, v, c32, (unsigned)(nn * c32));
+    } else if (v.nrhs > 8 && (long)nn * c16 >= 512) {
+        k_ulv_leaf<DOWN, 2, 2><<<wgs((long)nn * c16), 256, 0, s>>>(a, v, c16, (unsigned)(nn * c16));
+    } else {
+        k_ulv_leaf<DOWN, 1, 4><<<wgs((long)nn * c8), 256, 0, s>>>(a, v, c8, (unsigned)(nn * c8));
+    }
 }
 
 // C = G~^{-1} Y, or C += G~^{-1} Y with accumulate (the last level adds to C)
@@ -1213,83 +1371,95 @@ void ulv_solve_impl(hss_ulv_s *f, const double2 *Y, long ldy, double2 *C, long l
         a.roff = (const long *)(mb + f->meta_roff[l]);
         return a;
     };
-    const int tilesN = (nrhs + 31) / 32;
     auto mmax = [&](int l) {
         int v = 0;
         for (int x : f->m[l]) v = x > v ? x : v;
         return v;
     };
-    // few right-hand sides on large nodes: rows on lanes, W streamed once per 8 columns
-    // (k_ulv_narrow), over S slices of the inner dimension so that about 2048 waves stream
-    auto narrow = [&](int l) { return nrhs <= kNarrowMaxCols && f->WH.p && mmax(l) >= kNarrowMinRows; };
-    auto slices = [&](int l) { return narrow_slices(f->rows[l], mmax(l)); };
-    double2 *part = nullptr;
-    if (f->WH.p && nrhs <= kNarrowMaxCols) {
-        part = base + off;
-        off += narrow_part_rows(f) * kNarrowCols;
-    }
-    // bottom-up
-    for (int l = Lh; l >= 1; --l) {
-        const int tilesM = (mmax(l) + 31) / 32;
-        if (tilesM == 0) continue;
-        const double2 *yin = (l == Lh) ? Y : Yl[l];
-        long ldin = (l == Lh) ? ldy : f->rows[l];
-        FIO_TIMED("ulv_up", s);
-        if (narrow(l)) {
-            const int S = slices(l);
-            for (int c0 = 0; c0 < nrhs; c0 += kNarrowCols) {
-                dim3 g((unsigned)((mmax(l) + 63) / 64), (unsigned)f->m[l].size(), (unsigned)S);
-                k_ulv_narrow<false><<<g, 64, 0, s>>>(args(l), nullptr, yin, ldin, nullptr, 0, nullptr, 0, nrhs, c0,
-                                                     S, f->rows[l], part);
-                dim3 g2((unsigned)((mmax(l) * kNarrowCols + 255) / 256), (unsigned)f->m[l].size());
-                k_ulv_narrow_sum<false><<<g2, 256, 0, s>>>(args(l), part, S, f->rows[l], nrhs, c0, Bl[l], f->rows[l],
-                                                           Yl[l - 1], f->rows[l - 1], nullptr, 0, 0);
-            }
-        } else if (mmax(l) > 32 && mmax(l) <= 64) {
-            dim3 grid((unsigned)((nrhs + 63) / 64), f->m[l].size());
-            k_ulv_level64<false><<<grid, 256, 0, s>>>(args(l), yin, ldin, Bl[l], f->rows[l], Yl[l - 1],
-                                                      f->rows[l - 1], nullptr, 0, nrhs, 0);
-        } else {
-            dim3 grid(tilesM * tilesN, f->m[l].size());
-            k_ulv_level<false><<<grid, 256, 0, s>>>(args(l), yin, ldin, Bl[l], f->rows[l], Yl[l - 1], f->rows[l - 1],
-                                                    nullptr, 0, nrhs, tilesN, 0);
+    auto vecs = [&](int l) {
+        LevelVecs v;
+        v.Yin = l == Lh ? Y : Yl[l];
+        v.Yout = l == Lh ? C : Yl[l];
+        v.Bh = Bl[l];
+        v.Ylo = Yl[l - 1];
+        v.ldy = f->rows[l];
+        v.ldb = f->rows[l];
+        v.ldlo = f->rows[l - 1];
+        v.nrhs = nrhs;
+        v.accum = l == Lh && accumulate ? 1 : 0;
+        return v;
+    };
+    // levels 1 .. lt run in bands, the first of them with the root
+    int lt = 0;
+    while (lt < Lh && mmax(lt + 1) <= kBandRows) ++lt;
+    std::vector<std::pair<int, int>> bands;      // (top level, levels)
+    if (lt > 0) {
+        const int nt = lt < kBandLevels ? lt : kBandLevels;
+        bands.push_back({1, nt});
+        const int rest = lt - nt, nb = (rest + kBandLevels - 1) / kBandLevels;
+        for (int b = 0, l = nt + 1; b < nb; ++b) {
+            const int n = rest / nb + (b < rest % nb ? 1 : 0);
+            bands.push_back({l, n});
+            l += n;
         }
+    }
+    auto band = [&](size_t b) {
+        const int la = bands[b].first, n = bands[b].second, ll = la + n - 1;
+        BandArgs a{};
+        a.nlev = n;
+        for (int i = 0; i < n; ++i) {
+            a.lv[i] = args(la + i);
+            a.Bh[i] = Bl[la + i];
+            a.ldb[i] = f->rows[la + i];
+        }
+        a.Yin = ll == Lh ? Y : Yl[ll];
+        a.Yout = ll == Lh ? C : Yl[ll];
+        a.ldin = ll == Lh ? ldy : f->rows[ll];
+        a.ldout = ll == Lh ? ldc : f->rows[ll];
+        a.Ylo = Yl[la - 1];
+        a.ldlo = f->rows[la - 1];
+        a.Linv = f->Linv.as<double2>();
+        a.m0 = f->m0;
+        a.nrhs = nrhs;
+        a.accum = ll == Lh && accumulate ? 1 : 0;
+        return a;
+    };
+    const unsigned cg = (unsigned)((nrhs + 7) / 8);
+    // bottom-up
+    for (int l = Lh; l > lt; --l) {
+        if (mmax(l) == 0) continue;
+        FIO_TIMED("ulv_up", s);
+        LevelVecs v = vecs(l);
+        if (l == Lh) v.ldy = ldy;
+        ulv_level<false>(args(l), v, (int)f->m[l].size(), mmax(l), s);
+    }
+    for (size_t b = bands.size(); b-- > 1;) {
+        FIO_TIMED("ulv_up", s);
+        k_ulv_band<BAND_UP><<<dim3(1u << bands[b].first, cg), 256, 0, s>>>(band(b));
     }
     // root: Y0 <- Linv^* Linv Y0
-    if (f->m0 > 0) {
-        ZgemmDesc d0{f->Linv.as<double2>(), Yl[0], rt, f->m0, nrhs, f->m0, f->m0, f->m0, f->m0};
-        ZgemmDesc d1{f->Linv.as<double2>(), rt, Yl[0], f->m0, nrhs, f->m0, f->m0, f->m0, f->m0};
+    if (lt > 0) {
         FIO_TIMED("ulv_root", s);
-        zgemm_one(d0, false, zc(1.0), zc(0.0), s);
-        zgemm_one(d1, true, zc(1.0), zc(0.0), s);
+        k_ulv_band<BAND_TOP><<<dim3(1, cg), 256, 0, s>>>(band(0));
+    } else if (f->m0 > 0) {
+        FIO_TIMED("ulv_root", s);
+        LevelArgs a = args(0);
+        a.W = f->Linv.as<double2>();
+        LevelVecs v{Yl[0], Yl[0], nullptr, rt, f->m0, 0, f->m0, nrhs, 0};
+        ulv_level<false>(a, v, 1, f->m0, s);
+        ulv_level<true>(a, v, 1, f->m0, s);
     }
     // top-down
-    for (int l = 1; l <= Lh; ++l) {
-        const int tilesM = (mmax(l) + 31) / 32;
-        if (tilesM == 0) continue;
-        double2 *yout = (l == Lh) ? C : Yl[l];
-        long ldout = (l == Lh) ? ldc : f->rows[l];
-        const int acc_l = (l == Lh && accumulate) ? 1 : 0;
+    for (size_t b = 1; b < bands.size(); ++b) {
         FIO_TIMED("ulv_down", s);
-        if (narrow(l)) {
-            const int S = slices(l);
-            for (int c0 = 0; c0 < nrhs; c0 += kNarrowCols) {
-                dim3 g((unsigned)((mmax(l) + 63) / 64), (unsigned)f->m[l].size(), (unsigned)S);
-                k_ulv_narrow<true><<<g, 64, 0, s>>>(args(l), f->WH.as<double2>(), nullptr, 0, Bl[l], f->rows[l],
-                                                    Yl[l - 1], f->rows[l - 1], nrhs, c0, S, f->rows[l], part);
-                dim3 g2((unsigned)((mmax(l) * kNarrowCols + 255) / 256), (unsigned)f->m[l].size());
-                k_ulv_narrow_sum<true><<<g2, 256, 0, s>>>(args(l), part, S, f->rows[l], nrhs, c0, nullptr, 0,
-                                                          nullptr, 0, yout, ldout, acc_l);
-            }
-        } else if (mmax(l) > 32 && mmax(l) <= 64) {
-            dim3 grid((unsigned)((nrhs + 63) / 64), f->m[l].size());
-            k_ulv_level64<true><<<grid, 256, 0, s>>>(args(l), nullptr, 0, Bl[l], f->rows[l], Yl[l - 1],
-                                                     f->rows[l - 1], yout, ldout, nrhs, acc_l);
-        } else {
-            dim3 grid(tilesM * tilesN, f->m[l].size());
-            k_ulv_level<true><<<grid, 256, 0, s>>>(args(l), nullptr, 0, Bl[l], f->rows[l], Yl[l - 1], f->rows[l - 1],
-                                                   yout, ldout, nrhs, tilesN, acc_l);
-        }
+        k_ulv_band<BAND_DOWN><<<dim3(1u << bands[b].first, cg), 256, 0, s>>>(band(b));
+    }
+    for (int l = lt + 1; l <= Lh; ++l) {
+        if (mmax(l) == 0) continue;
+        FIO_TIMED("ulv_down", s);
+        LevelVecs v = vecs(l);
+        if (l == Lh) v.ldy = ldc;
+        ulv_level<true>(args(l), v, (int)f->m[l].size(), mmax(l), s);
     }
     FIO_HIP(hipGetLastError());
 }
