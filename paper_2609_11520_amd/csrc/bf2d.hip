@@ -305,8 +305,10 @@ __device__ __forceinline__ double2 to_z(float2 v) { return zc(v.x, v.y); }
 // nothing.  The blocks of one output and the coefficients they act on are consecutive in memory, so the
 // product runs over all their columns as one inner dimension, 4 at a time; entries go straight from
 // memory to registers, D steps ahead, at a wave-uniform address plus a lane offset that does not change.
+// The bound on waves per SIMD keeps the accumulators in the same 96 registers as the rest for 3 row tiles (5
+// waves; 4 without it: n = 64, 70 columns 1040 -> 1002 us).
 template <typename T, int NR, int NC, bool VEC, int D>
-__global__ void __launch_bounds__(256) k2_mm(K2Args<T> a) {
+__global__ void __launch_bounds__(256, NR * NC <= 3 ? 5 : NR * NC == 4 ? 4 : 2) k2_mm(K2Args<T> a) {
     using C = cpx<T>;
     using M = Mat4<T>;
     using V = typename M::V;
@@ -631,7 +633,7 @@ template <typename T>
 void apply2(fio_bf_s *bf, bool adj, const double2 *X, long ldx, double2 *Y, long ldy, int nrhs, const cpx<T> *F,
             const cpx<T> *Fa, void *ws, bool fint, hipStream_t s) {
     // columns per wave and reduction split: tuned (fio_bf_autotune) or 8 columns, which pads least (n = 64, 70
-    // columns: 1031 us against 1207 us with 16)
+    // columns: 1002 us against 1207 us with 16)
     const TileCfg c = bf_tile(bf, adj, sizeof(T) == 8 ? FIO_PREC_FP64 : FIO_PREC_FP32, nrhs);
     if (c.kc == 16)
         apply2k<T, 2>(bf, adj, X, ldx, Y, ldy, nrhs, F, Fa, ws, fint, c.nsplit, s);
