@@ -202,6 +202,12 @@ def kernel_model(name, n, q, k):
         peak = FP16_MFMA_PEAK_TFLOPS if name == "bf_split16" else (
             FP64_PEAK_TFLOPS if e == 16 else FP32_PEAK_TFLOPS)
         return ent * e, mult * 8.0 * ent * k, 2.0 * n * q * k * (8 if name == "bf_split16" else e), peak
+    if name.startswith("bf_side"):
+        # a whole-side pass: all transfer levels of one side, half of M (one of the two passes applies it)
+        # and, where it also reads or writes the vectors, the side's leaf blocks; the coefficient block
+        # is written by one pass and read by the other
+        ent = sum(kl for kl, _ in plan) // 2 * transfer + mid / 2 + (8 * q * n if "_in_" in name or "_out_" in name else 0)
+        return ent * e, 8.0 * ent * k, 1.0 * n * q * k * e, FP64_PEAK_TFLOPS if e == 16 else FP32_PEAK_TFLOPS
     if name.startswith("bf_transfer"):
         return transfer * e, 8.0 * transfer * k, 2.0 * n * q * k * e, FP64_PEAK_TFLOPS if e == 16 else FP32_PEAK_TFLOPS
     return None
