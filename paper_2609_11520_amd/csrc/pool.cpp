@@ -1,6 +1,6 @@
 // Device memory of the calls that build and destroy handles.
 //
-// The driver hands out memory it has cleared: once a process has cycled through the card's free memory,
+// The kernel driver hands out memory it has cleared: once a process has cycled through the card's free memory,
 // hipFree or hipMalloc waits for the clearing of what it frees or takes (2 GiB blocks on MI355X: 0.3 ms each
 // for the first 200 GB, then 20 to 320 ms), and an offline stage of N = 2^16 goes through about 6 GB: 31 ms
 // in the first 28 of a row, 194 ms in the next.  Blocks released while a handle is built or destroyed are
