@@ -20,6 +20,8 @@
  *    immutable once built and are released by the matching *_destroy.  Applies
  *    and solves on one handle may run concurrently on different streams when
  *    each call gets its own workspace.
+ *  - Device memory released while a handle is built or destroyed stays with the
+ *    process for the next handle, up to 8 GiB (see fio_memory_trim).
  *  - Vector ordering of the discrete FIO (Section 1, eq. fio): spatial entry i
  *    is x_i = i / N, frequency entry j is xi_j = j - N/2.
  */
@@ -478,6 +480,22 @@ fio_status fio_server_stats(fio_server_t s, long *completed, long *batches, long
                             size_t *peak_bytes);
 double fio_server_now(fio_server_t s);
 void fio_server_destroy(fio_server_t s);
+
+/* ---------------------------------------------------------------------------
+ * Device memory kept between handles.  The calls that build, import or destroy
+ * handles keep the blocks that they release, their own temporaries and those of
+ * the handles, for the next such call: at most 8 GiB and 1024 blocks.  A block is
+ * given back to the device when 64 such calls have not used it, when newer ones
+ * exceed these bounds, and all of them when an allocation of this library fails.
+ * An allocation of other code in the process, or of another process, that fails
+ * gives nothing back by itself: call fio_memory_trim before it, or after the last
+ * handle has been built.  It keeps the most recently released blocks of at most
+ * keep_bytes in all (0: none) and waits for the kernels that use the others, as
+ * hipFree does; not while a stream of the process is being captured.
+ * fio_memory_kept returns the bytes kept now.  Both may be called from any thread.
+ * ------------------------------------------------------------------------- */
+void fio_memory_trim(size_t keep_bytes);
+size_t fio_memory_kept(void);
 
 /* ---------------------------------------------------------------------------
  * Measurement hooks.  While enabled, the library brackets each of its hot

@@ -18,7 +18,8 @@ from ._lib import (FIO_PREC_FP64, FIO_PREC_FP32, FIO_PREC_SPLIT_FP16, FIO_SOLVE_
 
 __all__ = ["BF", "HSS", "ULV", "approx_solve", "colmajor", "empty", "FIO_PREC_FP64", "FIO_PREC_FP32",
            "FIO_PREC_SPLIT_FP16", "FIO_SOLVE_DIRECT", "FIO_SOLVE_IR", "FIO_SOLVE_PCG", "FIO_AMP_ONE",
-           "FIO_AMP_GAUSSIAN_SUM", "FIO_AMP_HANKEL", "FIO_PHASE2_ANISO", "FIO_PHASE2_ISO", "FioError", "lib"]
+           "FIO_AMP_GAUSSIAN_SUM", "FIO_AMP_HANKEL", "FIO_PHASE2_ANISO", "FIO_PHASE2_ISO", "FioError", "lib",
+           "trim_memory", "memory_kept"]
 
 
 def lib():
@@ -70,9 +71,20 @@ def require_colmajor(x, n, what):
     return x, (x.stride(1) if k > 1 else n)
 
 
-def empty(n, k, device="cuda"):
+def _alloc(shape, dtype, device="cuda"):
+    # the library's kept blocks (trim_memory) make room when torch's allocator finds none
     torch = _torch()
-    return torch.empty((k, n), dtype=torch.complex128, device=device).t()
+    try:
+        return torch.empty(shape, dtype=dtype, device=device)
+    except torch.cuda.OutOfMemoryError:
+        if memory_kept() == 0:
+            raise
+    trim_memory()
+    return torch.empty(shape, dtype=dtype, device=device)
+
+
+def empty(n, k, device="cuda"):
+    return _alloc((k, n), _torch().complex128, device).t()
 
 
 def _ptr(t):
@@ -80,8 +92,7 @@ def _ptr(t):
 
 
 def _workspace(nbytes):
-    torch = _torch()
-    return torch.empty(max(int(nbytes), 1), dtype=torch.uint8, device="cuda")
+    return _alloc(max(int(nbytes), 1), _torch().uint8)
 
 
 class BF:
@@ -434,6 +445,17 @@ def approx_solve_static(bf, ulv, U, mode=FIO_SOLVE_DIRECT, prec=FIO_PREC_FP64, m
 
 def approx_solve_static_max_bytes():
     return lib().fio_approx_solve_static_max_bytes()
+
+
+def trim_memory(keep_bytes=0):
+    """Gives back the device memory that the library keeps between handles (at most 8 GiB), down to
+    keep_bytes (fio_memory_trim).  Call it when no more handles will be built soon and others need the memory."""
+    lib().fio_memory_trim(int(keep_bytes))
+
+
+def memory_kept():
+    """Bytes of device memory kept between handles."""
+    return lib().fio_memory_kept()
 
 
 def timing_enable(on=True):

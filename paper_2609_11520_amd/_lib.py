@@ -104,6 +104,8 @@ PROTOS = {
     "fio_server_stats": (i32, [vp, C.POINTER(lg), C.POINTER(lg), C.POINTER(lg), C.POINTER(sz)]),
     "fio_server_now": (C.c_double, [vp]),
     "fio_server_destroy": (None, [vp]),
+    "fio_memory_trim": (None, [sz]),
+    "fio_memory_kept": (sz, []),
     "fio_timing_enable": (None, [i32]),
     "fio_timing_reset": (None, []),
     "fio_timing_query": (i32, [C.c_char_p, C.POINTER(lg), C.POINTER(C.c_double)]),

@@ -4,14 +4,15 @@
 // hipFree or hipMalloc waits for the clearing of what it frees or takes (2 GiB blocks on MI355X: 0.3 ms each
 // for the first 200 GB, then 20 to 320 ms), and an offline stage of N = 2^16 goes through about 6 GB: 31 ms
 // in the first 28 of a row, 194 ms in the next.  Blocks released while a handle is built or destroyed are
-// therefore kept for the next one, at most kPoolBytes of them; they are given back when they have not
-// been used for kPoolAge such calls, when newer ones need the room and when the device runs out of memory.
+// therefore kept for the next one, at most kBounds.bytes of them; they are given back when they have not
+// been used for kBounds.age such calls, when newer ones need the room, when the device runs out of memory, and by
+// fio_memory_trim.
 //
 // A kept block may still be read or written by kernels in flight (on any stream).  hipFree would have
 // waited for them; here the next owner does, once, before it takes a block that was kept after the
-// last such wait.
-#include <iterator>
-#include <map>
+// last such wait.  The lock is not held while the device is waited for, here or in hipFree.
+#include "pool.h"
+
 #include <new>
 
 #include "common.h"
@@ -19,31 +20,11 @@
 namespace fio {
 namespace {
 
-constexpr size_t kPoolBytes = (size_t)8 << 30;    // under 3 % of the card
-constexpr size_t kPoolBlocks = 1024;
-constexpr long kPoolAge = 64;
-
-struct Kept {
-    void *p;
-    int dev;
-    long tick;                                    // PoolScope count when it was kept
-    long epoch;                                   // order of keeping
-};
-
-using It = std::multimap<size_t, Kept>::iterator;
+constexpr PoolBounds kBounds{(size_t)8 << 30, 1024, 64};    // 8 GiB: under 3 % of the card
 
 struct Pool {
     std::mutex mu;
-    std::multimap<size_t, Kept> kept;             // by capacity
-    size_t bytes = 0;
-    long tick = 0, epoch = 0;
-    std::map<int, long> waited;                   // per device: blocks up to this epoch are idle
-
-    It drop(It it) {
-        (void)hipFree(it->second.p);
-        bytes -= it->first;
-        return kept.erase(it);
-    }
+    BlockPool q{kBounds};
 };
 
 // never destroyed: handles may outlive the static objects of the library
@@ -54,36 +35,41 @@ Pool &pool() {
 
 thread_local int t_depth = 0;
 
-// the least recently kept blocks beyond the bounds
-void evict(Pool &q) {
-    while (!q.kept.empty() && (q.bytes > kPoolBytes || q.kept.size() > kPoolBlocks)) {
-        It old = q.kept.begin();
-        for (It it = q.kept.begin(); it != q.kept.end(); ++it)
-            if (it->second.epoch < old->second.epoch) old = it;
-        q.drop(old);
-    }
+void release(const PoolBlocks &b) {
+    for (const auto &x : b) (void)hipFree(x.second.p);
 }
 
-// a block of at least `bytes` that wastes at most a quarter (and 64 KiB) of its size
-void *take(size_t bytes, int dev, size_t *cap) {
-    Pool &q = pool();
-    std::lock_guard<std::mutex> lk(q.mu);
-    for (It it = q.kept.lower_bound(bytes); it != q.kept.end() && it->first <= bytes + bytes / 4 + 65536; ++it) {
-        if (it->second.dev != dev) continue;
-        if (it->second.epoch > q.waited[dev]) {
-            if (hipDeviceSynchronize() != hipSuccess) {
-                (void)hipGetLastError();
-                return nullptr;
-            }
-            q.waited[dev] = q.epoch;
-        }
-        void *p = it->second.p;
-        *cap = it->first;
-        q.bytes -= it->first;
-        q.kept.erase(it);
-        return p;
+void trim(size_t keep) {
+    PoolBlocks out;
+    {
+        Pool &pl = pool();
+        std::lock_guard<std::mutex> lk(pl.mu);
+        pl.q.shrink(keep, kBounds.blocks, out);
     }
-    return nullptr;
+    release(out);
+}
+
+// a kept block of at least `bytes` that nothing uses any more, or null
+void *take(size_t bytes, int dev, size_t *cap) {
+    Pool &pl = pool();
+    PoolBlock b;
+    bool wait = false;
+    long upto = 0;
+    {
+        std::lock_guard<std::mutex> lk(pl.mu);
+        if (!pl.q.take(bytes, dev, cap, &b, &wait)) return nullptr;
+        upto = pl.q.epoch();
+    }
+    if (wait) {
+        if (hipDeviceSynchronize() != hipSuccess) {
+            (void)hipGetLastError();
+            dev_free(b.p, *cap, dev);
+            return nullptr;
+        }
+        std::lock_guard<std::mutex> lk(pl.mu);
+        pl.q.waited(dev, upto);
+    }
+    return b.p;
 }
 
 }  // namespace
@@ -93,12 +79,11 @@ void *dev_alloc(size_t bytes, size_t *cap, int *dev) {
     size_t c = bytes;
     void *p = t_depth > 0 ? take(bytes, *dev, &c) : nullptr;
     if (!p) {
+        c = bytes;
         hipError_t e = hipMalloc(&p, bytes);
         if (e == hipErrorOutOfMemory) {
             (void)hipGetLastError();
-            Pool &q = pool();
-            std::lock_guard<std::mutex> lk(q.mu);
-            for (It it = q.kept.begin(); it != q.kept.end();) it = q.drop(it);
+            trim(0);
             e = hipMalloc(&p, bytes);
         }
         FIO_HIP(e);
@@ -108,17 +93,18 @@ void *dev_alloc(size_t bytes, size_t *cap, int *dev) {
 }
 
 void dev_free(void *p, size_t cap, int dev) {
-    if (t_depth > 0 && cap <= kPoolBytes) {
-        Pool &q = pool();
-        std::lock_guard<std::mutex> lk(q.mu);
+    if (t_depth > 0 && cap <= kBounds.bytes) {
+        PoolBlocks out;
+        bool kept = true;
         try {
-            q.kept.emplace(cap, Kept{p, dev, q.tick, q.epoch + 1});
-            ++q.epoch;
-            q.bytes += cap;
-            evict(q);
-            return;
+            Pool &pl = pool();
+            std::lock_guard<std::mutex> lk(pl.mu);
+            pl.q.keep(p, cap, dev, out);
         } catch (const std::bad_alloc &) {
+            kept = false;
         }
+        release(out);
+        if (kept) return;
     }
     (void)hipFree(p);
 }
@@ -127,11 +113,21 @@ PoolScope::PoolScope() { ++t_depth; }
 
 PoolScope::~PoolScope() {
     if (--t_depth > 0) return;
-    Pool &q = pool();
-    std::lock_guard<std::mutex> lk(q.mu);
-    ++q.tick;
-    for (It it = q.kept.begin(); it != q.kept.end();)
-        it = q.tick - it->second.tick > kPoolAge ? q.drop(it) : std::next(it);
+    PoolBlocks out;
+    {
+        Pool &pl = pool();
+        std::lock_guard<std::mutex> lk(pl.mu);
+        pl.q.end_call(out);
+    }
+    release(out);
 }
 
 }  // namespace fio
+
+extern "C" void fio_memory_trim(size_t keep_bytes) { fio::trim(keep_bytes); }
+
+extern "C" size_t fio_memory_kept(void) {
+    fio::Pool &pl = fio::pool();
+    std::lock_guard<std::mutex> lk(pl.mu);
+    return pl.q.bytes();
+}
