@@ -107,7 +107,7 @@ __global__ void __launch_bounds__(NB == 8 ? 1024 : 512) k_qr_panel(const WyNode 
             __syncthreads();
             const double2 x0 = srow[c];
             const double a2 = x0.x * x0.x + x0.y * x0.y, sigma = sqrt(a2 + tot[0]);
-            if (sigma > 0.0) {
+            if (sigma != 0.0) {                  // a NaN goes on into every column
                 const double aa = sqrt(a2);
                 const double2 ph = aa > 0.0 ? zc(x0.x / aa, x0.y / aa) : zc(1.0, 0.0);
                 const double2 beta = zc(-ph.x * sigma, -ph.y * sigma);
@@ -195,7 +195,7 @@ __global__ void __launch_bounds__(1024) k_qr_column(const WyNode *__restrict__ n
     const double a2 = x0.x * x0.x + x0.y * x0.y, sigma = sqrt(a2 + p), aa = sqrt(a2);
     double ta = 0.0;
     double2 beta = zc(0.0, 0.0);
-    if (sigma > 0.0) {
+    if (sigma != 0.0) {
         const double2 ph = aa > 0.0 ? zc(x0.x / aa, x0.y / aa) : zc(1.0, 0.0);
         beta = zc(-ph.x * sigma, -ph.y * sigma);
         const double2 den = csub(x0, beta);

@@ -141,7 +141,7 @@ __global__ void __launch_bounds__(1024) k_ulv_node(FactArgs a) {
             for (int i = tid; i < n; i += nt) part += x[i].x * x[i].x + x[i].y * x[i].y;
             const double sigma = sqrt(wsum(part, sh));
             double tau = 0.0;
-            if (sigma > 0.0) {
+            if (sigma != 0.0) {                  // a NaN goes on into every column
                 const double aa = sqrt(al.x * al.x + al.y * al.y);
                 double2 ph = aa > 0.0 ? zc(al.x / aa, al.y / aa) : zc(1.0, 0.0);
                 double2 beta = zc(-ph.x * sigma, -ph.y * sigma);
