@@ -37,7 +37,8 @@ struct fio_bf_s {
     fio::DevBuf f16;                   // split-fp16 transfer blocks: hi and lo planes (FIO_PREC_SPLIT_FP16)
     bool split16 = false;              // FIO_PREC_SPLIT_FP16 copies built (1D, q = 9)
     // structured transfer factors (built on the GPU only): twiddles of every B and C level and
-    // the two shared Lagrange matrices P_c(i, t) (host copy, passed as kernel arguments)
+    // the two shared Lagrange matrices P_c(i, t) (host copy, passed as kernel arguments); q = 9: in FP32, of the
+    // 3 levels next to the leaves, where the split-FP16 copies were asked for
     bool structured = false;
     fio::DevBuf tw64, tw32;
     double Pchild[2 * 16 * 16] = {};
@@ -78,5 +79,5 @@ size_t bf_ws_bytes(const fio_bf_s *bf, int nrhs, fio_prec prec);
 int tile_key(bool adj, fio_prec prec, int nrhs);
 // the tuned configuration for an apply (all zero when none was tuned)
 TileCfg bf_tile(const fio_bf_s *bf, bool adj, fio_prec prec, int nrhs);
-size_t bf_tw_off(const fio_bf_s *bf, bool cside, int lev);   // element offset of a level's twiddles
+size_t bf_tw_off(const fio_bf_s *bf, bool cside, int lev);   // element offset of a stored level's twiddles
 }  // namespace fio

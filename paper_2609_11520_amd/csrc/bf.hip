@@ -83,7 +83,8 @@ bool leaf_fused_disabled() { return g_leaf_fused_off; }
 
 size_t bf_tw_off(const fio_bf_s *bf, bool cside, int lev) {
     const size_t ntw = (size_t)(bf->N / 2) * 8 * bf->q;
-    return ((cside ? bf->nl : 0) + (size_t)lev) * ntw;
+    const int first = bf->q == kSideQ ? bf->nl - 3 : 0, levels = bf->nl - first;
+    return ((size_t)(cside ? levels : 0) + (size_t)(lev - first)) * ntw;
 }
 
 size_t bf_coef_elems(const fio_bf_s *bf, int nrhs) { return (size_t)bf->N * bf->q * (size_t)nrhs; }
@@ -338,6 +339,25 @@ static void bf_generate(fio_bf_s *bf, hipStream_t s) {
 
 void bf_make_lowprec(fio_bf_s *bf, hipStream_t s);   // bf_lowprec.hip
 
+// q = 9: the FP32 twiddles of the 3 levels next to the leaves, for the matrix-core engine's first pass
+static void make_leaf_pass_tw(fio_bf_s *bf, hipStream_t s) {
+    const Geo g = geo_of(bf);
+    const Nodes tn = make_nodes(bf->q);
+    const size_t ntw = (size_t)(bf->N / 2) * 8 * bf->q;
+    bf->tw32.alloc(6 * ntw * sizeof(float2));
+    DevBuf tw(ntw * sizeof(double2));
+    for (int lev = bf->nl - 3; lev < bf->nl; ++lev)
+        for (int cs = 0; cs < 2; ++cs) {
+            if (cs)
+                gen_TW_C<<<grid1d(ntw, 256), 256, 0, s>>>(g, tn, bf->h + lev, tw.as<double2>());
+            else
+                gen_TW_B<<<grid1d(ntw, 256), 256, 0, s>>>(g, tn, bf->h + lev, tw.as<double2>());
+            cvt_f64_f32<<<grid1d(ntw, 256), 256, 0, s>>>(tw.as<double2>(), bf->tw32.as<float2>() + bf_tw_off(bf, cs, lev),
+                                                         ntw);
+        }
+    FIO_HIP(hipGetLastError());
+}
+
 static void bf_make_copies(fio_bf_s *bf, hipStream_t s) {
     const bool want16 = (bf->desc.prec_mask & (1u << FIO_PREC_SPLIT_FP16)) != 0;
     if (want16 && (bf->dim != 1 || bf->q != 9)) throw Err{FIO_ERR_UNSUPPORTED};
@@ -349,6 +369,7 @@ static void bf_make_copies(fio_bf_s *bf, hipStream_t s) {
                                                          bf->total);
         if (side_built(bf)) {
             side_make_f32(bf, s);
+            if (want16 && bf->nl >= 3) make_leaf_pass_tw(bf, s);
         } else if (bf->structured) {
             const size_t ntw = 2 * bf->nl * (size_t)(bf->N / 2) * 8 * bf->q;
             bf->tw32.alloc(ntw * sizeof(float2));

@@ -1068,6 +1068,8 @@ static void apply_q(fio_bf_s *bf, bool adj, const double2 *X, long ldx, double2 
         if (tc.kmax > 0 && tc.kmax < kmax) kmax = tc.kmax;
         if (split && tc.valu) split = false;
     }
+    // q = 9 keeps one structured pass: the first one, leaf factor folded in, of the matrix-core engine
+    constexpr bool kStruct = Q != kSideQ || sizeof(T) == 4;
     auto pass = [&](bool a, bool cside, int lo, int hi, bool epi, bool leaf = false) {
         if constexpr (fused_q<Q>()) {
             const int kl = hi - lo;
@@ -1091,8 +1093,8 @@ static void apply_q(fio_bf_s *bf, bool adj, const double2 *X, long ldx, double2 
                     return;
                 }
             }
-            if constexpr (Q != kSideQ) {
-                if (bf->structured) {
+            if constexpr (kStruct) {
+                if (bf->structured && (leaf || Q != kSideQ)) {
                     StructArgs<T, Q> sa;
                     const cpx<T> *TWb = f64 ? reinterpret_cast<const cpx<T> *>(bf->tw64.p)
                                             : reinterpret_cast<const cpx<T> *>(bf->tw32.p);
@@ -1130,7 +1132,7 @@ static void apply_q(fio_bf_s *bf, bool adj, const double2 *X, long ldx, double2 
                     if (leaf) {
                         FIO_TIMED(f64 ? "bf_struct_leaf_f64" : "bf_struct_leaf_f32", s);
                         run_struct_leaf<T, Q>(sa, a, epi, bf->N, s);
-                    } else {
+                    } else if constexpr (Q != kSideQ) {
                         FIO_TIMED(f64 ? "bf_struct_f64" : "bf_struct_f32", s);
                         run_struct<T, Q>(sa, kl, a, epi, bf->N, s);
                     }
@@ -1172,7 +1174,7 @@ static void apply_q(fio_bf_s *bf, bool adj, const double2 *X, long ldx, double2 
     };
     // The first leaf factor folds into a first pass of 3 levels of structured factors (one leaf box per
     // wave) when its workgroups can be grouped by 8 per XCD (2^L' / 8 % 8 == 0).
-    const bool leaf_fused = Q != kSideQ && leaf_foldable<T, Q>() && fused && bf->structured && !leaf_fused_disabled() &&
+    const bool leaf_fused = kStruct && leaf_foldable<T, Q>() && fused && bf->structured && !leaf_fused_disabled() &&
                             !leaf_sep && (kmax < bf->nl ? kmax : bf->nl) == 3 && bf->Lp >= 6;
     const bool tiled = ((1L << bf->Lp) % 4) == 0;
     const dim3 tgrid((unsigned)((1L << bf->Lp) / 4), (unsigned)((nrhs + 63) / 64));
