@@ -1,6 +1,8 @@
 // Side passes of the 1D structured butterfly (see bf_side.h): table generation and kernels.
 #include "bf_side.h"
 
+#include <algorithm>
+
 #include "bf_apply.h"
 #include "ddmath.h"
 
@@ -887,7 +889,7 @@ template <typename T> static SideArgs<T> side_args(const fio_bf_s *bf, bool csid
     a.mat = reinterpret_cast<const T *>(t);
     a.mid = o.amp ? kSideEMamp : kSideEM;
     a.nrhs = nrhs;
-    // columns per workgroup: at most 8, the same for every chunk
+    // columns per workgroup: at most 8 (see side_pass), the same for every chunk
     a.nch = (nrhs + 7) / 8;
     a.kc = (nrhs + a.nch - 1) / a.nch;
     a.L = bf->L;
@@ -906,6 +908,14 @@ static void side_pass(SideArgs<T> a, bool cside, bool adj, int j0, int nlev, hip
     a.kl = nlev;
     if (cside || j0 > 0) a.mid = 0;      // M follows the C side: before the first level of the B side
     const int G = 1 << (nlev - 1);
+    // A shorter pass moves the coefficients more often and has threads to spare: 256 bytes of a row per workgroup
+    // instead of 8 columns (as long as it has 256 threads).  One level per pass in FP32, 64 columns, N = 2^16 / 2^18:
+    // 1430 / 6770 -> 1255 / 5810 us, three levels with the leaf factors apart 850 / 3510 -> 765 / 3140 us.
+    const int cap = std::min((int)(256 / sizeof(cpx<T>)), 256 / G);
+    if (nlev < a.Lp - a.h && cap > 8) {
+        a.nch = (a.nrhs + cap - 1) / cap;
+        a.kc = (a.nrhs + a.nch - 1) / a.nch;
+    }
     // sub-butterflies per workgroup: enough for one full wave
     a.nsb = 1;
     while (a.nsb * G * a.kc < 64) a.nsb *= 2;
