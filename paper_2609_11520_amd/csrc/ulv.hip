@@ -632,7 +632,7 @@ __device__ __forceinline__ void ulv_tile(Mat4<double>::V P, Mat4<double>::V Q, i
             tq = -tq;
             q = -q;
         }
-        put(Mat4<double>::row(lane, i) + (im ? Mat4<double>::row(0, 2) : 0), im ? zc(tp - q, p + tq) : zc(p - tq, tp + q));
+        put(i, Mat4<double>::row(lane, i) + (im ? Mat4<double>::row(0, 2) : 0), im ? zc(tp - q, p + tq) : zc(p - tq, tp + q));
     }
 }
 
@@ -705,7 +705,7 @@ __global__ void __launch_bounds__(512) k_ulv_mm(LevelArgs a, LevelVecs v, int rg
     __shared__ double2 part[KS * NR * 128];
 #pragma unroll
     for (int t = 0; t < NR; ++t)
-        ulv_tile<DOWN>(P[t], Q[t], lane, [&](int r, double2 z) { part[(wave * 16 * NR + 16 * t + r) * 8 + (lr & 7)] = z; });
+        ulv_tile<DOWN>(P[t], Q[t], lane, [&](int, int r, double2 z) { part[(wave * 16 * NR + 16 * t + r) * 8 + (lr & 7)] = z; });
     __syncthreads();
     for (int e = threadIdx.x; e < 128 * NR; e += 512) {
         const int gm = r0 + (e >> 3), gc = cg * 8 + (e & 7);
@@ -799,7 +799,7 @@ __global__ void __launch_bounds__(64 * CW * RG) k_ulv_leaf(LevelArgs a, LevelVec
     __syncthreads();
 #pragma unroll
     for (int t = 0; t < NR; ++t)
-        ulv_tile<DOWN>(P[t], Q[t], lane, [&](int r, double2 z) { xs[(xc + (lr & 7)) * LD + r0 + 16 * t + r] = z; });
+        ulv_tile<DOWN>(P[t], Q[t], lane, [&](int, int r, double2 z) { xs[(xc + (lr & 7)) * LD + r0 + 16 * t + r] = z; });
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < NCOL / NW; ++j) {
@@ -808,101 +808,123 @@ __global__ void __launch_bounds__(64 * CW * RG) k_ulv_leaf(LevelArgs a, LevelVec
     }
 }
 
-// The same for more than 16 columns, 32 per workgroup: W goes through LDS in two halves of 32 inner indices, which
-// the 8 waves (4 column groups, 2 pairs of row tiles) share.  Lanes of a matrix tile run along the rows of
-// its operand first, so W^* from memory costs four times the cache accesses of W (4096 leaves, 64 columns:
-// up 236, down 304 us with k_ulv_leaf's loads; 228 and 255 here, where the matrix rate allows 115 and the
-// 0.8 GB moved 160).
-template <bool DOWN>
-__global__ void __launch_bounds__(512) k_ulv_leaf32(LevelArgs a, LevelVecs v, int cgroups, unsigned nwork) {
+// The same for wider blocks and for levels of many nodes: a workgroup of RG x CG waves forms 16 NR RG rows for 8 CG
+// columns of a node, W and the vectors through LDS in chunks of 32 inner indices, the next chunk on its way to
+// registers while one is used, so that waves share what they read and W^* is read along its columns.  Inner
+// indices in the order of k_ulv_leaf, or (SPLIT) of k_ulv_mm, its 8 slices one after another.
+// N = 2^16 with 512 leaves of 128 rows, a solve of 64 columns: 467 us with k_ulv_mm (which reads W once per 8
+// columns), 300 us with tiles of 32 x 32 on the vector units, 235 us; 8 columns 109, 170 and 93 us.  4096 leaves of 64
+// rows, 64 columns: 613 us with W in halves of 32 inner indices and the whole vectors in LDS, 549 us; 33 columns 563 ->
+// 420 us, 1024 leaves and 512 columns 1086 -> 980 us, 512 leaves of 32 rows and 512 columns 433 -> 241 us (whose rows
+// beyond the node and columns beyond the block were multiplied too).
+template <bool DOWN, int NR, int RG, int CG, bool SPLIT>
+__global__ void __launch_bounds__(64 * RG * CG) k_ulv_wide(LevelArgs a, LevelVecs v, int rgroups, int cgroups, unsigned nwork) {
     using M = Mat4<double>;
     using V = M::V;
-    constexpr int NR = 2, LD = 65, LW = 33;
-    __shared__ double2 xs[32 * LD], ws[64 * LW];               // [column][row], [result row][inner index]
+    constexpr int RT = 16 * NR * RG, CT = 8 * CG, NT = 64 * RG * CG, KC = 32, LW = KC + 1, LX = KC + 2, LD = RT + 1;
+    constexpr int EW = RT * KC / NT, EX = CT * KC / NT, EO = RT * CT / NT;
+    __shared__ double2 lds[RT * LW + CT * LX];
+    static_assert(CT * LD <= RT * LW + CT * LX, "the results are staged in the same LDS");
+    double2 *ws = lds, *xs = lds + RT * LW;                    // [row][inner], [column][inner]
     const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lk = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // consecutive workgroups run on one XCD, whose L2 then serves the column groups of a node
     const unsigned work = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
     if (work >= nwork) return;
-    const int node = work / cgroups, c0 = (work - node * cgroups) * 32;
+    const int c0 = work % cgroups * CT, rn = work / cgroups, g0 = rn % rgroups * RT, node = rn / rgroups;
     const int m = a.m[node], k = a.k[node];
-    if (m == 0) return;
+    if (g0 >= m) return;
     const long yo = a.yoff[node], ro = a.roff[node];
     const double2 *W = a.W + a.woff[node];
-    const int r0 = (wave >> 2) * 16 * NR, xc = (wave & 3) * 8;
-    const int ns = (m + 7) >> 3;
-    // entry j of the thread in a half of W, consecutive lanes along a column, and its place
-    auto wat = [&](int half, int j) {
-        const int i = DOWN ? (tid >> 5) + 16 * j : lane, l = 32 * half + (DOWN ? tid & 31 : (tid >> 6) + 8 * j);
-        const int ic = i < m ? i : m - 1, lc = l < m ? l : m - 1;
-        return W[DOWN ? lc + ic * m : ic + lc * m];
+    const int r0 = wave / CG * 16 * NR, xc = wave % CG * 8;
+    const bool act = g0 + r0 < m && c0 + xc < v.nrhs;
+    double wr[EW], wi[EW], xr[EX], xi[EX];                     // (arrays of pairs would be kept in memory)
+    auto fetch = [&](int l0) {
+#pragma unroll
+        for (int j = 0; j < EW; ++j) {
+            const int e = tid + NT * j, r = g0 + (DOWN ? e / KC : e % RT), l = l0 + (DOWN ? e % KC : e / RT);
+            const int rc = r < m ? r : m - 1, lc = l < m ? l : m - 1;
+            const double2 w = W[DOWN ? lc + (size_t)rc * m : rc + (size_t)lc * m];
+            wr[j] = w.x;
+            wi[j] = w.y;
+        }
+#pragma unroll
+        for (int j = 0; j < EX; ++j) {
+            const int e = tid + NT * j, c = c0 + e / KC, l = l0 + e % KC;
+            const int cc = c < v.nrhs ? c : v.nrhs - 1, lc = l < m ? l : m - 1;
+            const double2 *p = DOWN ? (lc < k ? v.Bh + (yo + lc) + (size_t)cc * v.ldb : v.Ylo + (ro + lc - k) + (size_t)cc * v.ldlo)
+                                    : v.Yin + (yo + lc) + (size_t)cc * v.ldy;
+            const double2 x = *p;
+            xr[j] = l < m ? x.x : 0.0;
+            xi[j] = l < m ? x.y : 0.0;
+        }
     };
-    auto wput = [&](int j, double2 w) {
-        ws[DOWN ? ((tid >> 5) + 16 * j) * LW + (tid & 31) : lane * LW + (tid >> 6) + 8 * j] = w;
-    };
-    auto xat = [&](int j) {
-        const int c = wave + 8 * j, gc = c0 + c < v.nrhs ? c0 + c : v.nrhs - 1, lc = lane < m ? lane : m - 1;
-        return *(DOWN ? (lc < k ? v.Bh + (yo + lc) + (size_t)gc * v.ldb : v.Ylo + (ro + lc - k) + (size_t)gc * v.ldlo)
-                      : v.Yin + (yo + lc) + (size_t)gc * v.ldy);
-    };
-    auto xput = [&](int j, double2 x) { xs[(wave + 8 * j) * LD + lane] = lane < m ? x : zc(0.0, 0.0); };
-    double2 w0 = wat(0, 0), w1 = wat(0, 1), w2 = wat(0, 2), w3 = wat(0, 3);
-    {
-        const double2 x0 = xat(0), x1 = xat(1), x2 = xat(2), x3 = xat(3);
-        wput(0, w0);
-        wput(1, w1);
-        wput(2, w2);
-        wput(3, w3);
-        xput(0, x0);
-        xput(1, x1);
-        xput(2, x2);
-        xput(3, x3);
-    }
-    __syncthreads();
     V P[NR], Q[NR];
+    double2 sum[NR][2];
 #pragma unroll
-    for (int t = 0; t < NR; ++t) P[t] = Q[t] = V{0, 0, 0, 0};
-    const double *xb = reinterpret_cast<const double *>(xs + (xc + (lr & 7)) * LD + 2 * lk) + (lr >> 3);
-    const double2 *wb = ws + (r0 + lr) * LW + 2 * lk;
-    auto half = [&](int h) {
+    for (int t = 0; t < NR; ++t) {
+        P[t] = Q[t] = V{0, 0, 0, 0};
+        sum[t][0] = sum[t][1] = zc(-0.0, -0.0);
+    }
+    // adds the slice's products to the sums
+    auto flush = [&]() {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            if (4 * h + q >= ns) break;
+        for (int t = 0; t < NR; ++t) {
+            ulv_tile<DOWN>(P[t], Q[t], lane, [&](int i, int, double2 z) { sum[t][i] = cadd(sum[t][i], z); });
+            P[t] = Q[t] = V{0, 0, 0, 0};
+        }
+    };
+    // steps of 4 inner indices, and of a slice
+    const int ns = SPLIT ? (m + 3) >> 2 : 2 * ((m + 7) >> 3), per = SPLIT ? (ns + 7) >> 3 : ns;
+    const double2 *wb = ws + (r0 + lr) * LW + (SPLIT ? lk : 2 * lk);
+    const double *xb = reinterpret_cast<const double *>(xs + (xc + (lr & 7)) * LX + (SPLIT ? lk : 2 * lk)) + (lr >> 3);
+    int left = per;
+    for (int s0 = -KC / 4;; s0 += KC / 4) {
+        const bool more = s0 + KC / 4 < ns;
+        if (more) fetch(4 * s0 + KC);
+        if (act && s0 >= 0) {
 #pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const double x = xb[16 * (4 * h + q) + 2 * u];
+            for (int q = 0; q < KC / 4; ++q) {
+                if (s0 + q >= ns) break;
+                const int l = SPLIT ? 4 * q : 8 * (q >> 1) + (q & 1);
+                const double x = xb[2 * l];
 #pragma unroll
                 for (int t = 0; t < NR; ++t) {
-                    const double2 w = wb[16 * t * LW + 8 * q + u];
+                    const double2 w = wb[16 * t * LW + l];
                     P[t] = M::mac(w.x, x, P[t]);
                     Q[t] = M::mac(w.y, x, Q[t]);
                 }
+                if (SPLIT && --left == 0) {
+                    flush();
+                    left = per;
+                }
             }
         }
-    };
-    // the second half is on its way while the first is used
-    w0 = wat(1, 0);
-    w1 = wat(1, 1);
-    w2 = wat(1, 2);
-    w3 = wat(1, 3);
-    half(0);
-    __syncthreads();
-    if (m > 32) {
-        wput(0, w0);
-        wput(1, w1);
-        wput(2, w2);
-        wput(3, w3);
         __syncthreads();
-        half(1);
+        if (!more) break;
+#pragma unroll
+        for (int j = 0; j < EW; ++j) {
+            const int e = tid + NT * j;
+            ws[DOWN ? e / KC * LW + e % KC : e % RT * LW + e / RT] = zc(wr[j], wi[j]);
+        }
+#pragma unroll
+        for (int j = 0; j < EX; ++j) {
+            const int e = tid + NT * j;
+            xs[e / KC * LX + e % KC] = zc(xr[j], xi[j]);
+        }
         __syncthreads();
     }
+    if (!SPLIT || left != per) flush();
 #pragma unroll
     for (int t = 0; t < NR; ++t)
-        ulv_tile<DOWN>(P[t], Q[t], lane, [&](int r, double2 z) { xs[(xc + (lr & 7)) * LD + r0 + 16 * t + r] = z; });
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+            lds[(xc + (lr & 7)) * LD + r0 + 16 * t + M::row(lane, i) + (lr >= 8 ? M::row(0, 2) : 0)] = sum[t][i];
     __syncthreads();
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int c = wave + 8 * j;
-        if (lane < m && c0 + c < v.nrhs) ulv_put<DOWN>(v, yo, ro, k, lane, c0 + c, xs[c * LD + lane]);
+    for (int j = 0; j < EO; ++j) {
+        const int e = tid + NT * j, r = g0 + e % RT, c = e / RT;
+        if (r < m && c0 + c < v.nrhs) ulv_put<DOWN>(v, yo, ro, k, r, c0 + c, lds[c * LD + e % RT]);
     }
 }
 
@@ -1319,28 +1341,52 @@ static size_t ulv_ws_bytes(const hss_ulv_s *f, int nrhs) {
     return (rows + 8 * (size_t)(f->Lh + 2)) * (size_t)nrhs * sizeof(double2) + 8192;
 }
 
-// One level of nn nodes of at most mmax rows.  Both kernels sum a column in an order that depends on the level
-// alone; the rows and columns of a workgroup only split the work: the wider tile that still gives 2
-// workgroups per CU, and no more columns than there are.
+// One level of nn nodes of at most mmax rows.  A column is summed in an order that depends on the level alone; the
+// rows and columns of a workgroup only split the work.
 template <bool DOWN> static void ulv_level(const LevelArgs &a, const LevelVecs &v, int nn, int mmax, hipStream_t s) {
     auto wgs = [](long n) {
         if (n > (1L << 31)) throw Err{FIO_ERR_UNSUPPORTED};
         return dim3((unsigned)((n + 7) / 8 * 8));
     };
-    const int rt = (mmax + 15) / 16, c8 = (v.nrhs + 7) / 8, c16 = (v.nrhs + 15) / 16, c32 = (v.nrhs + 31) / 32;
-    if (mmax > 64) {
+    const int rt = (mmax + 15) / 16, r64 = (mmax + 63) / 64, c8 = (v.nrhs + 7) / 8, c16 = (v.nrhs + 15) / 16,
+              c32 = (v.nrhs + 31) / 32;
+    // 16 columns per workgroup where 32 would leave half of one's columns empty (4096 leaves of 64 rows, 33 columns:
+    // 508 -> 420 us)
+    const bool by16 = c16 & 1;
+    const long n8 = (long)nn * r64 * c8, n16 = (long)nn * r64 * c16, n32 = (long)nn * r64 * c32;
+    if (mmax > 64 && nn < 128) {
+        // Few nodes: the inner dimension is split over the waves of a workgroup.  64 nodes of 256 rows take 56 us a
+        // solve of one column split and 60 us with the kernels of many nodes, 128 of 128 rows 52 and 52 us, but 64
+        // columns 108 and 89 us.  Two workgroups per CU of the wide form are enough: 2D n = 64, 256 columns
+        // 749 us, with k_ulv_mm 806 us.
         const int r2 = (rt + 1) / 2;
-        const long n2 = (long)nn * c8 * r2, n1 = (long)nn * c8 * rt;
-        if (n2 >= 512)
-            k_ulv_mm<DOWN, 2><<<wgs(n2), 512, 0, s>>>(a, v, r2, c8, (unsigned)n2);
+        const long m2 = (long)nn * c8 * r2, m1 = (long)nn * c8 * rt;
+        if (n32 >= 512)
+            k_ulv_wide<DOWN, 2, 2, 4, true><<<wgs(n32), 512, 0, s>>>(a, v, r64, c32, (unsigned)n32);
+        else if (m2 >= 512)
+            k_ulv_mm<DOWN, 2><<<wgs(m2), 512, 0, s>>>(a, v, r2, c8, (unsigned)m2);
         else
-            k_ulv_mm<DOWN, 1><<<wgs(n1), 512, 0, s>>>(a, v, rt, c8, (unsigned)n1);
-    } else if (v.nrhs > 16 && (long)nn * c32 >= 512) {
-        k_ulv_leaf32<DOWN><<<wgs((long)nn * c32), 512, 0, s>>>(a, v, c32, (unsigned)(nn * c32));
-    } else if (v.nrhs > 8 && (long)nn * c16 >= 512) {
-        k_ulv_leaf<DOWN, 2, 2><<<wgs((long)nn * c16), 256, 0, s>>>(a, v, c16, (unsigned)(nn * c16));
+            k_ulv_mm<DOWN, 1><<<wgs(m1), 512, 0, s>>>(a, v, rt, c8, (unsigned)m1);
+    } else if (mmax > 64) {
+        if (v.nrhs <= 8)
+            k_ulv_wide<DOWN, 1, 4, 1, false><<<wgs(n8), 256, 0, s>>>(a, v, r64, c8, (unsigned)n8);
+        else if (by16)
+            k_ulv_wide<DOWN, 1, 4, 2, false><<<wgs(n16), 512, 0, s>>>(a, v, r64, c16, (unsigned)n16);
+        else
+            k_ulv_wide<DOWN, 2, 2, 4, false><<<wgs(n32), 512, 0, s>>>(a, v, r64, c32, (unsigned)n32);
+    } else if (v.nrhs > 16 && n32 >= 512) {
+        if (mmax <= 16)
+            k_ulv_wide<DOWN, 1, 1, 4, false><<<wgs(n32), 256, 0, s>>>(a, v, 1, c32, (unsigned)n32);
+        else if (mmax <= 32)
+            k_ulv_wide<DOWN, 1, 2, 4, false><<<wgs(n32), 512, 0, s>>>(a, v, 1, c32, (unsigned)n32);
+        else if (by16)
+            k_ulv_wide<DOWN, 1, 4, 2, false><<<wgs(n16), 512, 0, s>>>(a, v, 1, c16, (unsigned)n16);
+        else
+            k_ulv_wide<DOWN, 2, 2, 4, false><<<wgs(n32), 512, 0, s>>>(a, v, 1, c32, (unsigned)n32);
+    } else if (v.nrhs > 8 && n16 >= 512) {
+        k_ulv_leaf<DOWN, 2, 2><<<wgs(n16), 256, 0, s>>>(a, v, c16, (unsigned)n16);
     } else {
-        k_ulv_leaf<DOWN, 1, 4><<<wgs((long)nn * c8), 256, 0, s>>>(a, v, c8, (unsigned)(nn * c8));
+        k_ulv_leaf<DOWN, 1, 4><<<wgs(n8), 256, 0, s>>>(a, v, c8, (unsigned)n8);
     }
 }
 
