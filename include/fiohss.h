@@ -221,12 +221,13 @@ fio_status fio_bf_set_tile(fio_bf_t bf, int adj, fio_prec prec, int nrhs, int kc
 /* One tile configuration of an apply (fio_bf_autotune's candidates).  0 everywhere is the
  * built-in default. */
 typedef struct {
-    int kc;        /* dim 2: right-hand sides per wave, 0 (the default, 8), 8 or 16 */
+    int kc;        /* dim 2: right-hand sides per wave, 0 (the default: 8, FP32 with q >= 10 mostly 16), 8 or 16 */
     int nsplit;    /* dim 2: reduction split of the U and V^* steps, 0 or a power of two dividing the
                       partner count, at most 16 */
     int kmax;      /* dim 1: transfer levels per fused pass, 0 (as many as a pass holds) or 1..3 */
     int leaf_sep;  /* dim 1: 1 runs the leaf factors as their own kernels instead of folding them into
-                      the passes next to them */
+                      the passes next to them (q other than 9, and the matrix cores: the first one, into
+                      a first pass of 3 levels) */
     int valu;      /* dim 1, FIO_PREC_SPLIT_FP16 only, with kmax > 0: 1 runs the transfer passes in FP32 on
                       the vector units instead of split FP16 on the matrix cores (kmax = 0 runs the
                       vector units on factors built by the library, the matrix cores on imported ones) */

@@ -531,6 +531,10 @@ template <typename T, int NC, bool VEC> void run_step(K2Args<T> &a, long nout, h
     a.cgroups = a.ldc / (8 * NC);
     const int nrt = (a.rows + 15) / 16, groups = (nrt + 3) / 4, nr = (nrt + groups - 1) / groups;
     const long waves = nout * a.nsplit * a.cgroups;            // per row group
+    if constexpr (sizeof(T) == 4 && NC == 2) {
+        if (nrt == 7 && waves >= kFewWaves) return launch_mm<T, 7, NC, VEC, 1>(a, nout, s);
+        if (nrt == 8 && waves >= kFewWaves) return launch_mm<T, 8, NC, VEC, 1>(a, nout, s);
+    }
     if (nr == 1 || waves * ((nrt + 1) / 2) < kFewWaves)
         launch_mm<T, 1, NC, VEC, 4>(a, nout, s);
     else if (nr == 2 || waves * groups < kFewWaves)
@@ -632,10 +636,14 @@ void apply2k(fio_bf_s *bf, bool adj, const double2 *X, long ldx, double2 *Y, lon
 template <typename T>
 void apply2(fio_bf_s *bf, bool adj, const double2 *X, long ldx, double2 *Y, long ldy, int nrhs, const cpx<T> *F,
             const cpx<T> *Fa, void *ws, bool fint, hipStream_t s) {
-    // columns per wave and reduction split: tuned (fio_bf_autotune) or 8 columns, which pads least (n = 64, 70
-    // columns: 1002 us against 1207 us with 16)
+    // Columns per wave and reduction split: tuned (fio_bf_autotune), or 8 columns, which pad least (n = 64, 70 columns:
+    // 1002 us against 1064 us with 16; where no column is added the tuner takes 16 for large blocks: n = 128, 64
+    // columns 7010 against 6320 us).  FP32 with 7 or 8 row tiles (see run_step): 16, except on the smallest
+    // operators and where a third or more of the columns would be padding.
     const TileCfg c = bf_tile(bf, adj, sizeof(T) == 8 ? FIO_PREC_FP64 : FIO_PREC_FP32, nrhs);
-    if (c.kc == 16)
+    const int c8 = (nrhs + 7) / 8;
+    const bool wide32 = sizeof(T) == 4 && bf->q >= 10 && bf->n1 >= 32 && c8 != 1 && c8 != 3;
+    if (c.kc == 16 || (c.kc == 0 && wide32))
         apply2k<T, 2>(bf, adj, X, ldx, Y, ldy, nrhs, F, Fa, ws, fint, c.nsplit, s);
     else
         apply2k<T, 1>(bf, adj, X, ldx, Y, ldy, nrhs, F, Fa, ws, fint, c.nsplit, s);
