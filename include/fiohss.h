@@ -49,8 +49,9 @@ typedef enum {
 typedef enum {
     FIO_PREC_FP64 = 0,           /* complex128 factors and coefficients */
     FIO_PREC_FP32 = 1,           /* complex64 factors and coefficients, complex128 input/output */
-    FIO_PREC_SPLIT_FP16 = 2      /* transfer blocks and coefficients split into hi + lo fp16 halves,
-                                    MFMA with fp32 accumulation (see fio_bf_apply) */
+    FIO_PREC_SPLIT_FP16 = 2      /* FP32 accuracy by the faster engine: the FP32 passes, or transfer blocks and
+                                    coefficients split into hi + lo fp16 halves on the matrix cores with fp32
+                                    accumulation (see fio_bf_apply) */
 } fio_prec;
 
 typedef enum { FIO_AMP_ONE = 0, FIO_AMP_GAUSSIAN_SUM = 1, FIO_AMP_HANKEL = 2 } fio_amp_kind;
@@ -172,15 +173,19 @@ fio_status fio_bf_workspace_size(fio_bf_t bf, int nrhs, fio_prec prec, size_t *b
  * by the handle (then calls on the handle must not overlap).  X and Y must
  * not overlap.
  * FIO_PREC_SPLIT_FP16 (the growth direction of the refinement's low-precision
- * K~^*): every transfer block a and its input coefficients x are split into
+ * K~^*): on factors built by the library the default is the FP32 apply, which is
+ * faster at every width and more exact.  Imported factors, and built ones where a
+ * tile configuration selects the matrix cores (fio_tile: kmax > 0, valu = 0), run
+ * split: every transfer block a and its input coefficients x are split into
  * half-precision parts a_hi + a_lo, x_hi + x_lo, and a x is formed on the matrix
  * cores as a_hi x_hi + a_hi x_lo + a_lo x_hi with FP32 accumulation; each
  * column is scaled by a power of two per pass so that its entries sit well
  * inside half range (any FP32-representable input scale works).  The middle
  * factor is folded into the neighbouring transfer level (FP64 products before
  * the split); leaf factors and the coefficient buffers between passes are
- * FP32.  Accuracy is that of FP32 (about 1e-6 relative per apply).  A
- * FIO_ERR_ARG is returned when the handle holds no such copy. */
+ * FP32, and so is a first pass of 3 levels that a leaf factor folds into.
+ * Accuracy is that of FP32 (about 1e-6 relative per apply).  A FIO_ERR_ARG is
+ * returned when the handle holds no such copy. */
 fio_status fio_bf_apply(fio_bf_t bf, const void *X, long ldx, void *Y, long ldy, int nrhs,
                         fio_prec prec, void *ws, size_t ws_bytes, void *stream);
 
@@ -196,12 +201,13 @@ fio_status fio_bf_apply_adj(fio_bf_t bf, const void *X, long ldx, void *Y, long 
  * two of nrhs, all counts >= 64 in one bucket) and precision use it.  Candidates: for dim = 2
  * the column chunk of the workgroups (8 or 16) times the reduction split of the U and V^*
  * steps (4, 8, 16 dividing the partner count); for dim = 1 (q = 9) the number of transfer
- * levels per fused pass (1, 2, 3), with 3 levels the leaf factors folded into the passes
- * or run as their own kernels, and for FIO_PREC_SPLIT_FP16 each of these with the transfer passes
- * on the matrix cores (split FP16) or on the vector units (FP32); the built-in default (whole sides
- * per pass, on the vector units) is always a candidate (fio_tile describes a candidate).  Every candidate applies the same operator
- * (results differ at most by rounding order, and the FP32 engine is the more accurate one of a
- * split-precision request).  Y (ldy >= N)
+ * levels per fused pass (1, 2, 3), with 3 levels the leaf factors folded into the passes or run as
+ * their own kernels, and for FIO_PREC_SPLIT_FP16 each of these on the matrix cores (split FP16)
+ * and on the vector units (FP32); on factors built by the library also whole sides per pass with
+ * the leaf factors as their own kernels.  The built-in default (whole sides, on the vector units,
+ * for built factors) is always a candidate (fio_tile describes a candidate).  Every candidate
+ * applies the same operator (results differ at most by rounding order, and the FP32 engine is the
+ * more accurate one of a split-precision request).  Y (ldy >= N)
  * receives the last apply; `ws` as for fio_bf_apply (NULL: the handle's workspace).  When
  * `report` is not NULL, a NUL-terminated summary of the timings and the choices is written to
  * it (at most report_len bytes).  Synchronous.  Must not run concurrently with applies on the

@@ -6,12 +6,12 @@
 
 namespace fio {
 // Tile configuration of the applies for one (direction, precision, column bucket); 0 = the
-// built-in default.  kc: 2D column chunk (8 or 16); nsplit: 2D reduction split of the U / V^*
+// built-in default.  kc: 2D columns per wave (8 or 16); nsplit: 2D reduction split of the U / V^*
 // steps; kmax: 1D levels per fused pass.
 struct TileCfg {
     int kc = 0, nsplit = 0, kmax = 0;
-    int leaf_sep = 0;   // 1D: run the first leaf factor as its own kernel (no fold into the first pass)
-    int valu = 0;       // 1D split FP16: run the transfer passes as FP32 structured passes (vector units)
+    int leaf_sep = 0;   // 1D: run the leaf factors as their own kernels (no fold into the passes next to them)
+    int valu = 0;       // 1D split FP16: run the transfer passes in FP32 on the vector units
 };
 // Section 5.1's Gaussian-sum amplitude (m = 0: a = 1), passed to the factor generation by value
 constexpr int kMaxAmpTerms = 16;

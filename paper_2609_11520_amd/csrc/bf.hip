@@ -423,9 +423,10 @@ static std::vector<TileCfg> tile_candidates(const fio_bf_s *bf, fio_prec prec) {
             for (int ns : {4, 8, 16})
                 if (ns <= nmax && T % ns == 0) c.push_back(TileCfg{kc, ns, 0});
     } else if (bf->nl > 0 && bf->q == 9) {
-        // levels per fused pass; with 3, the first leaf factor folded in or run on its own; in
-        // split precision, each of these with the transfer passes on the matrix cores (split
-        // FP16) or on the vector units (FP32, the more accurate of the two)
+        // whole sides with the leaf factors on their own; levels per fused pass; with 3, the leaf
+        // factors folded in or run on their own; in split precision, each of these with the transfer
+        // passes on the matrix cores (split FP16) or on the vector units (FP32, the more accurate)
+        if (side_built(bf)) c.push_back(TileCfg{0, 0, 0, 1});
         for (int valu : {0, 1}) {
             if (valu && prec != FIO_PREC_SPLIT_FP16) continue;
             for (int km : {1, 2, 3}) c.push_back(TileCfg{0, 0, km, 0, valu});

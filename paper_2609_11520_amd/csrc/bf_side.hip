@@ -1010,9 +1010,11 @@ void side_apply(const fio_bf_s *bf, bool adj, const double2 *X, long ldx, double
     // coarse partners in turn, so it needs enough of them to keep the card busy.  Measured in-pass against
     // a leaf kernel of its own (FP64 / FP32 ms of an apply, 64 columns unless noted): adjoint N = 2^18 3.42 /
     // 1.80 against 4.02 / 2.08, 2^16 0.78 / 0.43 against 0.84 / 0.49, 2^18 with 16 columns (1024 workgroups)
-    // 0.88 / 0.50 against 0.96 / 0.53, 2^14 (1024 one-wave workgroups) 0.20 / 0.13 against 0.21 / 0.12;
-    // forward (whose FP64 form spills) 2^18 3.49 / 1.83 against 3.60 / 2.01, 2^16 (2048 workgroups) 0.87 / 0.46
-    // against 0.80 / 0.46, 2^18 with 32 columns 1.80 / 0.94 against 1.78 / 1.01.
+    // 0.88 / 0.50 against 0.96 / 0.53, 2^14 (4 levels, 1024 one-wave workgroups) 0.20 / 0.13 against 0.21 / 0.12,
+    // the same: hence at least 5 levels; forward 2^18 3.49 / 1.83 against 3.60 / 2.01, 2^16 (2048 workgroups)
+    // 0.87 / 0.46 against 0.80 / 0.46, 2^18 with 32 columns 1.80 / 0.94 against 1.78 / 1.01.  The in-pass forms
+    // hold 16 row sums beside the two pairs and spill: forward 99 registers a lane in FP64 and 30 in FP32, adjoint
+    // 75 and 10 (of the others, the FP64 adjoint B side 14 and the FP32 forward B side 4).
     const long groups = ((long)1 << bf->h) * o.nch;
     const bool out = !leaf_sep && step >= nl && nl >= 5 && groups >= (adj ? 1024 : sizeof(T) == 8 ? 4096 : 2048);
     for (int done = 0; done < nl;) {

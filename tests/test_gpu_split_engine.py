@@ -88,3 +88,16 @@ def test_refinement_on_the_matrix_cores():
     assert ran["bf_split16"] >= 6 and info.rel_res <= 5e-9
     err = np.linalg.norm(host(fr) - f, axis=0) / np.linalg.norm(f, axis=0)
     assert err.max() < 1e-8
+
+
+def test_whole_sides_with_separate_leaves_are_a_candidate():
+    # 2^16 has 5 levels a side, more than any pinned pass length: the choice between leaf factors in the whole-side
+    # passes and on their own is one of the tuner's
+    F = fiohss()
+    n, k = 1 << 16, 64
+    step("autotune candidates n=2^16")
+    B = gpu_bf(F, n, 9, "sin16", imported=False, precs=(F.FIO_PREC_FP64, F.FIO_PREC_FP32, SPLIT))
+    X = dev(fi.complex_gaussian(43, fi.PURPOSE_PROBE, n, k))
+    for prec in (F.FIO_PREC_FP64, F.FIO_PREC_FP32, SPLIT):
+        rep = B.autotune(X, prec=prec, reps=1)
+        assert "kmax=0 leaf_sep=0 valu=0" in rep and "kmax=0 leaf_sep=1 valu=0" in rep
