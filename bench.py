@@ -13,12 +13,13 @@ as the headline, and the run exits with status 3 if the headline misses it):
   fp64  : K~^* and K~ applied in FP64;
   mixed : K~^* applied in FP32 (FP32 factors and coefficients), residual K~ f and
           the ULV solve in FP64;
-  split16: as mixed, with the transfer factors of K~^* applied on the matrix cores
-          in split FP16 (hi + lo halves, FP32 accumulation).
+  split16: as mixed, in split precision: by default and as tuned the FP32 passes, or the
+          transfer factors of K~^* on the matrix cores in split FP16 (hi + lo halves, FP32
+          accumulation); `dtype` and `split_precision_engines` name what ran.
 `value` is the faster mixed path's RHS/s (64 / seconds per step; `config.mixed_variant`
 names it); the FP64 path and the other mixed path are reported beside it.  Offline work
 (BF, HSS and ULV construction) happens before the timed region; inputs are resident in
-HBM when it starts.  Also reported: `roofline` (explicit-form work of the dominant
+HBM when it starts.  Also reported: `roofline` (the algorithmic work of the dominant
 kernel against the published peaks, spill and counter traffic beside it), the serving
 workload in split-FP16 and FP64 at 200 requests/s and at a saturating rate, the N = 2^16
 direct FP64 solve (with c = 0), the 2D and variable-amplitude workloads, and the oracle
@@ -56,7 +57,7 @@ def kernel_source_hash():
     """Hash of the butterfly apply kernels' source; stored counter traffic is valid only for it."""
     import hashlib
     h = hashlib.sha256()
-    for f in ("bf_apply.h", "bf_apply_f64.hip", "bf_apply_f32.hip", "bf_lowprec.hip"):
+    for f in ("bf_apply.h", "bf_apply_f64.hip", "bf_apply_f32.hip", "bf_lowprec.hip", "bf_side.h", "bf_side.hip"):
         with open(os.path.join(ROOT, "paper_2609_11520_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
@@ -119,7 +120,18 @@ def traffic_from(fetch_dir, write_dir, n=1 << 18, k=64, q=9, out_path=None):
         raise SystemExit("the 1 GiB calibration copy was not found in the counter runs")
     fs, ws = one_gib_kib / max(copies), one_gib_kib / max(cf)
     tiles = n >> 3
+    # whole sides: 2^nl pairs and 8 columns per workgroup; the passes that end in the output rows run 8 partners each
+    nl = sum(kl for kl, _ in pass_plan(n)) // 2
+    side = (n >> nl) * (-(-k // 8)) * (4 << nl)
+
+    def side_pass(t, *forms):
+        return lambda nm: any("k_side_pass<%s, %s>" % (t, f) in nm for f in forms)
+    first, last = ("true, false, false", "false, true, false"), ("false, false, true", "true, true, true")
     labels = {
+        "bf_side_in_f64": (side_pass("double", *first), side),
+        "bf_side_in_f32": (side_pass("float", *first), side),
+        "bf_side_out_f64": (side_pass("double", *last), side // 8),
+        "bf_side_out_f32": (side_pass("float", *last), side // 8),
         "bf_split16": (lambda nm: nm.startswith("void fio::(anonymous namespace)::k_split_fused<3,")
                        or "k_split_fused<3," in nm, tiles * 512),
         "bf_struct_f64": (lambda nm: "k_struct_fused<double, 9, 3," in nm and nm.split(">")[0].endswith("false"), tiles * 512),
@@ -131,8 +143,8 @@ def traffic_from(fetch_dir, write_dir, n=1 << 18, k=64, q=9, out_path=None):
     }
     out = {"source_hash": kernel_source_hash(), "fetch_scale": fs, "write_scale": ws, "kernels": {},
            "note": "hbm_bytes_per_launch: FETCH_SIZE x fetch_scale + WRITE_SIZE x write_scale per launch "
-                   "(KiB -> bytes), N=2^%d, %d RHS; algorithmic and spill bytes per launch by the explicit-form "
-                   "model of bench.kernel_model" % (int(np.log2(n)), k)}
+                   "(KiB -> bytes), N=2^%d, %d RHS; algorithmic and spill bytes per launch by "
+                   "bench.kernel_model" % (int(np.log2(n)), k)}
     rows = []
     for lab, (match, grid) in labels.items():
         ds = [d for d, (nm, g, _) in write.items() if match(nm) and g == grid and d in fetch]
@@ -154,7 +166,7 @@ def traffic_from(fetch_dir, write_dir, n=1 << 18, k=64, q=9, out_path=None):
         json.dump(out, fh, indent=1)
     print("calibration: FETCH_SIZE x %.4f, WRITE_SIZE x %.4f (1 GiB copy)" % (fs, ws))
     print()
-    print("| kernel | dispatches | FETCH_SIZE KiB | WRITE_SIZE KiB | HBM bytes | explicit-form bytes | ratio | spill bytes |")
+    print("| kernel | dispatches | FETCH_SIZE KiB | WRITE_SIZE KiB | HBM bytes | algorithmic bytes | ratio | spill bytes |")
     print("|---|---|---|---|---|---|---|---|")
     for lab, nd, fk, wk, hb, ab, sb in rows:
         print("| %s | %d | %.0f | %.0f | %.3e | %s | %s | %s |" % (
@@ -181,17 +193,20 @@ def pass_plan(n, kmax=3):
 
 
 def kernel_model(name, n, q, k):
-    """Algorithmic work per launch of the butterfly kernels, by the explicit-factor count:
-    (bytes, flops, spill_bytes, peak_tflops).
+    """Algorithmic work per launch of the butterfly kernels: (bytes, flops, spill_bytes, peak_tflops).
 
-    The method's work is the product with the explicit factors of eq. bf: every entry read once
-    per apply (16 B in FP64, 8 B in FP32 or as split-FP16 hi + lo halves) and a complex
-    multiply-add (8 flops) per entry and column; the three split products count 3 x 8.  A
-    structured pass (3 transfer levels of (N/2) 4q^2 entries each, plus M's N q^2 on the pass that
-    applies it) is charged those entries whatever form the kernel reads them in.  The N x k
-    vectors read and written by an apply (2 N k 16 B) belong to its leaf kernels; the per-pass
-    round trip of the coefficient block (2 N q k e) is an implementation cost, reported apart as
-    spill_bytes."""
+    Kernels that read the explicit factors of eq. bf, and the split and per-pair twiddle passes, are
+    priced by the explicit-factor count: every entry read once per apply (16 B in FP64, 8 B in FP32 or
+    as split-FP16 hi + lo halves) and a complex multiply-add (8 flops) per entry and column; the three
+    split products count 3 x 8.  A pass of 3 transfer levels of (N/2) 4q^2 entries each, plus M's N q^2
+    on the pass that applies it, is charged those entries whatever form the kernel reads them in.
+    Whole-side passes ("bf_side") multiply far fewer: they are priced by the real products that their
+    form cannot do without, 2 x 2 q^2 multiply-adds per transfer group and column (both children share
+    one product per child), 8 q per leaf pair, 16 q per middle pair (half of it per pass), and by the
+    vectors and the leaf table; their other tables fit the caches.
+    The N x k vectors read and written by an apply (2 N k 16 B) belong to its leaf kernels, or to
+    the passes that read and write them; the round trips of the coefficient block (N q k e each way) are an
+    implementation cost, reported apart as spill_bytes."""
     e = 16 if name.endswith("f64") else 8
     plan = pass_plan(n)
     transfer = (n // 2) * 4 * q * q              # entries of one transfer level
@@ -203,19 +218,29 @@ def kernel_model(name, n, q, k):
             FP64_PEAK_TFLOPS if e == 16 else FP32_PEAK_TFLOPS)
         return ent * e, mult * 8.0 * ent * k, 2.0 * n * q * k * (8 if name == "bf_split16" else e), peak
     if name.startswith("bf_side"):
-        # a whole-side pass: all transfer levels of one side, half of M (one of the two passes applies it)
-        # and, where it also reads or writes the vectors, the side's leaf blocks; the coefficient block
-        # is written by one pass and read by the other
-        ent = sum(kl for kl, _ in plan) // 2 * transfer + mid / 2 + (8 * q * n if "_in_" in name or "_out_" in name else 0)
-        return ent * e, 8.0 * ent * k, 1.0 * n * q * k * e, FP64_PEAK_TFLOPS if e == 16 else FP32_PEAK_TFLOPS
+        nl = sum(kl for kl, _ in plan) // 2
+        ends = "_in_" in name or "_out_" in name
+        flops = k * (nl * (n / 2) * 8.0 * q * q + (16.0 * q * n if ends else 0.0) + 16.0 * q * n)
+        return (16 * n * k + 4 * n * e if ends else 0), flops, 1.0 * n * q * k * e, (
+            FP64_PEAK_TFLOPS if e == 16 else FP32_PEAK_TFLOPS)
     if name.startswith("bf_transfer"):
         return transfer * e, 8.0 * transfer * k, 2.0 * n * q * k * e, FP64_PEAK_TFLOPS if e == 16 else FP32_PEAK_TFLOPS
     return None
 
 
+def engine_of(kernels):
+    """The engine of a split-precision apply, from the names of the kernels that ran."""
+    return "mfma" if "bf_split16" in kernels else "valu"
+
+
+def compute_dtype(head, kernels):
+    """The compute types of the headline variant, from the kernels that its timed steps ran."""
+    return "fp16x2+fp32+fp64" if head == "split16" and engine_of(kernels) == "mfma" else "fp32+fp64"
+
+
 def roofline_of(name, n, q, k, avg_ms, traffic):
-    """The roofline record of one kernel: bound = the larger of the explicit-factor byte and flop
-    times at the published peaks; frac = bound time / measured time."""
+    """The roofline record of one kernel: bound = the larger of the byte and flop times of kernel_model
+    at the published peaks; frac = bound time / measured time."""
     m = kernel_model(name, n, q, k)
     if m is None:
         return None
@@ -233,7 +258,7 @@ def roofline_of(name, n, q, k, avg_ms, traffic):
               "algorithmic_bytes_per_launch": int(byts), "algorithmic_flops_per_launch": float(flops),
               "spill_bytes_per_launch": int(spill),
               "achieved_with_spill_gbs": round((byts + spill) / (avg_ms * 1e-3) / 1e9, 1),
-              "traffic_over_algorithmic": None if traffic is None else round(traffic / byts, 3)})
+              "traffic_over_algorithmic": None if traffic is None or not byts else round(traffic / byts, 3)})
     if name.endswith("f32"):
         r["fp32_nonpacked_peak"] = FP32_NONPACKED_TFLOPS
     return r
@@ -822,16 +847,14 @@ def main():
             with open(a.tune_file, "w") as fh:
                 fh.write(B.tune_export())
     log("autotuned tiles (%s)" % tune_source, json.dumps(tuned))
-    # the split-precision K~^* apply with each engine pinned (matrix cores: split-FP16 passes;
-    # vector units: FP32 structured passes), whatever the tuner chose, so that both engines are
-    # measured on every run; the tuned configuration is restored afterwards
+    # the split-precision K~^* apply with each engine (matrix cores: split-FP16 passes of 3 levels,
+    # pinned; vector units: the FP32 whole-side passes, the default), whatever the tuner chose, so
+    # that both engines are measured on every run, and the tuned configuration, to name its engine
     split_engines = {}
     tuned_adj = B.get_tile(k, prec=F.FIO_PREC_SPLIT_FP16, adj=True)
     wsa = torch.empty(B.workspace_size(k, F.FIO_PREC_SPLIT_FP16), dtype=torch.uint8, device=dev)
     ya = F.empty(n, k)
-    for eng, valu in (("mfma", 0), ("valu", 1)):
-        cfg = dict(tuned_adj)
-        cfg.update(kmax=3, valu=valu)
+    for eng, cfg in (("mfma", dict(kmax=3)), ("valu", {}), ("tuned", tuned_adj)):
         B.set_tile(k, F.FIO_PREC_SPLIT_FP16, True, **cfg)
         for _ in range(2):
             B.apply_adj(u, prec=F.FIO_PREC_SPLIT_FP16, out=ya, ws=wsa)
@@ -845,15 +868,14 @@ def main():
         e1.record()
         sync()
         F.timing_enable(False)
-        rec = {"apply_ms": round(e0.elapsed_time(e1) / 10, 4)}
-        pk = "bf_split16" if valu == 0 else "bf_struct_f32"
-        cnt, ms = F.timing_query(pk)
-        if cnt:
-            rec["pass_kernel"] = pk
-            rec["roofline"] = roofline_of(pk, n, q, k, ms / cnt, stored_traffic(pk))
-        split_engines[eng] = rec
-    B.set_tile(k, F.FIO_PREC_SPLIT_FP16, True, **tuned_adj)
-    split_engines["tuned_adjoint_engine"] = "valu" if tuned_adj["valu"] else "mfma"
+        ran = {kn: F.timing_query(kn) for kn in F.timing_names()}
+        if eng == "tuned":
+            split_engines["tuned_adjoint_engine"] = engine_of(ran)
+            continue
+        pk = max(ran, key=lambda kn: ran[kn][1])         # the kernel that takes most of the apply
+        split_engines[eng] = {"apply_ms": round(e0.elapsed_time(e1) / 10, 4), "pass_kernel": pk,
+                              "kernels": sorted(ran), "engine": engine_of(ran),
+                              "roofline": roofline_of(pk, n, q, k, ran[pk][1] / ran[pk][0], stored_traffic(pk))}
     del ya, wsa
     log("split-precision K~^* engines", json.dumps(split_engines))
 
@@ -1056,8 +1078,7 @@ def main():
     line = {
         "metric": METRIC, "value": round(mixed["value"], 2), "unit": "RHS/s", "n_gpus": 1, "steps": a.steps,
         "warmup": a.warmup, "ms_per_step": round(mixed["ms_per_step"], 3), "higher_is_better": True,
-        "scaling": "weak", "vs_baseline": None, "dtype": ("fp16x2+fp32+fp64" if head == "split16" and split_engines["tuned_adjoint_engine"] == "mfma"
-                  else "fp32+fp64"),
+        "scaling": "weak", "vs_baseline": None, "dtype": compute_dtype(head, kernel_stats[head]),
         "data": "synthetic",
         "config": {"workload": "1D FIO N=2^%d, c(x)=(2+sin 2pi x)/16, q=%d, HSS tol %g, p=10, %d RHS, "
                                "refinement steps calibrated to rel residual %g" % (int(np.log2(n)), q, a.hss_tol, k,
