@@ -571,26 +571,43 @@ template <typename T, bool ADJ, typename V> FIO_SIDE_FN void side_middle(V m, cp
     }
 }
 
-// middle block of one pair with an amplitude (its entries 64 apart at m)
-template <typename T, bool ADJ> FIO_SIDE_FN void side_middle_full(const cpx<T> *m, cpx<T> (&x)[9]) {
+// Middle blocks of the thread's two pairs with an amplitude: entries 64 apart at m, those of the second pair next to
+// the first's (in FP32 one load for both).  The loads bound it: one pair after the other, N = 2^16 forward, 64
+// columns, took 1430 us in FP64 (1370 with 64-column tiles and scalar loads), both at once 1280 us.
+template <typename T> struct MidPair {
+    cpx<T> a, b;
+};
+FIO_SIDE_FN MidPair<float> mid_pair(const float2 *m) {
+    const float4 v = *reinterpret_cast<const float4 *>(m);
+    return {make_float2(v.x, v.y), make_float2(v.z, v.w)};
+}
+FIO_SIDE_FN MidPair<double> mid_pair(const double2 *m) { return {m[0], m[1]}; }
+
+template <typename T, bool ADJ> FIO_SIDE_FN void side_middle_full(const cpx<T> *m, cpx<T> (&x0)[9], cpx<T> (&x1)[9]) {
     using C = cpx<T>;
-    C y[9];
+    C y0[9], y1[9];
 #pragma unroll
-    for (int i = 0; i < 9; ++i) y[i] = czero<C>();
+    for (int i = 0; i < 9; ++i) y0[i] = y1[i] = czero<C>();
 #pragma unroll
     for (int i = 0; i < 9; ++i) {
         load_fence();
 #pragma unroll
         for (int j = 0; j < 9; ++j) {
-            const C v = m[(i * 9 + j) * 64];
-            if constexpr (ADJ)
-                cfmac(y[j], v, x[i]);
-            else
-                cfma(y[i], v, x[j]);
+            const MidPair<T> v = mid_pair(m + (i * 9 + j) * 64);
+            if constexpr (ADJ) {
+                cfmac(y0[j], v.a, x0[i]);
+                cfmac(y1[j], v.b, x1[i]);
+            } else {
+                cfma(y0[i], v.a, x0[j]);
+                cfma(y1[i], v.b, x1[j]);
+            }
         }
     }
 #pragma unroll
-    for (int i = 0; i < 9; ++i) x[i] = y[i];
+    for (int i = 0; i < 9; ++i) {
+        x0[i] = y0[i];
+        x1[i] = y1[i];
+    }
 }
 
 template <typename T, bool ADJ>
@@ -598,9 +615,7 @@ FIO_SIDE_FN void side_apply_mid(const SideArgs<T> &a, unsigned box, unsigned neg
                                 cpx<T> (&x1)[9]) {
     if (a.mid == kSideEMamp) {
         const cpx<T> *m = a.M + (pair >> 6) * kSideEMamp * 64 + (pair & 63);
-        side_middle_full<T, ADJ>(m, x0);
-        load_fence();
-        side_middle_full<T, ADJ>(m + 1, x1);
+        side_middle_full<T, ADJ>(m, x0, x1);
     } else if (a.nsb == 1) {
         const int o = __builtin_amdgcn_readfirstlane((int)(box * 2 + neg) * kSideEM);
         side_middle<T, ADJ>((scalar_ptr<T>)(uintptr_t)(a.M + o), x0, x1);
@@ -1015,8 +1030,11 @@ void side_apply(const fio_bf_s *bf, bool adj, const double2 *X, long ldx, double
     // 0.87 / 0.46 against 0.80 / 0.46, 2^18 with 32 columns 1.80 / 0.94 against 1.78 / 1.01.  The in-pass forms
     // hold 16 row sums beside the two pairs and spill: forward 99 registers a lane in FP64 and 30 in FP32, adjoint
     // 75 and 10 (of the others, the FP64 adjoint B side 14 and the FP32 forward B side 4).
+    // With an amplitude the FP32 forward one also reads two blocks of 81 entries per partner and column chunk: 2^16
+    // with 64 / 150 columns 0.91 / 1.83 against 0.54 / 1.33, 2^18 3.17 against 2.29: never.
     const long groups = ((long)1 << bf->h) * o.nch;
-    const bool out = !leaf_sep && step >= nl && nl >= 5 && groups >= (adj ? 1024 : sizeof(T) == 8 ? 4096 : 2048);
+    const bool out = !leaf_sep && step >= nl && nl >= 5 && groups >= (adj ? 1024 : sizeof(T) == 8 ? 4096 : 2048) &&
+                     (adj || sizeof(T) == 8 || o.mid != kSideEMamp);
     for (int done = 0; done < nl;) {
         const int n = nl - done < step ? nl - done : step;
         o.in = cur;
