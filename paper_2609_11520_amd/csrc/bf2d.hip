@@ -30,8 +30,8 @@
 // q^2 coefficients, or a leaf box's b^2 values) for 8 or 16 right-hand sides and runs the products on the
 // matrix cores.  The leaf-box sums over 4^lc blocks are split over waves and reduced in a fixed
 // order; every column is summed in the same order at any width and split of rows (deterministic
-// results).  Few columns: the factor stream bounds it (n = 128, 8 columns: 9.6 GB in 1.90 ms, 5.0 TB/s; one
-// lane per row took 1.97 ms).  Many columns: the FP64 matrix rate (n = 64, 144 columns: 46 of 75
+// results).  Few columns: the factor stream bounds it (n = 128, 8 columns: 9.6 GB in 1.83 ms, 5.2 TB/s; one
+// lane per row took 1.89 ms, no more than runs differ by).  Many columns: the FP64 matrix rate (n = 64, 144 columns: 46 of 75
 // TFLOP/s with the 81 rows padded to 96; one lane per row reached 24).  In between the launches of few, long waves: n = 8
 // 105 -> 27 us, n = 16 80 -> 26 us at 8 columns.
 //

@@ -9,8 +9,9 @@
 //   W = [L11^{-1} Q1^*; Q2^* - Dhat21 L11^{-1} Q1^*]
 // so that the bottom-up step is [bhat1; yhat2] = W y_tau and the top-down step is
 // c_tau = W^* [bhat1; chat2]; the root keeps Linv = L_rho^{-1}.  The online solve
-// is therefore one batched product per level and direction (k_ulv_mm), with the levels of small
-// nodes in bands of up to four (k_ulv_band).
+// is therefore one batched product per level and direction (k_ulv_leaf for leaves of up to 64 rows,
+// k_ulv_mm for larger nodes, k_ulv_wide for wide blocks and many nodes), with the levels of small nodes
+// in bands of up to four (k_ulv_band).
 #include "hss.h"
 #include "hss_qr.h"
 #include "mat4.h"
